@@ -88,11 +88,10 @@ extern "C" {
                                 sources supported on the interfaces, only the
                                 boundary values needed)                       */
 #define HELM_FLAG_GEMM_4M 512 /* complex64 substitution GEMMs form each complex
-                                product from four real matrix-core products;
-                                by default they take three (Pr Qr, Pi Qi and
-                                (Pr + Pi)(Qr + Qi)), whose rounding error is
-                                bounded in norm rather than per component.
-                                No effect on HELM_FP64 handles               */
+                                product from four real ones.  They always do
+                                (each real product from bf16 products of
+                                exactly split floats, at FP32 accuracy), so
+                                the flag changes nothing                     */
 #define HELM_FLAG_FACTOR_4M 1024 /* the complex64 factorization's sweep GEMM
                                 forms each complex product from four real
                                 products (default: three, as the

@@ -159,9 +159,8 @@ struct Handle {
   // the forward substitution GEMM only), one bit per KClass
   unsigned profile_mask = 0;
   void set_profile(int flags);
-  // three-product complex64 GEMMs: substitutions (unless HELM_FLAG_GEMM_4M),
-  // factorization sweep (unless HELM_FLAG_FACTOR_4M)
-  bool gemm3m = false, factor3m = false;
+  // three-product complex64 factorization sweep (unless HELM_FLAG_FACTOR_4M)
+  bool factor3m = false;
   bool profile() const { return profile_mask != 0; }
   KStat kstats[K_NCLASS];
   std::vector<PendingEvent> pending;

@@ -13,6 +13,7 @@
 
 #include "kernels.h"
 #include "kernels_common.h"
+#include "kernels_split.h"
 
 namespace helm {
 namespace kern {
@@ -104,17 +105,18 @@ k_fwd_gather(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   }
 }
 
-// Occupancy floor (waves per SIMD) asked of the compiler for the
-// substitution GEMM tiles: 4 for the complex64 tiles, which then fit in 128
-// registers without spilling (at its default the compiler spends up to
-// ~160 on hoisting LDS reads and drops to 3 waves, which measured slower);
-// 3 for the three-product 64 x 64 tile (2 at the compiler's default); no
-// floor for the four-product 64 x 64 and the complex128 tiles, which would
-// spill.
-template <typename T, int BM, int BN, bool M3> constexpr int gemm_waves() {
-  if (sizeof(T) != 4) return 1;
-  if (BM == 64 && BN == 64) return M3 ? 3 : 1;
-  return 4;
+// Partial products of a split front: rows [m0, ...) < n of chunk `chunk`.
+template <typename T, class O, class Acc>
+__device__ __forceinline__ void store_partial(const Acc& acc, C_t<T>* S, long long row0, int m0,
+                                              int n0, int n, int k) {
+  const O o;
+#pragma unroll
+  for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+    for (int j = 0; j < O::NC; ++j) {
+      const int gm = m0 + o.r[i], gc = n0 + o.c[j];
+      if (gm < n && gc < k) st(S + (row0 + gm) * k + gc, acc_at(acc, i, j));
+    }
 }
 
 // Forward GEMM epilogue of an unsplit front: pivot rows to Z, boundary rows
@@ -122,12 +124,11 @@ template <typename T, int BM, int BN, bool M3> constexpr int gemm_waves() {
 // all of this lane's outputs are loaded first, then the child values, then
 // the results are stored, so that the latencies of each group of loads
 // overlap instead of following one another output by output.
-template <typename T, int BM, int BN, bool M3>
-__device__ __forceinline__ void fwd_epilogue(const WaveAcc<T, BM, BN, M3>& acc, const FrontDev& f,
+template <typename T, class O, class Acc>
+__device__ __forceinline__ void fwd_epilogue(const Acc& acc, const FrontDev& f,
                                              const ChildSum<T>& cs, C_t<T>* Z, C_t<T>* Uo,
                                              int m0, int n0, int k) {
   using C = C_t<T>;
-  using O = LaneOut<T, BM, BN>;
   const O o;
   const int n = f.s + f.b;
   int q[2][O::NR];
@@ -170,15 +171,16 @@ __device__ __forceinline__ void fwd_epilogue(const WaveAcc<T, BM, BN, M3>& acc, 
 
 // forward, step 2: [X(S); Ub] = [F11^-1 w_S; Ub - F21 F11^-1 w_S], the K
 // (pivot) dimension optionally split into chunks (partials to scratch).
-// M3: the three-product complex form (complex64 only).
-template <typename T, int BN, bool M3>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(gemm_waves<T, FWD_BM, BN, M3>(), 8)))
+// complex128 on the FP64 matrix cores, complex64 on the split tile.
+template <typename T> constexpr bool split_form() { return sizeof(T) == 4; }
+
+template <typename T, int BN>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(split_form<T>() ? 3 : 1, 8)))
 k_fwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
            const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
            const LayerDev* __restrict__ layers, int k, void* scratch) {
   using C = C_t<T>;
   constexpr int BM = FWD_BM;
-  __shared__ GemmSmem<T, BM, BN, true, M3> sm;
   const int ntn = (k + BN - 1) / BN;
   const int mt = blockIdx.x / ntn, nt = blockIdx.x % ntn;
   const int2 tm = tmap[mt];
@@ -193,23 +195,31 @@ k_fwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const int m0 = (local / tk.nch_f) * BM, n0 = nt * BN;
   const int kb = chunk * tk.kc_f;
   const int ke = min(f.s, kb + tk.kc_f);
-  const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
   // P = FT (col-major, rows m), Q = X(S) (rows = pivots, columns = RHS)
-  const C* X = reinterpret_cast<const C*>(L.X);
-  View<T> pv{FT, 1, (long long)n, n, f.s};
-  View<T> qv{X + (long long)f.off * k, 1, (long long)k, k, f.s};
-  WaveAcc<T, BM, BN, M3> acc;
-  gemm_tile<T, BM, true, true>(sm, acc, pv, qv, m0, n0, kb, ke);
-  if (tk.nch_f > 1) {
-    C* S = reinterpret_cast<C*>(scratch);
-    for_each_acc<T, BM>(acc, [&](int r, int c, C z) {
-      const int gm = m0 + r, gc = n0 + c;
-      if (gm < n && gc < k) st(S + (tk.scr_f + (long long)chunk * n + gm) * k + gc, z);
-    });
-    return;
+  const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
+  const C* X = reinterpret_cast<const C*>(L.X) + (long long)f.off * k;
+  auto finish = [&](const auto& acc, auto out) {
+    using O = decltype(out);
+    if (tk.nch_f > 1)
+      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), tk.scr_f + (long long)chunk * n, m0,
+                          n0, n, k);
+    else
+      fwd_epilogue<T, O>(acc, f, ChildSum<T>(fronts, f, L, raw), reinterpret_cast<C*>(L.Wt),
+                         ub_ptr<T>(L, f.ub_parity), m0, n0, k);
+  };
+  if constexpr (split_form<T>()) {
+    __shared__ SplitSmem<BN> sm;
+    SplitAcc<BM, BN> acc;
+    split_tile<BM, BN, false, false>(sm, acc, SplitP{FT, n, n}, SplitQ{X, k, k, nullptr}, m0, n0,
+                                     kb, ke);
+    finish(acc, SplitOut<BM, BN>());
+  } else {
+    __shared__ GemmSmem<T, BM, BN, true> sm;
+    WaveAcc<T, BM, BN> acc;
+    gemm_tile<T, BM, true, true>(sm, acc, View<T>{FT, 1, (long long)n, n, f.s},
+                                 View<T>{X, 1, (long long)k, k, f.s}, m0, n0, kb, ke);
+    finish(acc, LaneOut<T, BM, BN>());
   }
-  fwd_epilogue<T, BM, BN>(acc, f, ChildSum<T>(fronts, f, L, raw), reinterpret_cast<C*>(L.Wt),
-                          ub_ptr<T>(L, f.ub_parity), m0, n0, k);
 }
 
 // elements per thread and pass of the split-K reductions
@@ -262,13 +272,12 @@ k_fwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // backward: X(S) = Z(S) + (-F21 F11^-1)^T X(B); X(B) is read in place
 // through the front's boundary index list, the K (boundary) dimension
 // optionally split.  Fronts without boundary (roots) just copy Z(S).
-template <typename T, int BM, int BN, bool M3>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(gemm_waves<T, BM, BN, M3>(), 8)))
+template <typename T, int BM, int BN>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(split_form<T>() ? 3 : 1, 8)))
 k_bwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
            const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
            const LayerDev* __restrict__ layers, int k, void* scratch) {
   using C = C_t<T>;
-  __shared__ GemmSmem<T, BM, BN, false, M3> sm;
   const int ntn = (k + BN - 1) / BN;
   const int mt = blockIdx.x / ntn, nt = blockIdx.x % ntn;
   const int2 tm = tmap[mt];
@@ -283,44 +292,53 @@ k_bwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const int m0 = (local / tk.nch_b) * BM, n0 = nt * BN;
   const int kb = chunk * tk.kc_b;
   const int ke = min(f.b, kb + tk.kc_b);
-  const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
+  // P(m, q) = FT[(s + q) + m n]  (transposed lower block, contiguous in q),
+  // Q(q, c) = X[B[q] k + c]
+  const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac + f.s;
   C* X = reinterpret_cast<C*>(L.X);
-  // P(m, q) = FT[(s + q) + m n]  (transposed lower block, contiguous in q)
-  View<T> pv{FT + f.s, (long long)n, 1, f.s, f.b};
-  // Q(c, q) = X[B[q] k + c]
-  View<T> qv{X, 1, (long long)k, k, f.b, L.bidx + f.bidx};
-  WaveAcc<T, BM, BN, M3> acc;
-  gemm_tile<T, BM, false, true>(sm, acc, pv, qv, m0, n0, kb, ke);
-  if (tk.nch_b > 1) {
-    C* S = reinterpret_cast<C*>(scratch);
-    for_each_acc<T, BM>(acc, [&](int r, int c, C z) {
-      const int gm = m0 + r, gc = n0 + c;
-      if (gm < f.s && gc < k) st(S + (tk.scr_b + (long long)chunk * f.s + gm) * k + gc, z);
-    });
-    return;
+  auto finish = [&](const auto& acc, auto out) {
+    using O = decltype(out);
+    if (tk.nch_b > 1) {
+      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), tk.scr_b + (long long)chunk * f.s,
+                          m0, n0, f.s, k);
+      return;
+    }
+    // X(S) = Z(S) + product: every Z value of the lane is loaded before the
+    // first store (X and Z are distinct buffers, but the compiler cannot tell)
+    const O o;
+    const C* Z = reinterpret_cast<const C*>(L.Wt);
+    C zv[O::NR][O::NC];
+#pragma unroll
+    for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+      for (int j = 0; j < O::NC; ++j) {
+        const int gm = m0 + o.r[i], gc = n0 + o.c[j];
+        zv[i][j] = ld_or_zero(gm < f.s && gc < k && !(raw & kZeroZ),
+                              Z + (long long)(f.off + gm) * k + gc);
+      }
+#pragma unroll
+    for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+      for (int j = 0; j < O::NC; ++j) {
+        const int gm = m0 + o.r[i], gc = n0 + o.c[j];
+        if (gm < f.s && gc < k)
+          st(X + (long long)(f.off + gm) * k + gc, cadd(zv[i][j], acc_at(acc, i, j)));
+      }
+  };
+  if constexpr (split_form<T>()) {
+    __shared__ SplitSmem<BN> sm;
+    SplitAcc<BM, BN> acc;
+    split_tile<BM, BN, true, true>(sm, acc, SplitP{FT, n, f.s}, SplitQ{X, k, k, L.bidx + f.bidx},
+                                   m0, n0, kb, ke);
+    finish(acc, SplitOut<BM, BN>());
+  } else {
+    __shared__ GemmSmem<T, BM, BN, false> sm;
+    WaveAcc<T, BM, BN> acc;
+    gemm_tile<T, BM, false, true>(sm, acc, View<T>{FT, (long long)n, 1, f.s, f.b},
+                                  View<T>{X, 1, (long long)k, k, f.b, L.bidx + f.bidx}, m0, n0,
+                                  kb, ke);
+    finish(acc, LaneOut<T, BM, BN>());
   }
-  // X(S) = Z(S) + product: every Z value of the lane is loaded before the
-  // first store (X and Z are distinct buffers, but the compiler cannot tell)
-  using O = LaneOut<T, BM, BN>;
-  const O o;
-  const C* Z = reinterpret_cast<const C*>(L.Wt);
-  C zv[O::NR][O::NC];
-#pragma unroll
-  for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-    for (int j = 0; j < O::NC; ++j) {
-      const int gm = m0 + o.r[i], gc = n0 + o.c[j];
-      zv[i][j] = ld_or_zero(gm < f.s && gc < k && !(raw & kZeroZ),
-                            Z + (long long)(f.off + gm) * k + gc);
-    }
-#pragma unroll
-  for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-    for (int j = 0; j < O::NC; ++j) {
-      const int gm = m0 + o.r[i], gc = n0 + o.c[j];
-      if (gm < f.s && gc < k)
-        st(X + (long long)(f.off + gm) * k + gc, cadd(zv[i][j], acc_at(acc, i, j)));
-    }
 }
 
 template <typename T, int NT>
@@ -618,24 +636,19 @@ void launch_fwd_gather(const FrontDev* fr, const int* ids, int n, const int2* tm
 template <typename T>
 void launch_fwd_gemm(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
                      const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bn, bool m3, hipStream_t st, hipEvent_t t0,
+                     void* scratch, int bn, hipStream_t st, hipEvent_t t0,
                      hipEvent_t t1) {
   if (total_tiles <= 0) return;
   const int ntn = (k + bn - 1) / bn;
   const dim3 grid(total_tiles * ntn);
-#define HELM_FWD(BN_, M3_)                                                                  \
+#define HELM_FWD(BN_)                                                                       \
   if (t0)                                                                                   \
-    hipExtLaunchKernelGGL((k_fwd_gemm<T, BN_, M3_>), grid, dim3(256), 0, st, t0, t1, 0, fr, \
-                          ids, tasks, n, tmap, layers, k, scratch);                         \
+    hipExtLaunchKernelGGL((k_fwd_gemm<T, BN_>), grid, dim3(256), 0, st, t0, t1, 0, fr, ids, \
+                          tasks, n, tmap, layers, k, scratch);                              \
   else                                                                                      \
-    hipLaunchKernelGGL((k_fwd_gemm<T, BN_, M3_>), grid, dim3(256), 0, st, fr, ids, tasks,   \
-                       n, tmap, layers, k, scratch)
-  constexpr bool C64 = sizeof(T) == 4;   // the three-product form is for complex64
-  if (C64 && m3) {
-    if (bn == 16) HELM_FWD(16, C64); else if (bn == 32) HELM_FWD(32, C64); else HELM_FWD(64, C64);
-  } else {
-    if (bn == 16) HELM_FWD(16, false); else if (bn == 32) HELM_FWD(32, false); else HELM_FWD(64, false);
-  }
+    hipLaunchKernelGGL((k_fwd_gemm<T, BN_>), grid, dim3(256), 0, st, fr, ids, tasks, n,     \
+                       tmap, layers, k, scratch)
+  if (bn == 16) { HELM_FWD(16); } else if (bn == 32) { HELM_FWD(32); } else { HELM_FWD(64); }
 #undef HELM_FWD
 }
 template <typename T>
@@ -653,35 +666,27 @@ void launch_fwd_reduce(const FrontDev* fr, const int* ids, const SolveTask* task
 template <typename T>
 void launch_bwd_gemm(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
                      const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bm, int bn, bool m3, hipStream_t st, hipEvent_t t0,
+                     void* scratch, int bm, int bn, hipStream_t st, hipEvent_t t0,
                      hipEvent_t t1) {
   if (total_tiles <= 0) return;
   // a 32 x 16 tile has fewer MFMA blocks than waves: use 32 columns there
   if (bm == 32 && bn == 16) bn = 32;
   const int ntn = (k + bn - 1) / bn;
   const dim3 grid(total_tiles * ntn);
-#define HELM_BWD(BM_, BN_, M3_)                                                              \
-  if (t0)                                                                                    \
-    hipExtLaunchKernelGGL((k_bwd_gemm<T, BM_, BN_, M3_>), grid, dim3(256), 0, st, t0, t1, 0, \
-                          fr, ids, tasks, n, tmap, layers, k, scratch);                      \
-  else                                                                                       \
-    hipLaunchKernelGGL((k_bwd_gemm<T, BM_, BN_, M3_>), grid, dim3(256), 0, st, fr, ids,      \
-                       tasks, n, tmap, layers, k, scratch)
-#define HELM_BWD_ALL(M3_)                                                                   \
-  if (bm == 32) {                                                                           \
-    if (bn == 32) { HELM_BWD(32, 32, M3_); } else { HELM_BWD(32, 64, M3_); }                \
-  } else {                                                                                  \
-    if (bn == 16) { HELM_BWD(64, 16, M3_); }                                                \
-    else if (bn == 32) { HELM_BWD(64, 32, M3_); }                                           \
-    else { HELM_BWD(64, 64, M3_); }                                                         \
-  }
-  constexpr bool C64 = sizeof(T) == 4;   // the three-product form is for complex64
-  if (C64 && m3) {
-    HELM_BWD_ALL(C64)
+#define HELM_BWD(BM_, BN_)                                                                  \
+  if (t0)                                                                                   \
+    hipExtLaunchKernelGGL((k_bwd_gemm<T, BM_, BN_>), grid, dim3(256), 0, st, t0, t1, 0, fr, \
+                          ids, tasks, n, tmap, layers, k, scratch);                         \
+  else                                                                                      \
+    hipLaunchKernelGGL((k_bwd_gemm<T, BM_, BN_>), grid, dim3(256), 0, st, fr, ids, tasks,   \
+                       n, tmap, layers, k, scratch)
+  if (bm == 32) {
+    if (bn == 32) { HELM_BWD(32, 32); } else { HELM_BWD(32, 64); }
   } else {
-    HELM_BWD_ALL(false)
+    if (bn == 16) { HELM_BWD(64, 16); }
+    else if (bn == 32) { HELM_BWD(64, 32); }
+    else { HELM_BWD(64, 64); }
   }
-#undef HELM_BWD_ALL
 #undef HELM_BWD
 }
 template <typename T>
@@ -702,14 +707,14 @@ void launch_bwd_reduce(const FrontDev* fr, const int* ids, const SolveTask* task
                                      int, const LayerDev*, int, hipStream_t);        \
   template void launch_fwd_gemm<T>(const FrontDev*, const int*, const SolveTask*,    \
                                    int, const int2*, int, const LayerDev*, int,       \
-                                   void*, int, bool, hipStream_t, hipEvent_t,         \
+                                   void*, int, hipStream_t, hipEvent_t,               \
                                    hipEvent_t);                                      \
   template void launch_fwd_reduce<T>(const FrontDev*, const int*, const SolveTask*,  \
                                      int, const int2*, int, const LayerDev*, int,     \
                                      const void*, hipStream_t);                      \
   template void launch_bwd_gemm<T>(const FrontDev*, const int*, const SolveTask*,    \
                                    int, const int2*, int, const LayerDev*, int,       \
-                                   void*, int, int, bool, hipStream_t, hipEvent_t,    \
+                                   void*, int, int, hipStream_t, hipEvent_t,          \
                                    hipEvent_t);                                      \
   template void launch_bwd_reduce<T>(const FrontDev*, const int*, const SolveTask*,  \
                                      int, const int2*, int, const LayerDev*, int,     \
