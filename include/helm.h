@@ -92,11 +92,9 @@ extern "C" {
                                 (each real product from bf16 products of
                                 exactly split floats, at FP32 accuracy), so
                                 the flag changes nothing                     */
-#define HELM_FLAG_FACTOR_4M 1024 /* the complex64 factorization's sweep GEMM
-                                forms each complex product from four real
-                                products (default: three, as the
-                                substitutions).  No effect on HELM_FP64
-                                handles                                      */
+#define HELM_FLAG_FACTOR_4M 1024 /* the same for the complex64 factorization's
+                                sweep GEMM: four real products whether set or
+                                not                                           */
 #define HELM_FLAG_NO_NARROW 2048 /* every refinement step and every GMRES
                                 iteration runs at the batch's full width.  By
                                 default (mixed) a column that meets the target

@@ -114,7 +114,6 @@ void Handle::set_profile(int flags) {
   profile_mask = 0;
   if (flags & HELM_FLAG_PROFILE) profile_mask = (1u << K_NCLASS) - 1;
   if (flags & HELM_FLAG_PROFILE_FWD) profile_mask |= 1u << K_FWD_GEMM;
-  factor3m = prec == HELM_MIXED && !(flags & HELM_FLAG_FACTOR_4M);
 }
 
 // An event recorded on the handle's stream, for the timing of class cls
@@ -501,7 +500,7 @@ void Handle::factorize_t() {
         prof_end(K_SWAP_JO, e1, 0, 0);
         e1 = prof_begin(K_SWEEP_GEMM);
         kern::launch_sweep_gemm<T>(fr, ids, n_act, fd.pFull.as<int2>(), fd.pFull_h[n_act],
-                                   k, nb, ws0.p, ws1.p, factor3m, st);
+                                   k, nb, ws0.p, ws1.p, st);
         prof_end(K_SWEEP_GEMM, e1, sw_flops, sw_bytes);
         e1 = prof_begin(K_UPDATE_OJ);
         kern::launch_update_OJ<T>(fr, ids, n_act, fd.pCol.as<int2>(), fd.pCol_h[n_act], k,

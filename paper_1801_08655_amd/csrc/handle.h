@@ -159,8 +159,6 @@ struct Handle {
   // the forward substitution GEMM only), one bit per KClass
   unsigned profile_mask = 0;
   void set_profile(int flags);
-  // three-product complex64 factorization sweep (unless HELM_FLAG_FACTOR_4M)
-  bool factor3m = false;
   bool profile() const { return profile_mask != 0; }
   KStat kstats[K_NCLASS];
   std::vector<PendingEvent> pending;

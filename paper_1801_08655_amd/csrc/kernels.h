@@ -47,10 +47,9 @@ void launch_swap_JO(const FrontDev* fronts, const int* ids, int n_active,
                     const long long* panel_off, const long long* perm_off,
                     hipStream_t st);
 template <typename T>
-// m3: three real products per complex product (complex64 only)
 void launch_sweep_gemm(const FrontDev* fronts, const int* ids, int n_active,
                        const int2* tmap, int total, int k, int nb, void* ws0,
-                       void* ws1, bool m3, hipStream_t st);
+                       void* ws1, hipStream_t st);
 template <typename T>
 void launch_update_OJ(const FrontDev* fronts, const int* ids, int n_active,
                       const int2* tmap, int total, int k, int nb, void* ws0,

@@ -15,6 +15,7 @@
 // the transpose of -F21 F11^-1 in place of F11^-1 F12.
 #include "kernels.h"
 #include "kernels_common.h"
+#include "kernels_split.h"
 
 namespace helm {
 namespace kern {
@@ -980,14 +981,19 @@ k_swap_JO(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // symmetric operator's backward step uses the transpose of -F21 F11^-1) nor
 // the parent's extend-add (the Schur block) ever reads.  Tiles that lie
 // wholly in J or in that block return at once.
+// Bound: the trailing entries streamed from and to HBM once per pivot block
+// (complex64 at 200^3: 5.7 TB; 3.5 TB/s) and the latency of a two-step
+// product between them.  complex64 runs on the split bf16 tile: 1916 -> 1639
+// ms of a 200^3 factorization and 93 -> 80 ms of a 100^3 one against the FP32
+// tile.  Loading the tile's entries before the product needs 200 registers
+// (2 waves per SIMD): 1809 ms; kept at 3 waves it spills: 3688.
 // --------------------------------------------------------------------------
-template <typename T, bool M3>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (M3 ? 3 : 4) : 1, 8)))
+template <typename T>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1, 8)))
 k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
              int n_active, const int2* __restrict__ tmap, int k, int nb,
              void* ws0, void* ws1) {
   using C = C_t<T>;
-  __shared__ GemmSmem<T, 64, 64, false, M3> sm;
   const int2 tm = tmap[blockIdx.x];
   const int a = tm.x;
   const FrontDev f = fronts[ids[a]];
@@ -1000,36 +1006,48 @@ k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const bool rowsJ = i0 >= k && i0 + GT <= k + nbf, colsJ = j0 >= k && j0 + GT <= k + nbf;
   if (rowsJ || colsJ || (i0 + GT <= k && j0 >= f.s)) return;   // uniform per block
   C* F = front_ptr<T>(ws0, ws1, f);
-  // P rows = C columns j: B^T(j, q) = F[(k+q) + j n]
-  View<T> pv{F + k, (long long)n, 1, n, nbf};
-  // Q columns = C rows i: A^T(q, i) = F[i + (k+q) n]
-  View<T> qv{F + (long long)k * n, 1, (long long)n, n, nbf};
-  WaveAcc<T, 64, 64, M3> acc;
-  gemm_tile<T, 64, false, true>(sm, acc, pv, qv, j0, i0, 0, nbf);
-  // F(i, j) -= acc: every entry of the lane is loaded before the first store
-  // (one latency for the group instead of a load-store chain per entry)
-  using O = LaneOut<T, 64, 64>;
-  const O o;
-  auto outside = [&](int gi, int gj) {
-    return gi < n && gj < n && (gi < k || gi >= k + nbf) && (gj < k || gj >= k + nbf) &&
-           !(gi < k && gj >= f.s);
+  // F(i, j) -= product: every entry of the lane is loaded before the first
+  // store (one latency for the group instead of a load-store chain per entry)
+  auto subtract = [&](const auto& acc, auto out) {
+    using O = decltype(out);
+    const O o;
+    auto outside = [&](int gi, int gj) {
+      return gi < n && gj < n && (gi < k || gi >= k + nbf) && (gj < k || gj >= k + nbf) &&
+             !(gi < k && gj >= f.s);
+    };
+    C cv[O::NR][O::NC];
+#pragma unroll
+    for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+      for (int j = 0; j < O::NC; ++j) {
+        const int gi = i0 + o.c[j], gj = j0 + o.r[i];
+        cv[i][j] = ld_or_zero(outside(gi, gj), F + (long long)gi + (long long)gj * n);
+      }
+#pragma unroll
+    for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+      for (int j = 0; j < O::NC; ++j) {
+        const int gi = i0 + o.c[j], gj = j0 + o.r[i];
+        if (outside(gi, gj))
+          st(F + (long long)gi + (long long)gj * n, csub(cv[i][j], acc_at(acc, i, j)));
+      }
   };
-  C cv[O::NR][O::NC];
-#pragma unroll
-  for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-    for (int j = 0; j < O::NC; ++j) {
-      const int gi = i0 + o.c[j], gj = j0 + o.r[i];
-      cv[i][j] = ld_or_zero(outside(gi, gj), F + (long long)gi + (long long)gj * n);
-    }
-#pragma unroll
-  for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-    for (int j = 0; j < O::NC; ++j) {
-      const int gi = i0 + o.c[j], gj = j0 + o.r[i];
-      if (outside(gi, gj))
-        st(F + (long long)gi + (long long)gj * n, csub(cv[i][j], acc_at(acc, i, j)));
-    }
+  // P rows = C columns j: B^T(j, q) = F[(k + q) + j n]
+  // Q columns = C rows i: A^T(q, i) = F[i + (k + q) n]
+  if constexpr (sizeof(T) == 4) {
+    __shared__ SplitSmem<64> sm;
+    SplitAcc<64, 64> acc;
+    split_tile<64, 64, true, false>(sm, acc, SplitP{F + k, n, n},
+                                    SplitQ{F + (long long)k * n, n, n, nullptr}, j0, i0, 0, nbf);
+    subtract(acc, SplitOut<64, 64>());
+  } else {
+    __shared__ GemmSmem<T, 64, 64> sm;
+    WaveAcc<T, 64, 64> acc;
+    gemm_tile<T, 64, false, true>(sm, acc, View<T>{F + k, (long long)n, 1, n, nbf},
+                                  View<T>{F + (long long)k * n, 1, (long long)n, n, nbf}, j0, i0,
+                                  0, nbf);
+    subtract(acc, LaneOut<T, 64, 64>());
+  }
 }
 
 // --------------------------------------------------------------------------
@@ -1217,15 +1235,10 @@ void launch_swap_JO(const FrontDev* fronts, const int* ids, int n_active,
 template <typename T>
 void launch_sweep_gemm(const FrontDev* fronts, const int* ids, int n_active,
                        const int2* tmap, int total, int k, int nb, void* ws0,
-                       void* ws1, bool m3, hipStream_t st) {
+                       void* ws1, hipStream_t st) {
   if (total <= 0) return;
-  constexpr bool C64 = sizeof(T) == 4;   // the three-product form is for complex64
-  if (C64 && m3)
-    hipLaunchKernelGGL((k_sweep_gemm<T, C64>), dim3(total), dim3(256), 0, st, fronts, ids,
-                       n_active, tmap, k, nb, ws0, ws1);
-  else
-    hipLaunchKernelGGL((k_sweep_gemm<T, false>), dim3(total), dim3(256), 0, st, fronts, ids,
-                       n_active, tmap, k, nb, ws0, ws1);
+  hipLaunchKernelGGL(k_sweep_gemm<T>, dim3(total), dim3(256), 0, st, fronts, ids, n_active,
+                     tmap, k, nb, ws0, ws1);
 }
 template <typename T>
 void launch_update_OJ(const FrontDev* fronts, const int* ids, int n_active,
@@ -1262,7 +1275,7 @@ void launch_store_factor(const FrontDev* fronts, const int* ids, int n_ids,
                                   const int*, const long long*, const long long*,  \
                                   hipStream_t);                                    \
   template void launch_sweep_gemm<T>(const FrontDev*, const int*, int, const int2*, \
-                                     int, int, int, void*, void*, bool, hipStream_t); \
+                                     int, int, int, void*, void*, hipStream_t);       \
   template void launch_update_OJ<T>(const FrontDev*, const int*, int, const int2*,  \
                                     int, int, int, void*, void*, const void*,      \
                                     const long long*, hipStream_t);                \
