@@ -284,7 +284,7 @@ int helm_kernel_stats(helm_handle* h, helm_kernel_stat* out, int max, int* count
  * batch width k, depth of the front trees), for the sets used so far.  A
  * layer set is described by its number of layers.  fwd_bn / bwd_bn are the
  * tile kinds in use: 16, 32 or 64 for MFMA tiles of that many columns, 1
- * for the vector path (default up to 2 columns, a candidate up to 4); when
+ * for the vector path (default and a candidate up to 4 columns); when
  * the choice was measured (HELM_FLAG_AUTOTUNE), t_fwd_us / t_bwd_us hold the
  * timed launch of each kind in the order 1, 16, 32, 64 (0 where a kind was
  * not tried).  Writes up to `max` records and the total to *count. */

@@ -55,6 +55,13 @@ std::vector<double2> to_d2(const std::vector<cd>& v) {
   return o;
 }
 
+// Workgroups a depth's vector launches aim at, forward and backward: with
+// fewer the tiles get narrower.  One column of one 100^3 layer, complex64:
+// forward depth 4 (400 tiles of 64 rows) 19 us at 64 rows, 22 at 32; backward
+// depth 8 (256 fronts of 41 pivots) 10.8 us at 512 workgroups, 12.3 at 256;
+// a whole pruned solve 356 us at 512, 360 at 256, 375 at 1024.
+constexpr long long kFwdVecTiles = 384, kBwdVecTiles = 512;
+
 int tiles64(long long n) { return (int)((n + 63) / 64); }
 int tiles16(long long n) { return (int)((n + 15) / 16); }
 
@@ -635,114 +642,121 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
   };
   auto fwd_on = [&](int f) { return !pr || pr->fwd[f]; };
   auto bwd_on = [&](int f) { return !pr || pr->bwd[f]; };
+  // Every list and map of the set is packed into one allocation, written by
+  // one copy: add() appends a vector and notes where its pointer goes.
+  std::vector<char> pack;
+  std::vector<std::pair<const void**, size_t>> fix;
+  auto add = [&](auto& slot, const auto& v) {
+    fix.emplace_back(reinterpret_cast<const void**>(&slot), pack.size());
+    const size_t bytes = v.size() * sizeof(v[0]);
+    const size_t at = pack.size();
+    pack.resize((at + bytes + 255) & ~(size_t)255);
+    if (bytes) std::memcpy(pack.data() + at, v.data(), bytes);
+  };
   for (int d = 0; d <= maxd; ++d) {
     auto D = std::make_unique<DepthList>();
-    std::vector<int> ids, all;   // backward list (flagged ids: ids_raw)
+    std::vector<int> all;
     for (int l : layers)
       if (d <= G.layers[l].max_depth)
         for (int q : G.layers[l].by_depth[d]) all.push_back(front_base[l] + q);
-    std::vector<int> ids_raw;
-    for (int f : all)
-      if (bwd_on(f)) {
-        ids.push_back(f);
-        ids_raw.push_back(f | (fwd_on(f) ? 0 : kZeroZ));
-      }
-    const size_t n = ids.size();
-    // backward: every front; a 32-row tile when the pivot blocks are small,
-    // K (boundary) split when the depth has few tiles
+    std::vector<SolveFront> bw, fw;
     double mean_s = 0;
-    for (int f : ids) mean_s += fronts_h[f].s;
+    for (int f : all) {
+      const FrontDev& F = fronts_h[f];
+      SolveFront r{};
+      r.fac = F.fac; r.ub = F.ub; r.s = F.s; r.b = F.b; r.off = F.off; r.layer = F.layer;
+      r.bidx = F.bidx; r.ub_parity = F.ub_parity; r.nch = 1; r.kc = 16;
+      r.inv[0] = r.inv[1] = -1;
+      const double sbs = (double)(F.s + F.b) * F.s, bs = (double)F.b * F.s;
+      if (bwd_on(f)) {
+        r.zero_z = fwd_on(f) ? 0 : 1;
+        bw.push_back(r);
+        mean_s += F.s;
+        D->sum_s += F.s; D->sum_b += F.b; D->sum_sbs += sbs; D->sum_bs += bs;
+        S->elems += bs;
+      }
+      if (fwd_on(f)) {
+        r.zero_z = 0;
+        for (int c = 0; c < 2; ++c)
+          if (F.child[c] >= 0 && fwd_on(F.child[c])) {
+            r.inv[c] = F.inv[c];
+            r.cub[c] = fronts_h[F.child[c]].ub;
+          }
+        fw.push_back(r);
+        D->fl_s += F.s; D->fl_b += F.b; D->fl_sbs += sbs;
+        S->elems += sbs;
+      }
+    }
+    const size_t n = bw.size(), nl = fw.size();
+    // backward: a 32-row tile when the pivot blocks are small, K (boundary)
+    // split when the depth has few tiles
     mean_s /= std::max<size_t>(n, 1);
     const int bm = mean_s <= 40 ? 32 : 64;
     D->bwd_bm = bm;
-    auto tilesB = [&](int s_) { return (s_ + bm - 1) / bm; };
-    long long tb = 0;
-    for (int f : ids) tb += tilesB(fronts_h[f].s);
-    std::vector<SolveTask> tasks(n);
-    std::vector<int> pBw(n + 1, 0), rB(n + 1, 0);
-    long long scr_b = 0;
+    auto tiles = [](long long rows, int t) { return (int)((rows + t - 1) / t); };
+    long long tb = 0, scr_b = 0;
+    for (const auto& r : bw) tb += tiles(r.s, bm);
+    std::vector<int> pB(n + 1, 0), rB(n + 1, 0);
     for (size_t a = 0; a < n; ++a) {
-      const FrontDev& F = fronts_h[ids[a]];
-      SolveTask& t = tasks[a];
-      t.nch_f = 1;
-      t.kc_f = 16;
-      t.scr_f = 0;
-      split(tb, F.b, t.nch_b, t.kc_b);
-      t.scr_b = scr_b;
-      if (t.nch_b > 1) scr_b += (long long)t.nch_b * F.s;
-      D->sum_s += F.s;
-      D->sum_b += F.b;
-      D->sum_sbs += (double)(F.s + F.b) * F.s;
-      D->sum_bs += (double)F.b * F.s;
-      pBw[a + 1] = pBw[a] + tilesB(F.s) * t.nch_b;
-      rB[a + 1] = rB[a] + (t.nch_b > 1 ? tiles16(F.s) : 0);
+      SolveFront& r = bw[a];
+      split(tb, r.b, r.nch, r.kc);
+      r.scr = scr_b;
+      if (r.nch > 1) scr_b += (long long)r.nch * r.s;
+      pB[a + 1] = pB[a] + tiles(r.s, bm) * r.nch;
+      rB[a + 1] = rB[a] + (r.nch > 1 ? tiles16(r.s) : 0);
     }
     // forward: every front takes the GEMM; only fronts with children need
     // the extend-add gather (leaves read their pivots straight from X)
-    std::vector<int> idsS, idsL;   // S: fronts with children (gather), L: all
-    std::vector<int> idsS_raw, idsL_raw;
-    for (int f : all) {
-      if (!fwd_on(f)) continue;
-      const FrontDev& F = fronts_h[f];
-      const double sbs = (double)(F.s + F.b) * F.s;
-      int flags = 0;
-      for (int c = 0; c < 2; ++c)
-        if (F.child[c] >= 0 && !fwd_on(F.child[c])) flags |= kSkipChild0 << c;
-      const bool kids = (F.child[0] >= 0 && !(flags & kSkipChild0)) ||
-                        (F.child[1] >= 0 && !(flags & kSkipChild1));
-      idsL.push_back(f);
-      idsL_raw.push_back(f | flags);
-      D->fl_s += F.s; D->fl_b += F.b; D->fl_sbs += sbs;
-      if (kids) {
-        idsS.push_back(f);
-        idsS_raw.push_back(f | flags);
-        D->fs_s += F.s; D->fs_b += F.b;
-      }
-    }
-    const size_t nl = idsL.size(), ng = idsS.size();
-    long long tf = 0;
-    for (int f : idsL) tf += tiles64(fronts_h[f].s + fronts_h[f].b);
-    std::vector<SolveTask> tasksL(nl);
-    std::vector<int> pSB(ng + 1, 0), pF(nl + 1, 0), rF(nl + 1, 0);
-    for (size_t a = 0; a < ng; ++a) pSB[a + 1] = pSB[a] + tiles16(fronts_h[idsS[a]].s);
-    long long scr_f = 0;
+    long long tf = 0, scr_f = 0;
+    for (const auto& r : fw) tf += tiles64(r.s + r.b);
+    std::vector<int> pS(nl + 1, 0), pF(nl + 1, 0), rF(nl + 1, 0);
     for (size_t a = 0; a < nl; ++a) {
-      const FrontDev& F = fronts_h[idsL[a]];
-      SolveTask& t = tasksL[a];
-      split(tf, F.s, t.nch_f, t.kc_f);
-      t.nch_b = 1;
-      t.kc_b = 16;
-      t.scr_b = 0;
-      t.scr_f = scr_f;
-      if (t.nch_f > 1) scr_f += (long long)t.nch_f * (F.s + F.b);
-      pF[a + 1] = pF[a] + tiles64(F.s + F.b) * t.nch_f;
-      rF[a + 1] = rF[a] + (t.nch_f > 1 ? tiles16(F.s + F.b) : 0);
+      SolveFront& r = fw[a];
+      split(tf, r.s, r.nch, r.kc);
+      r.scr = scr_f;
+      if (r.nch > 1) scr_f += (long long)r.nch * (r.s + r.b);
+      const bool kids = r.inv[0] >= 0 || r.inv[1] >= 0;
+      if (kids) { D->fs_s += r.s; D->fs_b += r.b; }
+      pS[a + 1] = pS[a] + (kids ? tiles16(r.s) : 0);
+      pF[a + 1] = pF[a] + tiles64(r.s + r.b) * r.nch;
+      rF[a + 1] = rF[a] + (r.nch > 1 ? tiles16(r.s + r.b) : 0);
     }
+    // vector path: the widest tiles that still give enough workgroups, one
+    // wave per 64-row tile where every front has few pivots
+    int max_s = 0;
+    for (const auto& r : fw) max_s = std::max(max_s, r.s);
+    D->vec_rows = tf >= kFwdVecTiles ? 64 : (tf >= kFwdVecTiles / 4 ? 32 : 16);
+    if (tf >= kFwdVecTiles && max_s <= 128) D->vec_rows = max_s <= 64 ? 1 : 2;
+    const int vrows = D->vec_rows < 16 ? 64 : D->vec_rows;
+    for (D->vec_rpg = bm == 32 ? 4 : 8; D->vec_rpg > 1; D->vec_rpg /= 2) {
+      long long w = 0;
+      for (const auto& r : bw) w += tiles(r.s, 8 * D->vec_rpg);
+      if (w >= kBwdVecTiles) break;
+    }
+    std::vector<int> vF(nl + 1, 0), vB(n + 1, 0);
+    for (size_t a = 0; a < nl; ++a) vF[a + 1] = vF[a] + tiles(fw[a].s + fw[a].b, vrows);
+    for (size_t a = 0; a < n; ++a) vB[a + 1] = vB[a] + tiles(bw[a].s, 8 * D->vec_rpg);
     D->n = (int)n;
-    D->nS = (int)idsS.size();
     D->nL = (int)nl;
-    for (int f : ids) S->elems += (double)fronts_h[f].b * fronts_h[f].s;
-    for (int f : idsL) S->elems += (double)(fronts_h[f].s + fronts_h[f].b) * fronts_h[f].s;
-    upload(D->ids, ids_raw, st);
-    upload(D->tasks, tasks, st);
-    upload(D->pBw, tile_map(pBw), st);
-    upload(D->rB, tile_map(rB), st);
-    upload(D->idsS, idsS_raw, st);
-    upload(D->idsL, idsL_raw, st);
-    upload(D->tasksL, tasksL, st);
-    upload(D->pSB, tile_map(pSB), st);
-    upload(D->pF, tile_map(pF), st);
-    upload(D->rF, tile_map(rF), st);
-    D->tSB = pSB.back();
-    D->tF = pF.back();
-    D->tBw = pBw.back();
-    D->tRF = rF.back();
-    D->tRB = rB.back();
+    add(D->bwd, bw);
+    add(D->fwd, fw);
+    auto map = [&](const int2*& slot, int& count, const std::vector<int>& prefix) {
+      add(slot, tile_map(prefix));
+      count = prefix.back();
+    };
+    map(D->pS, D->tS, pS);
+    map(D->pF, D->tF, pF);
+    map(D->rF, D->tRF, rF);
+    map(D->pB, D->tB, pB);
+    map(D->rB, D->tRB, rB);
+    map(D->vF, D->tVF, vF);
+    map(D->vB, D->tVB, vB);
     D->scratch_rows = std::max(scr_f, scr_b);
     S->scratch_rows = std::max(S->scratch_rows, D->scratch_rows);
     S->depth.push_back(std::move(D));
   }
-  HELM_HIP(hipStreamSynchronize(st));
+  upload(S->lists, pack, st);
+  for (auto& p : fix) *p.first = static_cast<const char*>(S->lists.p) + p.second;
   return S;
 }
 
@@ -799,34 +813,32 @@ void Handle::solve_layers(const LayerSet& set, int k) {
   solve_bytes += solve_elems(set) * (double)elem;
 }
 
-// Tile width from the batch width alone: the vector path for k <= 2 (up to
-// 4 columns it is one of the measured candidates), else the narrowest MFMA
-// tile of 16 / 32 / 64 columns that covers k (wider batches take several
-// 64-column tiles).
+// Tile width from the batch width alone: the vector path for k <= 4 (it has
+// no gather and no reduction launches: a pruned 100^3 layer solve of 3 columns
+// takes 425 us against 614 on the 16-column MFMA tile in complex64, 633
+// against 831 in complex128; 4 columns 438 / 615 and 788 / 833; 25^3 2.0 to
+// 2.3 times), else the narrowest MFMA tile of 16 / 32 / 64 columns that covers
+// k (wider batches take several 64-column tiles).
 static int mfma_bn(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
-static int width_bn(int k) { return k <= 2 ? 1 : mfma_bn(k); }
+static int width_bn(int k) { return k <= 4 ? 1 : mfma_bn(k); }
 
 // One depth's forward / backward GEMM launch with column width bn (1: the
 // vector path).
 template <typename T>
-void Handle::launch_fwd(const DepthList& D, const FrontDev* fr, const LayerDev* ld, int k,
-                        void* scr, int bn, hipEvent_t t0, hipEvent_t t1) {
+void Handle::launch_fwd(const DepthList& D, const LayerDev* ld, int k, void* scr, int bn,
+                        hipEvent_t t0, hipEvent_t t1) {
   if (bn == 1)
-    kern::launch_fwd_gemv<T>(fr, D.idsL.as<int>(), D.tasksL.as<SolveTask>(), D.nL,
-                             D.pF.as<int2>(), D.tF, ld, k, scr, st, t0, t1);
+    kern::launch_fwd_gemv<T>(D.fwd, D.vF, D.tVF, ld, k, D.vec_rows, st, t0, t1);
   else
-    kern::launch_fwd_gemm<T>(fr, D.idsL.as<int>(), D.tasksL.as<SolveTask>(), D.nL,
-                             D.pF.as<int2>(), D.tF, ld, k, scr, bn, st, t0, t1);
+    kern::launch_fwd_gemm<T>(D.fwd, D.pF, D.tF, ld, k, scr, bn, st, t0, t1);
 }
 template <typename T>
-void Handle::launch_bwd(const DepthList& D, const FrontDev* fr, const LayerDev* ld, int k,
-                        void* scr, int bn, hipEvent_t t0, hipEvent_t t1) {
+void Handle::launch_bwd(const DepthList& D, const LayerDev* ld, int k, void* scr, int bn,
+                        hipEvent_t t0, hipEvent_t t1) {
   if (bn == 1)
-    kern::launch_bwd_gemv<T>(fr, D.ids.as<int>(), D.tasks.as<SolveTask>(), D.n,
-                             D.pBw.as<int2>(), D.tBw, ld, k, scr, D.bwd_bm, st, t0, t1);
+    kern::launch_bwd_gemv<T>(D.bwd, D.vB, D.tVB, ld, k, D.vec_rpg, st, t0, t1);
   else
-    kern::launch_bwd_gemm<T>(fr, D.ids.as<int>(), D.tasks.as<SolveTask>(), D.n,
-                             D.pBw.as<int2>(), D.tBw, ld, k, scr, D.bwd_bm, bn, st, t0, t1);
+    kern::launch_bwd_gemm<T>(D.bwd, D.pB, D.tB, ld, k, scr, D.bwd_bm, bn, st, t0, t1);
 }
 
 const std::vector<Handle::TileChoice>& Handle::tile_plan(const LayerSet& set, int k) {
@@ -850,7 +862,6 @@ const std::vector<Handle::TileChoice>& Handle::tile_plan(const LayerSet& set, in
 // are read.
 template <typename T>
 void Handle::autotune_t(const LayerSet& set, int k, std::vector<TileChoice>& plan) {
-  const FrontDev* fr = fronts.as<FrontDev>();
   const LayerDev* ld = layers_d.as<LayerDev>();
   void* scr = scratch.p;
   size_t save_bytes = 0;
@@ -896,14 +907,14 @@ void Handle::autotune_t(const LayerSet& set, int k, std::vector<TileChoice>& pla
       if (bn > widest || (bn == 1 && k > 4)) continue;
       if (D.nL > 0) {
         double t = time_us([&] {
-          launch_fwd<T>(D, fr, ld, k, scr, bn);
+          launch_fwd<T>(D, ld, k, scr, bn);
         });
         c.t_fwd[w] = t;
         if (t < bf) { bf = t; c.fwd_bn = bn; }
       }
       if (D.bwd_bm == 32 && bn == 16) continue;   // not a distinct tile
       double t = time_us([&] {
-        launch_bwd<T>(D, fr, ld, k, scr, bn);
+        launch_bwd<T>(D, ld, k, scr, bn);
       });
       c.t_bwd[w] = t;
       if (t < bb) { bb = t; c.bwd_bn = bn; }
@@ -935,7 +946,6 @@ void Handle::solve_layers_t(const LayerSet& set, int k) {
 template <typename T>
 void Handle::run_layers_t(const LayerSet& set, int k, const LayerDev* ld, void* scr,
                           const TileChoice* tp, bool timing) {
-  const FrontDev* fr = fronts.as<FrontDev>();
   auto prof_begin = [&](int cls) { return timing ? this->prof_begin(cls) : nullptr; };
   const double e = (double)elem, kk = (double)k;
   const int wdef = width_bn(k);
@@ -944,55 +954,50 @@ void Handle::run_layers_t(const LayerSet& set, int k, const LayerDev* ld, void* 
   for (int d = set.max_depth; d >= 0; --d) {
     const DepthList& D = *set.depth[d];
     if (D.nL == 0) continue;   // (a pruned set may run a front forward only)
+    const int bn = fwd_bn(d);
     hipEvent_t a = nullptr;
-    if (D.nS > 0) {
+    if (bn != 1 && D.tS > 0) {
       a = prof_begin(K_FWD_GATHER);
-      kern::launch_fwd_gather<T>(fr, D.idsS.as<int>(), D.nS, D.pSB.as<int2>(), D.tSB, ld, k,
-                                 st);
+      kern::launch_fwd_gather<T>(D.fwd, D.pS, D.tS, ld, k, st);
       prof_end(K_FWD_GATHER, a, 0, 3.0 * D.fs_s * kk * e);
     }
-    if (D.nL > 0) {
-      const int* ids = D.idsL.as<int>();
-      const SolveTask* tk = D.tasksL.as<SolveTask>();
-      // timed by the launch itself: its start and stop, no event commands
-      // between it and its neighbours
-      hipEvent_t t0 = nullptr, t1 = nullptr;
-      if (timing && timed(K_FWD_GEMM)) {
-        t0 = take_event();
-        t1 = take_event();
-      }
-      launch_fwd<T>(D, fr, ld, k, scr, fwd_bn(d), t0, t1);
-      // factor block read once; pivots read, Z written, boundary updates
-      // written and the children's updates of the boundary rows read
-      if (t0)
-        pending.push_back(PendingEvent{K_FWD_GEMM, t0, t1, 8.0 * D.fl_sbs * kk,
-                                       D.fl_sbs * e + (2.0 * D.fl_s + D.fl_b + D.fs_b) * kk * e});
-      if (D.tRF > 0) {
-        a = prof_begin(K_FWD_REDUCE);
-        kern::launch_fwd_reduce<T>(fr, ids, tk, D.nL, D.rF.as<int2>(), D.tRF, ld, k, scr, st);
-        prof_end(K_FWD_REDUCE, a, 0, 0);
-      }
+    // timed by the launch itself: its start and stop, no event commands
+    // between it and its neighbours
+    hipEvent_t t0 = nullptr, t1 = nullptr;
+    if (timing && timed(K_FWD_GEMM)) {
+      t0 = take_event();
+      t1 = take_event();
+    }
+    launch_fwd<T>(D, ld, k, scr, bn, t0, t1);
+    // factor block read once; pivots read, Z written, boundary updates
+    // written and the children's updates of the boundary rows read
+    if (t0)
+      pending.push_back(PendingEvent{K_FWD_GEMM, t0, t1, 8.0 * D.fl_sbs * kk,
+                                     D.fl_sbs * e + (2.0 * D.fl_s + D.fl_b + D.fs_b) * kk * e});
+    if (bn != 1 && D.tRF > 0) {
+      a = prof_begin(K_FWD_REDUCE);
+      kern::launch_fwd_reduce<T>(D.fwd, D.rF, D.tRF, ld, k, scr, st);
+      prof_end(K_FWD_REDUCE, a, 0, 0);
     }
   }
   for (int d = 0; d <= set.max_depth; ++d) {
     const DepthList& D = *set.depth[d];
     if (D.n == 0) continue;
-    const int* ids = D.ids.as<int>();
-    const SolveTask* tk = D.tasks.as<SolveTask>();
+    const int bn = bwd_bn(d);
     // timed by the launch itself, as the forward GEMM
     hipEvent_t t0 = nullptr, t1 = nullptr;
     if (timing && timed(K_BWD_GEMM)) {
       t0 = take_event();
       t1 = take_event();
     }
-    launch_bwd<T>(D, fr, ld, k, scr, bwd_bn(d), t0, t1);
+    launch_bwd<T>(D, ld, k, scr, bn, t0, t1);
     // factor block read once; X(B) rows read, Z(S) read, X(S) written
     if (t0)
       pending.push_back(PendingEvent{K_BWD_GEMM, t0, t1, 8.0 * D.sum_bs * kk,
                                      D.sum_bs * e + (D.sum_b + 2.0 * D.sum_s) * kk * e});
-    if (D.tRB > 0) {
+    if (bn != 1 && D.tRB > 0) {
       hipEvent_t a = prof_begin(K_BWD_REDUCE);
-      kern::launch_bwd_reduce<T>(fr, ids, tk, D.n, D.rB.as<int2>(), D.tRB, ld, k, scr, st);
+      kern::launch_bwd_reduce<T>(D.bwd, D.rB, D.tRB, ld, k, scr, st);
       prof_end(K_BWD_REDUCE, a, 0, 0);
     }
   }

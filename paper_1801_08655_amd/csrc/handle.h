@@ -34,20 +34,25 @@ struct EventPair {
   double elapsed_ms(hipStream_t st) const;
 };
 
-// Fronts of one depth over a set of layers, for the substitutions.
+// Fronts of one depth over a set of layers, for the substitutions.  The
+// lists and tile maps are device pointers into the set's one allocation.
 struct DepthList {
-  int n = 0;
-  DevMem ids;                 // global front ids (backward: all fronts)
-  DevMem tasks;               // SolveTask per front (K splits, scratch offsets)
-  DevMem pBw, rB;             // backward GEMM tiles incl. K chunks; reduce tiles
-  int nS = 0;                 // forward: fronts with children (extend-add gather)
-  DevMem idsS;
-  int nL = 0;                 // forward: every front (GEMM)
-  DevMem idsL, tasksL;
-  DevMem pSB;                 // prefix of 64-row tiles of s+b of the gathered fronts
-  DevMem pF, rF;              // forward GEMM tiles incl. K chunks; reduce tiles
-  int tSB = 0, tF = 0, tBw = 0, tRF = 0, tRB = 0;
-  int bwd_bm = 64;            // row tile of the backward GEMM at this depth
+  int n = 0, nL = 0;              // fronts of the backward / forward pass
+  const SolveFront* bwd = nullptr;
+  const SolveFront* fwd = nullptr;
+  // tile maps (list index, tile) and their lengths
+  const int2* pS = nullptr;       // extend-add gather (forward fronts with children)
+  const int2* pF = nullptr;       // forward GEMM tiles incl. K chunks
+  const int2* rF = nullptr;       // forward reduce tiles (split fronts)
+  const int2* pB = nullptr;       // backward GEMM tiles incl. K chunks
+  const int2* rB = nullptr;       // backward reduce tiles
+  const int2* vF = nullptr;       // vector path: forward, backward
+  const int2* vB = nullptr;
+  int tS = 0, tF = 0, tRF = 0, tB = 0, tRB = 0, tVF = 0, tVB = 0;
+  int bwd_bm = 64;                // row tile of the backward GEMM at this depth
+  // vector path: forward row tile (1, 2: a wave per 64-row tile of fronts of
+  // at most 64, 128 pivots), backward rows per lane group
+  int vec_rows = 64, vec_rpg = 8;
   double sum_s = 0, sum_b = 0, sum_sbs = 0, sum_bs = 0;  // work counts, all fronts
   double fs_s = 0, fs_b = 0, fs_sbs = 0;    // fronts with children
   double fl_s = 0, fl_b = 0, fl_sbs = 0;    // all fronts (forward GEMM)
@@ -79,6 +84,7 @@ struct LayerSet {
   double elems = 0;             // factor elements one solve reads
   long long scratch_rows = 0;   // max over depths
   std::vector<std::unique_ptr<DepthList>> depth;
+  DevMem lists;                 // every depth's lists and tile maps
 };
 
 // Fronts of one depth of a factorization group, sorted by s (descending),
@@ -148,12 +154,12 @@ struct Handle {
   const std::vector<TileChoice>& tile_plan(const LayerSet& set, int k);
   template <typename T> void autotune_t(const LayerSet& set, int k,
                                         std::vector<TileChoice>& plan);
-  template <typename T> void launch_fwd(const DepthList& D, const FrontDev* fr,
-                                        const LayerDev* ld, int k, void* scr, int bn,
-                                        hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
-  template <typename T> void launch_bwd(const DepthList& D, const FrontDev* fr,
-                                        const LayerDev* ld, int k, void* scr, int bn,
-                                        hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+  template <typename T> void launch_fwd(const DepthList& D, const LayerDev* ld, int k,
+                                        void* scr, int bn, hipEvent_t t0 = nullptr,
+                                        hipEvent_t t1 = nullptr);
+  template <typename T> void launch_bwd(const DepthList& D, const LayerDev* ld, int k,
+                                        void* scr, int bn, hipEvent_t t0 = nullptr,
+                                        hipEvent_t t1 = nullptr);
 
   // kernel timing (HELM_FLAG_PROFILE: every class; HELM_FLAG_PROFILE_FWD:
   // the forward substitution GEMM only), one bit per KClass

@@ -60,23 +60,28 @@ struct FrontDev {
   int pad;
 };
 
-// The launch lists of a solve may carry flags in the top bits of a front id
-// (solves pruned to the fronts that touch their sources and read-outs): the
-// front's child 0 or 1 contributes nothing (its subtree holds no source), or
-// its forward result Z(S) is zero (no source below it, but a read-out).
-constexpr int kFrontIdMask = (1 << 27) - 1;
-constexpr int kSkipChild0 = 1 << 27;
-constexpr int kSkipChild1 = 1 << 28;
-constexpr int kZeroZ = 1 << 29;
-
-// Split of one front's substitution GEMMs along K (the pivot / boundary
-// dimension) into chunks computed by separate workgroups; partial products
-// go to a scratch area and are summed in a fixed order.
-struct SolveTask {
-  int nch_f, kc_f;   // forward: chunks, chunk length
-  int nch_b, kc_b;   // backward
-  long long scr_f;   // scratch row offset of the forward partials (nch_f x (s+b) rows)
-  long long scr_b;   // scratch row offset of the backward partials (nch_b x s rows)
+// One front in a launch list of the substitutions: everything a workgroup
+// needs in one record in list order (with its layer's pointers, a workgroup
+// reaches its operands through two dependent loads).  A list pruned to the
+// fronts that touch a solve's sources and read-outs drops a child without
+// sources (inv = -1) and marks a front without a forward result (zero_z).
+// The K dimension (pivots forward, boundary backward) of the GEMMs may be
+// split into nch chunks of kc computed by separate workgroups; the partial
+// products go to scratch rows from scr and are summed in a fixed order.
+struct SolveFront {
+  long long fac;     // element offset of [F11^-1; -F21 F11^-1] ((s+b) x s, col-major)
+  long long ub;      // row offset into the layer's update buffer
+  long long cub[2];  // the children's
+  long long scr;     // scratch row offset of the partial products
+  int s, b;          // pivots, boundary size
+  int off;           // ND index of the first pivot inside its layer
+  int layer;
+  int bidx;          // offset of the b sorted ND indices of the boundary
+  int inv[2];        // offsets of the front-row -> child-boundary maps (-1: no child)
+  int ub_parity;     // depth parity
+  int zero_z;        // the forward result Z(S) is zero (backward lists)
+  int nch, kc;       // chunks along K, chunk length
+  int pad;
 };
 
 // Per-layer base pointers for kernels that touch several layers at once.

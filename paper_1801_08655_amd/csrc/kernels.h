@@ -62,41 +62,38 @@ void launch_store_factor(const FrontDev* fronts, const int* ids, int n_ids,
                          const long long* perm_off, hipStream_t st);
 
 // --- substitutions (kernels_solve.hip) --------------------------------------
-template <typename T>
-void launch_fwd_gather(const FrontDev* fr, const int* ids, int n, const int2* tmap,
-                       int total, const LayerDev* layers, int k, hipStream_t st);
-template <typename T>
+// One depth of one solve: `list` the depth's fronts in launch order, `tmap`
+// the tile map of the launch (entry: list index, tile within the front).
 // t0 / t1 non-null: the launch records its own start and stop in them
 // (timing of the kernel alone, without event commands around it).
-void launch_fwd_gemm(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bn, hipStream_t st, hipEvent_t t0 = nullptr,
-                     hipEvent_t t1 = nullptr);
-// vector path of the substitutions for k <= 4 columns (same tiles and
-// scratch layout as launch_fwd_gemm / launch_bwd_gemm with 64-row tiles)
 template <typename T>
-void launch_fwd_gemv(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, hipStream_t st, hipEvent_t t0 = nullptr,
+void launch_fwd_gather(const SolveFront* list, const int2* tmap, int total,
+                       const LayerDev* layers, int k, hipStream_t st);
+template <typename T>
+void launch_fwd_gemm(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, void* scratch, int bn, hipStream_t st, hipEvent_t t0 = nullptr,
                      hipEvent_t t1 = nullptr);
 template <typename T>
-void launch_bwd_gemv(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bm, hipStream_t st, hipEvent_t t0 = nullptr,
-                     hipEvent_t t1 = nullptr);
+void launch_fwd_reduce(const SolveFront* list, const int2* tmap, int total,
+                       const LayerDev* layers, int k, const void* scratch, hipStream_t st);
 template <typename T>
-void launch_fwd_reduce(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                       const int2* tmap, int total, const LayerDev* layers, int k,
-                       const void* scratch, hipStream_t st);
-template <typename T>
-void launch_bwd_gemm(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bm, int bn, hipStream_t st,
+void launch_bwd_gemm(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, void* scratch, int bm, int bn, hipStream_t st,
                      hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 template <typename T>
-void launch_bwd_reduce(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                       const int2* tmap, int total, const LayerDev* layers, int k,
-                       const void* scratch, hipStream_t st);
+void launch_bwd_reduce(const SolveFront* list, const int2* tmap, int total,
+                       const LayerDev* layers, int k, const void* scratch, hipStream_t st);
+// vector path for k <= 4 columns: tiles of rtile (16, 32 or 64) rows forward
+// (1, 2: a wave per 64-row tile, every front of at most 64, 128 pivots), of
+// 8 rpg rows (rpg 1, 2, 4 or 8) backward
+template <typename T>
+void launch_fwd_gemv(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, int rtile, hipStream_t st, hipEvent_t t0 = nullptr,
+                     hipEvent_t t1 = nullptr);
+template <typename T>
+void launch_bwd_gemv(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, int rpg, hipStream_t st, hipEvent_t t0 = nullptr,
+                     hipEvent_t t1 = nullptr);
 
 // --- volumes, traces, Krylov (kernels_volume.hip) ---------------------------
 template <typename T>

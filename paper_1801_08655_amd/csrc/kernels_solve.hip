@@ -31,16 +31,12 @@ template <typename T> struct ChildSum {
   const C_t<T>* Uc;
   long long cub[2];
   const int* inv[2];
-  // raw: the list entry of the front (flags kSkipChild0/1 drop a child)
-  __device__ ChildSum(const FrontDev* fronts, const FrontDev& f, const LayerDev& L, int raw) {
+  __device__ __forceinline__ ChildSum(const SolveFront& f, const LayerDev& L) {
     Uc = reinterpret_cast<const C_t<T>*>(L.Ub[f.ub_parity ^ 1]);
+#pragma unroll
     for (int slot = 0; slot < 2; ++slot) {
-      cub[slot] = 0;
-      inv[slot] = nullptr;
-      if (f.child[slot] >= 0 && !(raw & (kSkipChild0 << slot))) {
-        cub[slot] = fronts[f.child[slot]].ub;
-        inv[slot] = L.inv + f.inv[slot];
-      }
+      cub[slot] = f.cub[slot];
+      inv[slot] = f.inv[slot] >= 0 ? L.inv + f.inv[slot] : nullptr;
     }
   }
   __device__ __forceinline__ C_t<T> operator()(int row, int col, int k) const {
@@ -59,18 +55,15 @@ template <typename T> struct ChildSum {
 // pivot rows, in place.  The boundary rows are summed in the GEMM epilogue.
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT)
-k_fwd_gather(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
-             int n_ids, const int2* __restrict__ tmap,
+k_fwd_gather(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
              const LayerDev* __restrict__ layers, int k) {
   using C = C_t<T>;
   const int2 tm = tmap[blockIdx.x];
-  const int a = tm.x;
-  const int raw = ids[a];
-  const FrontDev f = fronts[raw & kFrontIdMask];
+  const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int r0 = tm.y * RT;
   C* X = reinterpret_cast<C*>(L.X);
-  const ChildSum<T> cs(fronts, f, L, raw);
+  const ChildSum<T> cs(f, L);
   const int rows = (f.s - r0) < RT ? (f.s - r0) : RT;
   const int total = rows * k;
   // EPT elements (row, column) per thread and pass: child rows first, then
@@ -125,7 +118,7 @@ __device__ __forceinline__ void store_partial(const Acc& acc, C_t<T>* S, long lo
 // the results are stored, so that the latencies of each group of loads
 // overlap instead of following one another output by output.
 template <typename T, class O, class Acc>
-__device__ __forceinline__ void fwd_epilogue(const Acc& acc, const FrontDev& f,
+__device__ __forceinline__ void fwd_epilogue(const Acc& acc, const SolveFront& f,
                                              const ChildSum<T>& cs, C_t<T>* Z, C_t<T>* Uo,
                                              int m0, int n0, int k) {
   using C = C_t<T>;
@@ -176,35 +169,31 @@ template <typename T> constexpr bool split_form() { return sizeof(T) == 4; }
 
 template <typename T, int BN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(split_form<T>() ? 3 : 1, 8)))
-k_fwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
-           const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
+k_fwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
            const LayerDev* __restrict__ layers, int k, void* scratch) {
   using C = C_t<T>;
   constexpr int BM = FWD_BM;
   const int ntn = (k + BN - 1) / BN;
   const int mt = blockIdx.x / ntn, nt = blockIdx.x % ntn;
   const int2 tm = tmap[mt];
-  const int a = tm.x;
-  const int raw = ids[a];
-  const FrontDev f = fronts[raw & kFrontIdMask];
-  const SolveTask tk = tasks[a];
+  const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int n = f.s + f.b;
   const int local = tm.y;
-  const int chunk = local % tk.nch_f;
-  const int m0 = (local / tk.nch_f) * BM, n0 = nt * BN;
-  const int kb = chunk * tk.kc_f;
-  const int ke = min(f.s, kb + tk.kc_f);
+  const int chunk = local % f.nch;
+  const int m0 = (local / f.nch) * BM, n0 = nt * BN;
+  const int kb = chunk * f.kc;
+  const int ke = min(f.s, kb + f.kc);
   // P = FT (col-major, rows m), Q = X(S) (rows = pivots, columns = RHS)
   const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
   const C* X = reinterpret_cast<const C*>(L.X) + (long long)f.off * k;
   auto finish = [&](const auto& acc, auto out) {
     using O = decltype(out);
-    if (tk.nch_f > 1)
-      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), tk.scr_f + (long long)chunk * n, m0,
+    if (f.nch > 1)
+      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * n, m0,
                           n0, n, k);
     else
-      fwd_epilogue<T, O>(acc, f, ChildSum<T>(fronts, f, L, raw), reinterpret_cast<C*>(L.Wt),
+      fwd_epilogue<T, O>(acc, f, ChildSum<T>(f, L), reinterpret_cast<C*>(L.Wt),
                          ub_ptr<T>(L, f.ub_parity), m0, n0, k);
   };
   if constexpr (split_form<T>()) {
@@ -228,15 +217,11 @@ constexpr int RED_EPT = 4;
 // forward, step 3 (split fronts only): sum the chunk partials in order
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT)
-k_fwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
-             const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
+k_fwd_reduce(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
              const LayerDev* __restrict__ layers, int k, const void* scratch) {
   using C = C_t<T>;
   const int2 tm = tmap[blockIdx.x];
-  const int a = tm.x;
-  const int raw = ids[a];
-  const FrontDev f = fronts[raw & kFrontIdMask];
-  const SolveTask tk = tasks[a];
+  const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int n = f.s + f.b;
   const int r0 = tm.y * RT;
@@ -244,7 +229,7 @@ k_fwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const C* S = reinterpret_cast<const C*>(scratch);
   C* Z = reinterpret_cast<C*>(L.Wt);
   C* Uo = ub_ptr<T>(L, f.ub_parity);
-  const ChildSum<T> cs(fronts, f, L, raw);
+  const ChildSum<T> cs(f, L);
   // RED_EPT elements per thread at a time: all their loads, then the stores
   for (int e0 = 0; e0 < rows * k; e0 += NT * RED_EPT) {
     C z[RED_EPT];
@@ -254,8 +239,8 @@ k_fwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
       z[j] = czero<C>();
       if (e >= rows * k) continue;
       const int gm = r0 + e / k, gc = e % k;
-      for (int ch = 0; ch < tk.nch_f; ++ch)
-        z[j] = cadd(z[j], ld(S + (tk.scr_f + (long long)ch * n + gm) * k + gc));
+      for (int ch = 0; ch < f.nch; ++ch)
+        z[j] = cadd(z[j], ld(S + (f.scr + (long long)ch * n + gm) * k + gc));
       if (gm >= f.s) z[j] = cadd(z[j], cs(gm, gc, k));
     }
 #pragma unroll
@@ -274,32 +259,28 @@ k_fwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // optionally split.  Fronts without boundary (roots) just copy Z(S).
 template <typename T, int BM, int BN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(split_form<T>() ? 3 : 1, 8)))
-k_bwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
-           const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
+k_bwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
            const LayerDev* __restrict__ layers, int k, void* scratch) {
   using C = C_t<T>;
   const int ntn = (k + BN - 1) / BN;
   const int mt = blockIdx.x / ntn, nt = blockIdx.x % ntn;
   const int2 tm = tmap[mt];
-  const int a = tm.x;
-  const int raw = ids[a];
-  const FrontDev f = fronts[raw & kFrontIdMask];
-  const SolveTask tk = tasks[a];
+  const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int n = f.s + f.b;
   const int local = tm.y;
-  const int chunk = local % tk.nch_b;
-  const int m0 = (local / tk.nch_b) * BM, n0 = nt * BN;
-  const int kb = chunk * tk.kc_b;
-  const int ke = min(f.b, kb + tk.kc_b);
+  const int chunk = local % f.nch;
+  const int m0 = (local / f.nch) * BM, n0 = nt * BN;
+  const int kb = chunk * f.kc;
+  const int ke = min(f.b, kb + f.kc);
   // P(m, q) = FT[(s + q) + m n]  (transposed lower block, contiguous in q),
   // Q(q, c) = X[B[q] k + c]
   const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac + f.s;
   C* X = reinterpret_cast<C*>(L.X);
   auto finish = [&](const auto& acc, auto out) {
     using O = decltype(out);
-    if (tk.nch_b > 1) {
-      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), tk.scr_b + (long long)chunk * f.s,
+    if (f.nch > 1) {
+      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * f.s,
                           m0, n0, f.s, k);
       return;
     }
@@ -313,7 +294,7 @@ k_bwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 #pragma unroll
       for (int j = 0; j < O::NC; ++j) {
         const int gm = m0 + o.r[i], gc = n0 + o.c[j];
-        zv[i][j] = ld_or_zero(gm < f.s && gc < k && !(raw & kZeroZ),
+        zv[i][j] = ld_or_zero(gm < f.s && gc < k && !f.zero_z,
                               Z + (long long)(f.off + gm) * k + gc);
       }
 #pragma unroll
@@ -343,15 +324,11 @@ k_bwd_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT)
-k_bwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
-             const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
+k_bwd_reduce(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
              const LayerDev* __restrict__ layers, int k, const void* scratch) {
   using C = C_t<T>;
   const int2 tm = tmap[blockIdx.x];
-  const int a = tm.x;
-  const int raw = ids[a];
-  const FrontDev f = fronts[raw & kFrontIdMask];
-  const SolveTask tk = tasks[a];
+  const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int r0 = tm.y * RT;
   const int rows = min(RT, f.s - r0);
@@ -366,9 +343,9 @@ k_bwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
       z[j] = czero<C>();
       if (e >= rows * k) continue;
       const int gm = r0 + e / k, gc = e % k;
-      z[j] = ld_or_zero(!(raw & kZeroZ), Z + (long long)(f.off + gm) * k + gc);
-      for (int ch = 0; ch < tk.nch_b; ++ch)
-        z[j] = cadd(z[j], ld(S + (tk.scr_b + (long long)ch * f.s + gm) * k + gc));
+      z[j] = ld_or_zero(!f.zero_z, Z + (long long)(f.off + gm) * k + gc);
+      for (int ch = 0; ch < f.nch; ++ch)
+        z[j] = cadd(z[j], ld(S + (f.scr + (long long)ch * f.s + gm) * k + gc));
     }
 #pragma unroll
     for (int j = 0; j < RED_EPT; ++j) {
@@ -381,87 +358,222 @@ k_bwd_reduce(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 }
 
 // ---------------------------------------------------------------------------
-// Vector path for batches of KC <= KV columns (a template argument): the GEMMs above would pad
-// the columns to a 16-wide MFMA tile, so at k <= 4 the substitutions are
-// done with plain FMAs while streaming the factor blocks once, which makes
-// them bound by HBM bandwidth.  The tile and K-chunk decomposition (and the
-// scratch layout of split fronts) is the one of the MFMA kernels, so the
-// reduction kernels are shared.
+// Vector path for batches of KC <= 4 columns (a template argument): the GEMMs
+// above would pad the columns to a 16-wide MFMA tile, so the substitutions are
+// done with plain FMAs while streaming the factor blocks once.  Large fronts
+// are bound by HBM bandwidth, the others by the latency of the chain of
+// dependent loads in one launch, so a depth is one launch per pass: the
+// children's updates of the pivot rows are added while the right-hand side
+// is staged in LDS (no gather launch), and a depth with few tiles takes
+// narrower ones instead of a split K with a reduction launch.  Against
+// gather, GEMV and reduction launches, one pruned layer solve of one column:
+// 25^3 complex128 167 -> 103 us, 60^3 complex64 336 -> 219, 100^3 complex64
+// 476 -> 356 (factor blocks at 3 to 4 TB/s per launch) and complex128 627 ->
+// 561 (4 to 5 TB/s).
 // ---------------------------------------------------------------------------
-constexpr int KV = 4;
 
-// forward: one 64-row tile of one front and one K chunk per block; wave w
-// takes the pivot columns kb + w, kb + w + 4, ... and the 4 partial sums of
-// a row are added in LDS in fixed order.
-template <typename T, int KC>
+// forward: RTILE rows of one front per block (64, or 32 or 16 where 64-row
+// tiles are too few).  The 256 / RTILE threads of a row take the pivot columns
+// round robin; U columns are loaded ahead of the U being multiplied, and the
+// first ones before the right-hand side is staged.
+template <typename T, int KC, int RTILE>
 __global__ void __launch_bounds__(256)
-k_fwd_gemv(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
-           const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
-           const LayerDev* __restrict__ layers, int k, void* scratch) {
+k_fwd_gemv(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
+           const LayerDev* __restrict__ layers) {
   using C = C_t<T>;
-  __shared__ C red[3][64][KC];
-  const int mt = blockIdx.x;
-  const int2 tm = tmap[mt];
-  const int a = tm.x;
-  const int raw = ids[a];
-  const FrontDev f = fronts[raw & kFrontIdMask];
-  const SolveTask tk = tasks[a];
+  constexpr int NKP = 256 / RTILE, U = RTILE < 64 && sizeof(T) == 4 ? 16 : 8;
+  constexpr int QC = KC == 1 ? 1024 : (KC == 2 ? 512 : 256);   // pivots staged at a time
+  constexpr int EPT = QC * KC / 256;
+  static_assert(QC % (U * NKP) == 0, "whole batches per stage");
+  __shared__ C w[QC * KC];
+  __shared__ C red[3][RTILE][KC];
+  const int2 tm = tmap[blockIdx.x];
+  const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
-  const int n = f.s + f.b;
-  const int local = tm.y;
-  const int chunk = local % tk.nch_f;
-  const int m0 = (local / tk.nch_f) * 64;
-  const int kb = chunk * tk.kc_f;
-  const int ke = min(f.s, kb + tk.kc_f);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int m = m0 + lane;
-  const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
+  const int n = f.s + f.b, t = threadIdx.x;
+  const int row = t % RTILE, kp = t / RTILE;
+  const int m = tm.y * RTILE + row;
+  const C* col = reinterpret_cast<const C*>(L.fac) + f.fac + min(m, n - 1);
   const C* X = reinterpret_cast<const C*>(L.X) + (long long)f.off * KC;
+  const ChildSum<T> cs(f, L);
+  // the row's children's updates, in flight under everything that follows
+  C add[2][KC];
+#pragma unroll
+  for (int sl = 0; sl < 2; ++sl) {
+    const bool own = kp == 0 && m < n && m >= f.s && cs.inv[sl];
+    const int q = own ? ld(cs.inv[sl] + m) : -1;
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+      add[sl][c] = ld_or_zero(q >= 0, cs.Uc + (cs.cub[sl] + q) * KC + c);
+  }
   C acc[KC];
 #pragma unroll
   for (int c = 0; c < KC; ++c) acc[c] = czero<C>();
-  // q is the same for the whole wave: the right-hand-side values are
-  // loaded once per wave (scalar loads), the factor column by every lane
-  const int q0 = __builtin_amdgcn_readfirstlane(kb + w);
-  if (m < n) {
-#pragma unroll 4
-    for (int q = q0; q < ke; q += 4) {
-      const C fa = ld(FT + m + (long long)q * n);
-      const C* xq = X + (long long)q * KC;
+  for (int qb = 0; qb < f.s; qb += QC) {
+    const int nq = min(QC, f.s - qb);
+    C p[U], pn[U];
+    auto load = [&](C (&x)[U], int batch) {
 #pragma unroll
-      for (int c = 0; c < KC; ++c) cfma(acc[c], fa, ld(xq + c));
+      for (int u = 0; u < U; ++u) {
+        const int q = min(qb + (batch * U + u) * NKP + kp, f.s - 1);
+        x[u] = ld(col + (long long)q * n);
+      }
+    };
+    load(p, 0);
+    if (qb) __syncthreads();
+    // w = X(S) + children's updates, zero past the last pivot
+    {
+      int iq[2][EPT];
+      C v[EPT], u0[EPT], u1[EPT];
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) {
+        const int e = t + 256 * i, q = e / KC;
+        const bool ok = q < nq;
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+          iq[sl][i] = (ok && cs.inv[sl]) ? ld(cs.inv[sl] + qb + q) : -1;
+        v[i] = ld_or_zero(ok, X + (long long)qb * KC + e);
+      }
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) {
+        const int c = (t + 256 * i) % KC;
+        u0[i] = ld_or_zero(iq[0][i] >= 0, cs.Uc + (cs.cub[0] + iq[0][i]) * KC + c);
+        u1[i] = ld_or_zero(iq[1][i] >= 0, cs.Uc + (cs.cub[1] + iq[1][i]) * KC + c);
+      }
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) w[t + 256 * i] = cadd(v[i], cadd(u0[i], u1[i]));
+    }
+    __syncthreads();
+    const int nbatch = (nq + U * NKP - 1) / (U * NKP);
+    for (int b = 0; b < nbatch; ++b) {
+      if (b + 1 < nbatch) load(pn, b + 1);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const C* wq = &w[((b * U + u) * NKP + kp) * KC];
+#pragma unroll
+        for (int c = 0; c < KC; ++c) cfma(acc[c], p[u], wq[c]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) p[u] = pn[u];
     }
   }
-  if (w > 0) {
+  // the row's partial sums: the lanes of a wave, then the 4 waves, in order
 #pragma unroll
-    for (int c = 0; c < KC; ++c) red[w - 1][lane][c] = acc[c];
+  for (int c = 0; c < KC; ++c)
+#pragma unroll
+    for (int o = RTILE; o < 64; o <<= 1) {
+      acc[c].x += __shfl_xor(acc[c].x, o, 64);
+      acc[c].y += __shfl_xor(acc[c].y, o, 64);
+    }
+  const int wave = t >> 6;
+  if (wave > 0 && (t & 63) < RTILE) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c) red[wave - 1][row][c] = acc[c];
   }
   __syncthreads();
-  if (w != 0 || m >= n) return;
+  if (kp != 0 || m >= n) return;
   C* Z = reinterpret_cast<C*>(L.Wt);
   C* Uo = ub_ptr<T>(L, f.ub_parity);
-  C* S = reinterpret_cast<C*>(scratch);
-  const ChildSum<T> cs(fronts, f, L, raw);
-  C add[KC];
-#pragma unroll
-  for (int c = 0; c < KC; ++c) add[c] = czero<C>();
-  if (tk.nch_f == 1 && m >= f.s) {
-    // the row's children's updates, loaded before any store
-#pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-      const int q = cs.inv[sl] ? ld(cs.inv[sl] + m) : -1;
-      if (q >= 0) {
-#pragma unroll
-        for (int c = 0; c < KC; ++c) add[c] = cadd(add[c], ld(cs.Uc + (cs.cub[sl] + q) * KC + c));
-      }
-    }
-  }
 #pragma unroll
   for (int c = 0; c < KC; ++c) {
-    const C z = cadd(cadd(acc[c], red[0][lane][c]), cadd(red[1][lane][c], red[2][lane][c]));
-    if (tk.nch_f > 1) st(S + (tk.scr_f + (long long)chunk * n + m) * KC + c, z);
-    else if (m < f.s) st(Z + (long long)(f.off + m) * KC + c, z);
-    else st(Uo + (f.ub + m - f.s) * KC + c, cadd(z, add[c]));
+    const C z = cadd(cadd(acc[c], red[0][row][c]), cadd(red[1][row][c], red[2][row][c]));
+    if (m < f.s) st(Z + (long long)(f.off + m) * KC + c, z);
+    else st(Uo + (f.ub + m - f.s) * KC + c, cadd(z, cadd(add[0][c], add[1][c])));
+  }
+}
+
+// forward, depths whose fronts all have at most 64 NS pivots (the deep ones,
+// thousands of small fronts): one wave per 64-row tile, lane = row.  Lane q
+// holds the gathered right-hand side of pivots q, q + 64, ..., broadcast by
+// lane reads, so nothing waits at a barrier: the gather's two dependent loads
+// overlap the first U factor columns.
+template <typename T> __device__ __forceinline__ T lane_read(T v, int lane);
+template <> __device__ __forceinline__ float lane_read<float>(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+template <> __device__ __forceinline__ double lane_read<double>(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+template <typename T, int KC, int NS>
+__global__ void __launch_bounds__(256)
+k_fwd_gemv_wave(const SolveFront* __restrict__ list, const int2* __restrict__ tmap, int total,
+                const LayerDev* __restrict__ layers) {
+  using C = C_t<T>;
+  constexpr int U = 8;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = blockIdx.x * 4 + wave, lane = threadIdx.x & 63;
+  if (tile >= total) return;
+  const int2 tm = tmap[tile];
+  const SolveFront f = list[tm.x];
+  const LayerDev& L = layers[f.layer];
+  const int n = f.s + f.b, m = tm.y * 64 + lane;
+  const C* col = reinterpret_cast<const C*>(L.fac) + f.fac + min(m, n - 1);
+  const C* X = reinterpret_cast<const C*>(L.X) + (long long)f.off * KC;
+  const ChildSum<T> cs(f, L);
+  C p[U], pn[U];
+  auto load = [&](C (&x)[U], int q0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = ld(col + (long long)min(q0 + u, f.s - 1) * n);
+  };
+  load(p, 0);
+  // every index, then every value: the tile's boundary rows and the pivots
+  int iq[2][NS], im[2];
+#pragma unroll
+  for (int sl = 0; sl < 2; ++sl) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int q = lane + 64 * i;
+      iq[sl][i] = (q < f.s && cs.inv[sl]) ? ld(cs.inv[sl] + q) : -1;
+    }
+    im[sl] = (m >= f.s && m < n && cs.inv[sl]) ? ld(cs.inv[sl] + m) : -1;
+  }
+  C w[NS][KC], add[KC], acc[KC];
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    const C a0 = ld_or_zero(im[0] >= 0, cs.Uc + (cs.cub[0] + im[0]) * KC + c);
+    const C a1 = ld_or_zero(im[1] >= 0, cs.Uc + (cs.cub[1] + im[1]) * KC + c);
+    add[c] = cadd(a0, a1);
+    acc[c] = czero<C>();
+  }
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      const int q = lane + 64 * i;
+      const C x = ld_or_zero(q < f.s, X + (long long)q * KC + c);
+      const C u0 = ld_or_zero(iq[0][i] >= 0, cs.Uc + (cs.cub[0] + iq[0][i]) * KC + c);
+      const C u1 = ld_or_zero(iq[1][i] >= 0, cs.Uc + (cs.cub[1] + iq[1][i]) * KC + c);
+      w[i][c] = cadd(x, cadd(u0, u1));
+    }
+  // pivots in groups of U (past the last one the right-hand side is zero)
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    for (int q0 = 64 * i; q0 < 64 * (i + 1) && q0 < f.s; q0 += U) {
+      if (q0 + U < f.s) load(pn, q0 + U);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+          C x;
+          x.x = lane_read(w[i][c].x, q0 - 64 * i + u);
+          x.y = lane_read(w[i][c].y, q0 - 64 * i + u);
+          cfma(acc[c], p[u], x);
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u) p[u] = pn[u];
+    }
+  }
+  if (m >= n) return;
+  C* Z = reinterpret_cast<C*>(L.Wt);
+  C* Uo = ub_ptr<T>(L, f.ub_parity);
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    if (m < f.s) st(Z + (long long)(f.off + m) * KC + c, acc[c]);
+    else st(Uo + (f.ub + m - f.s) * KC + c, cadd(acc[c], add[c]));
   }
 }
 
@@ -469,39 +581,28 @@ template <typename T> __device__ __forceinline__ T shfl_xor_t(T v, int mask) {
   return __shfl_xor(v, mask, 64);
 }
 
-// backward: one BM-row tile (BM = 32 or 64) and one K chunk per block; the
-// 256 threads form 256 / GW groups of GW lanes and group g takes the rows
-// m0 + g, m0 + g + 256 / GW, ... (RPG of them) together: its lanes walk the
-// boundary index q (contiguous in the stored block), load X(B[q]) once for
-// all those rows and the factor entry of every row, so that several
-// independent factor loads are in flight per lane; a butterfly over the
-// group sums each row.
-template <typename T, int KC, int RPG, int GW = 16>
+// backward: 8 RPG rows of one front per block; the 256 threads form 8 groups
+// of 32 lanes and group g takes the rows m0 + g, m0 + g + 8, ... (RPG of
+// them) together: its lanes walk the boundary index q (contiguous in the
+// stored block), load X(B[q]) once for all those rows and the factor entry
+// of every row, so that several independent factor loads are in flight per
+// lane (fewer rows per group where the depth has few tiles, with more of the
+// boundary in flight instead).
+template <typename T, int KC, int RPG>
 __global__ void __launch_bounds__(256)
-k_bwd_gemv(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
-           const SolveTask* __restrict__ tasks, int n_ids, const int2* __restrict__ tmap,
-           const LayerDev* __restrict__ layers, int k, void* scratch) {
+k_bwd_gemv(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
+           const LayerDev* __restrict__ layers) {
   using C = C_t<T>;
-  constexpr int NG = 256 / GW;
-  constexpr int bm = NG * RPG;   // row tile
-  const int mt = blockIdx.x;
-  const int2 tm = tmap[mt];
-  const int a = tm.x;
-  const int raw = ids[a];
-  const FrontDev f = fronts[raw & kFrontIdMask];
-  const SolveTask tk = tasks[a];
+  constexpr int GW = 32, NG = 256 / GW;
+  const int2 tm = tmap[blockIdx.x];
+  const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int n = f.s + f.b;
-  const int local = tm.y;
-  const int chunk = local % tk.nch_b;
-  const int m0 = (local / tk.nch_b) * bm;
-  const int kb = chunk * tk.kc_b;
-  const int ke = min(f.b, kb + tk.kc_b);
+  const int m0 = tm.y * NG * RPG;
   const int g = threadIdx.x / GW, gl = threadIdx.x % GW;
   const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
   C* X = reinterpret_cast<C*>(L.X);
   const C* Z = reinterpret_cast<const C*>(L.Wt);
-  C* S = reinterpret_cast<C*>(scratch);
   const int* B = L.bidx + f.bidx;
   bool row_ok[RPG];
   const C* col[RPG];
@@ -511,13 +612,23 @@ k_bwd_gemv(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
     row_ok[r] = m < f.s;
     col[r] = FT + f.s + (long long)(row_ok[r] ? m : 0) * n;
   }
+  // the row and column this lane will write, and its forward result
+  int rsel = 0;
+#pragma unroll
+  for (int h = RPG / 2, off = GW / 2; h >= 1; h >>= 1, off >>= 1)
+    if (gl & off) rsel += h;
+  const int lo = gl & (GW / RPG - 1);
+  const int m = m0 + g + NG * rsel;
+  const bool mine = m < f.s && lo < KC;
+  const long long idx = (long long)(f.off + m) * KC + lo;
+  const C z0 = ld_or_zero(mine && !f.zero_z, Z + idx);
   C acc[RPG][KC];
 #pragma unroll
   for (int r = 0; r < RPG; ++r)
 #pragma unroll
     for (int c = 0; c < KC; ++c) acc[r][c] = czero<C>();
-#pragma unroll 2
-  for (int q = kb + gl; q < ke; q += GW) {
+#pragma unroll(RPG >= 4 ? 2 : (RPG == 2 ? 4 : 8))
+  for (int q = gl; q < f.b; q += GW) {
     const C* xb = X + (long long)ld(B + q) * KC;
     C fa[RPG], xv[KC];
 #pragma unroll
@@ -536,7 +647,6 @@ k_bwd_gemv(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   // share the row completes it (RPG = 8: 18 exchanges per column instead
   // of 80 for a butterfly per row)
   static_assert((RPG & (RPG - 1)) == 0 && RPG <= GW && KC <= GW / RPG, "group shape");
-  int rsel = 0;
 #pragma unroll
   for (int h = RPG / 2, off = GW / 2; h >= 1; h >>= 1, off >>= 1) {
     const bool up = (gl & off) != 0;
@@ -549,7 +659,6 @@ k_bwd_gemv(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
         acc[i][c].x = keep.x + shfl_xor_t(send.x, off);
         acc[i][c].y = keep.y + shfl_xor_t(send.y, off);
       }
-    if (up) rsel += h;
   }
 #pragma unroll
   for (int c = 0; c < KC; ++c)
@@ -558,33 +667,43 @@ k_bwd_gemv(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
       acc[0][c].x += shfl_xor_t(acc[0][c].x, off);
       acc[0][c].y += shfl_xor_t(acc[0][c].y, off);
     }
-  const int lo = gl & (GW / RPG - 1);
-  const int m = m0 + g + NG * rsel;
-  if (m < f.s && lo < KC) {
-    C z = acc[0][0];
+  if (!mine) return;
+  C z = acc[0][0];
 #pragma unroll
-    for (int c = 1; c < KC; ++c)
-      if (lo == c) z = acc[0][c];
-    const long long idx = (long long)(f.off + m) * KC + lo;
-    if (tk.nch_b > 1) st(S + (tk.scr_b + (long long)chunk * f.s + m) * KC + lo, z);
-    else st(X + idx, cadd(ld_or_zero(!(raw & kZeroZ), Z + idx), z));
-  }
+  for (int c = 1; c < KC; ++c)
+    if (lo == c) z = acc[0][c];
+  st(X + idx, cadd(z0, z));
 }
 
 }  // namespace
 
+// Launch with the start and stop events t0, t1 recorded by the launch itself
+// when given.
+#define HELM_SOLVE_LAUNCH(KERNEL, GRID, ...)                                               \
+  do {                                                                                     \
+    if (t0)                                                                                \
+      hipExtLaunchKernelGGL(KERNEL, dim3(GRID), dim3(256), 0, st, t0, t1, 0, __VA_ARGS__); \
+    else                                                                                   \
+      hipLaunchKernelGGL(KERNEL, dim3(GRID), dim3(256), 0, st, __VA_ARGS__);               \
+  } while (0)
+
 template <typename T>
-void launch_fwd_gemv(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
-  if (total_tiles <= 0) return;
-#define HELM_FWDV(KC_)                                                                      \
-  if (t0)                                                                                   \
-    hipExtLaunchKernelGGL((k_fwd_gemv<T, KC_>), dim3(total_tiles), dim3(256), 0, st, t0, t1, \
-                          0, fr, ids, tasks, n, tmap, layers, k, scratch);                  \
-  else                                                                                      \
-    hipLaunchKernelGGL((k_fwd_gemv<T, KC_>), dim3(total_tiles), dim3(256), 0, st, fr, ids,  \
-                       tasks, n, tmap, layers, k, scratch)
+void launch_fwd_gemv(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, int rtile, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+  if (total <= 0) return;
+  const int waves = (total + 3) / 4;   // rtile 1, 2: a wave per tile, 64 or 128 pivots
+#define HELM_FWDV(KC_)                                                                    \
+  switch (rtile) {                                                                        \
+    case 1:                                                                               \
+      HELM_SOLVE_LAUNCH((k_fwd_gemv_wave<T, KC_, 1>), waves, list, tmap, total, layers);  \
+      break;                                                                              \
+    case 2:                                                                               \
+      HELM_SOLVE_LAUNCH((k_fwd_gemv_wave<T, KC_, 2>), waves, list, tmap, total, layers);  \
+      break;                                                                              \
+    case 16: HELM_SOLVE_LAUNCH((k_fwd_gemv<T, KC_, 16>), total, list, tmap, layers); break; \
+    case 32: HELM_SOLVE_LAUNCH((k_fwd_gemv<T, KC_, 32>), total, list, tmap, layers); break; \
+    default: HELM_SOLVE_LAUNCH((k_fwd_gemv<T, KC_, 64>), total, list, tmap, layers); break; \
+  }
   switch (k) {
     case 1: HELM_FWDV(1); break;
     case 2: HELM_FWDV(2); break;
@@ -594,22 +713,15 @@ void launch_fwd_gemv(const FrontDev* fr, const int* ids, const SolveTask* tasks,
 #undef HELM_FWDV
 }
 template <typename T>
-void launch_bwd_gemv(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bm, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
-  if (total_tiles <= 0) return;
-#define HELM_BWDV1(RPG_, KC_)                                                              \
-  if (t0)                                                                                  \
-    hipExtLaunchKernelGGL((k_bwd_gemv<T, KC_, RPG_, 32>), dim3(total_tiles), dim3(256), 0, \
-                          st, t0, t1, 0, fr, ids, tasks, n, tmap, layers, k, scratch);     \
-  else                                                                                     \
-    hipLaunchKernelGGL((k_bwd_gemv<T, KC_, RPG_, 32>), dim3(total_tiles), dim3(256), 0,    \
-                       st, fr, ids, tasks, n, tmap, layers, k, scratch)
+void launch_bwd_gemv(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, int rpg, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+  if (total <= 0) return;
 #define HELM_BWDV(KC_)                                                                     \
-  if (bm == 32) {                                                                          \
-    HELM_BWDV1(4, KC_);                                                                    \
-  } else {                                                                                 \
-    HELM_BWDV1(8, KC_);                                                                    \
+  switch (rpg) {                                                                           \
+    case 1: HELM_SOLVE_LAUNCH((k_bwd_gemv<T, KC_, 1>), total, list, tmap, layers); break;  \
+    case 2: HELM_SOLVE_LAUNCH((k_bwd_gemv<T, KC_, 2>), total, list, tmap, layers); break;  \
+    case 4: HELM_SOLVE_LAUNCH((k_bwd_gemv<T, KC_, 4>), total, list, tmap, layers); break;  \
+    default: HELM_SOLVE_LAUNCH((k_bwd_gemv<T, KC_, 8>), total, list, tmap, layers); break; \
   }
   switch (k) {
     case 1: HELM_BWDV(1); break;
@@ -618,120 +730,85 @@ void launch_bwd_gemv(const FrontDev* fr, const int* ids, const SolveTask* tasks,
     default: HELM_BWDV(4); break;
   }
 #undef HELM_BWDV
-#undef HELM_BWDV1
 }
 
 template <typename T>
-void launch_fwd_gather(const FrontDev* fr, const int* ids, int n, const int2* tmap,
-                       int total, const LayerDev* layers, int k, hipStream_t st) {
+void launch_fwd_gather(const SolveFront* list, const int2* tmap, int total,
+                       const LayerDev* layers, int k, hipStream_t st) {
   if (total <= 0) return;
   // a tile is RT rows x k columns: one wave per tile for few columns
   if (k <= 4)
-    hipLaunchKernelGGL((k_fwd_gather<T, 64>), dim3(total), dim3(64), 0, st, fr, ids, n,
-                       tmap, layers, k);
+    hipLaunchKernelGGL((k_fwd_gather<T, 64>), dim3(total), dim3(64), 0, st, list, tmap, layers, k);
   else
-    hipLaunchKernelGGL((k_fwd_gather<T, 256>), dim3(total), dim3(256), 0, st, fr, ids, n,
-                       tmap, layers, k);
+    hipLaunchKernelGGL((k_fwd_gather<T, 256>), dim3(total), dim3(256), 0, st, list, tmap, layers,
+                       k);
 }
 template <typename T>
-void launch_fwd_gemm(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bn, hipStream_t st, hipEvent_t t0,
-                     hipEvent_t t1) {
-  if (total_tiles <= 0) return;
-  const int ntn = (k + bn - 1) / bn;
-  const dim3 grid(total_tiles * ntn);
-#define HELM_FWD(BN_)                                                                       \
-  if (t0)                                                                                   \
-    hipExtLaunchKernelGGL((k_fwd_gemm<T, BN_>), grid, dim3(256), 0, st, t0, t1, 0, fr, ids, \
-                          tasks, n, tmap, layers, k, scratch);                              \
-  else                                                                                      \
-    hipLaunchKernelGGL((k_fwd_gemm<T, BN_>), grid, dim3(256), 0, st, fr, ids, tasks, n,     \
-                       tmap, layers, k, scratch)
-  if (bn == 16) { HELM_FWD(16); } else if (bn == 32) { HELM_FWD(32); } else { HELM_FWD(64); }
-#undef HELM_FWD
+void launch_fwd_gemm(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, void* scratch, int bn, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+  if (total <= 0) return;
+  const int grid = total * ((k + bn - 1) / bn);
+  if (bn == 16) HELM_SOLVE_LAUNCH((k_fwd_gemm<T, 16>), grid, list, tmap, layers, k, scratch);
+  else if (bn == 32) HELM_SOLVE_LAUNCH((k_fwd_gemm<T, 32>), grid, list, tmap, layers, k, scratch);
+  else HELM_SOLVE_LAUNCH((k_fwd_gemm<T, 64>), grid, list, tmap, layers, k, scratch);
 }
 template <typename T>
-void launch_fwd_reduce(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                       const int2* tmap, int total, const LayerDev* layers, int k,
-                       const void* scratch, hipStream_t st) {
+void launch_fwd_reduce(const SolveFront* list, const int2* tmap, int total,
+                       const LayerDev* layers, int k, const void* scratch, hipStream_t st) {
   if (total <= 0) return;
   if (k <= 4)
-    hipLaunchKernelGGL((k_fwd_reduce<T, 64>), dim3(total), dim3(64), 0, st, fr, ids, tasks,
-                       n, tmap, layers, k, scratch);
+    hipLaunchKernelGGL((k_fwd_reduce<T, 64>), dim3(total), dim3(64), 0, st, list, tmap, layers, k,
+                       scratch);
   else
-    hipLaunchKernelGGL((k_fwd_reduce<T, 256>), dim3(total), dim3(256), 0, st, fr, ids, tasks,
-                       n, tmap, layers, k, scratch);
+    hipLaunchKernelGGL((k_fwd_reduce<T, 256>), dim3(total), dim3(256), 0, st, list, tmap, layers,
+                       k, scratch);
 }
 template <typename T>
-void launch_bwd_gemm(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                     const int2* tmap, int total_tiles, const LayerDev* layers, int k,
-                     void* scratch, int bm, int bn, hipStream_t st, hipEvent_t t0,
+void launch_bwd_gemm(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
+                     int k, void* scratch, int bm, int bn, hipStream_t st, hipEvent_t t0,
                      hipEvent_t t1) {
-  if (total_tiles <= 0) return;
+  if (total <= 0) return;
   // a 32 x 16 tile has fewer MFMA blocks than waves: use 32 columns there
   if (bm == 32 && bn == 16) bn = 32;
-  const int ntn = (k + bn - 1) / bn;
-  const dim3 grid(total_tiles * ntn);
-#define HELM_BWD(BM_, BN_)                                                                  \
-  if (t0)                                                                                   \
-    hipExtLaunchKernelGGL((k_bwd_gemm<T, BM_, BN_>), grid, dim3(256), 0, st, t0, t1, 0, fr, \
-                          ids, tasks, n, tmap, layers, k, scratch);                         \
-  else                                                                                      \
-    hipLaunchKernelGGL((k_bwd_gemm<T, BM_, BN_>), grid, dim3(256), 0, st, fr, ids, tasks,   \
-                       n, tmap, layers, k, scratch)
+  const int grid = total * ((k + bn - 1) / bn);
+#define HELM_BWD(BM_, BN_) \
+  HELM_SOLVE_LAUNCH((k_bwd_gemm<T, BM_, BN_>), grid, list, tmap, layers, k, scratch)
   if (bm == 32) {
-    if (bn == 32) { HELM_BWD(32, 32); } else { HELM_BWD(32, 64); }
+    if (bn == 32) HELM_BWD(32, 32); else HELM_BWD(32, 64);
   } else {
-    if (bn == 16) { HELM_BWD(64, 16); }
-    else if (bn == 32) { HELM_BWD(64, 32); }
-    else { HELM_BWD(64, 64); }
+    if (bn == 16) HELM_BWD(64, 16); else if (bn == 32) HELM_BWD(64, 32); else HELM_BWD(64, 64);
   }
 #undef HELM_BWD
 }
 template <typename T>
-void launch_bwd_reduce(const FrontDev* fr, const int* ids, const SolveTask* tasks, int n,
-                       const int2* tmap, int total, const LayerDev* layers, int k,
-                       const void* scratch, hipStream_t st) {
+void launch_bwd_reduce(const SolveFront* list, const int2* tmap, int total,
+                       const LayerDev* layers, int k, const void* scratch, hipStream_t st) {
   if (total <= 0) return;
   if (k <= 4)
-    hipLaunchKernelGGL((k_bwd_reduce<T, 64>), dim3(total), dim3(64), 0, st, fr, ids, tasks,
-                       n, tmap, layers, k, scratch);
+    hipLaunchKernelGGL((k_bwd_reduce<T, 64>), dim3(total), dim3(64), 0, st, list, tmap, layers, k,
+                       scratch);
   else
-    hipLaunchKernelGGL((k_bwd_reduce<T, 256>), dim3(total), dim3(256), 0, st, fr, ids, tasks,
-                       n, tmap, layers, k, scratch);
+    hipLaunchKernelGGL((k_bwd_reduce<T, 256>), dim3(total), dim3(256), 0, st, list, tmap, layers,
+                       k, scratch);
 }
 
-#define HELM_INST_SOLVE(T)                                                           \
-  template void launch_fwd_gather<T>(const FrontDev*, const int*, int, const int2*,   \
-                                     int, const LayerDev*, int, hipStream_t);        \
-  template void launch_fwd_gemm<T>(const FrontDev*, const int*, const SolveTask*,    \
-                                   int, const int2*, int, const LayerDev*, int,       \
-                                   void*, int, hipStream_t, hipEvent_t,               \
-                                   hipEvent_t);                                      \
-  template void launch_fwd_reduce<T>(const FrontDev*, const int*, const SolveTask*,  \
-                                     int, const int2*, int, const LayerDev*, int,     \
-                                     const void*, hipStream_t);                      \
-  template void launch_bwd_gemm<T>(const FrontDev*, const int*, const SolveTask*,    \
-                                   int, const int2*, int, const LayerDev*, int,       \
-                                   void*, int, int, hipStream_t, hipEvent_t,          \
-                                   hipEvent_t);                                      \
-  template void launch_bwd_reduce<T>(const FrontDev*, const int*, const SolveTask*,  \
-                                     int, const int2*, int, const LayerDev*, int,     \
-                                     const void*, hipStream_t);
+#define HELM_INST_SOLVE(T)                                                                     \
+  template void launch_fwd_gather<T>(const SolveFront*, const int2*, int, const LayerDev*,     \
+                                     int, hipStream_t);                                        \
+  template void launch_fwd_gemm<T>(const SolveFront*, const int2*, int, const LayerDev*, int,  \
+                                   void*, int, hipStream_t, hipEvent_t, hipEvent_t);           \
+  template void launch_fwd_reduce<T>(const SolveFront*, const int2*, int, const LayerDev*,     \
+                                     int, const void*, hipStream_t);                           \
+  template void launch_bwd_gemm<T>(const SolveFront*, const int2*, int, const LayerDev*, int,  \
+                                   void*, int, int, hipStream_t, hipEvent_t, hipEvent_t);      \
+  template void launch_bwd_reduce<T>(const SolveFront*, const int2*, int, const LayerDev*,     \
+                                     int, const void*, hipStream_t);                           \
+  template void launch_fwd_gemv<T>(const SolveFront*, const int2*, int, const LayerDev*, int,  \
+                                   int, hipStream_t, hipEvent_t, hipEvent_t);                  \
+  template void launch_bwd_gemv<T>(const SolveFront*, const int2*, int, const LayerDev*, int,  \
+                                   int, hipStream_t, hipEvent_t, hipEvent_t);
 HELM_INST_SOLVE(float)
 HELM_INST_SOLVE(double)
-
-#define HELM_INST_GEMV(T)                                                            \
-  template void launch_fwd_gemv<T>(const FrontDev*, const int*, const SolveTask*,    \
-                                   int, const int2*, int, const LayerDev*, int,       \
-                                   void*, hipStream_t, hipEvent_t, hipEvent_t);      \
-  template void launch_bwd_gemv<T>(const FrontDev*, const int*, const SolveTask*,    \
-                                   int, const int2*, int, const LayerDev*, int,       \
-                                   void*, int, hipStream_t, hipEvent_t, hipEvent_t);
-HELM_INST_GEMV(float)
-HELM_INST_GEMV(double)
-
 
 }  // namespace kern
 }  // namespace helm
