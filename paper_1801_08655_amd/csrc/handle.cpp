@@ -627,13 +627,19 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
   for (int l : layers) maxd = std::max(maxd, G.layers[l].max_depth);
   S->max_depth = maxd;
   // Split a front's K dimension when the depth has too few output tiles to
-  // fill the device: aim at ~2048 workgroups, chunks of >= 256.
-  const int target = 2048;
+  // fill the device: aim at `target` workgroups, chunks of >= kmin.  The
+  // partial products cost 2 k / kc of the factor bytes, their reduction a
+  // launch.  Pruned layer solves in us, (kmin, target) = (64, 512), (64, 768),
+  // (128, 1024), (256, 2048): complex128 97^3 at 21 columns 1051, 1045, 1066,
+  // 1113, at 64 columns 1954, 1940, 1989, 2107; complex64 60^3 at 64 columns
+  // 605, 623, 565, 624, 96^3 996, 1026, 999, 964, 160^3 at 32 columns 1503,
+  // 1461, 1464, 1467, 25^3 at 32 columns 199, 202, 208, 218.
+  const int target = prec == HELM_FP64 ? 768 : 1024, kmin = prec == HELM_FP64 ? 64 : 128;
   auto split = [&](long long tiles, int K, int& nch, int& kc) {
     nch = 1;
     if (K > 0 && tiles < target / 2) {
       long long want = (target + tiles - 1) / tiles;
-      nch = (int)std::max<long long>(1, std::min<long long>(want, K / 256));
+      nch = (int)std::max<long long>(1, std::min<long long>(want, K / kmin));
     }
     if (K <= 0) { nch = 1; kc = 16; return; }
     kc = (K + nch - 1) / nch;

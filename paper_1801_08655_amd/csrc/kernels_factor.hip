@@ -15,7 +15,7 @@
 // the transpose of -F21 F11^-1 in place of F11^-1 F12.
 #include "kernels.h"
 #include "kernels_common.h"
-#include "kernels_split.h"
+#include "kernels_tile.h"
 
 namespace helm {
 namespace kern {
@@ -983,13 +983,13 @@ k_swap_JO(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // wholly in J or in that block return at once.
 // Bound: the trailing entries streamed from and to HBM once per pivot block
 // (complex64 at 200^3: 5.7 TB; 3.5 TB/s) and the latency of a two-step
-// product between them.  complex64 runs on the split bf16 tile: 1916 -> 1639
+// product between them.  complex64 runs on the split bf16 tile: 1916 -> 1604
 // ms of a 200^3 factorization and 93 -> 80 ms of a 100^3 one against the FP32
-// tile.  Loading the tile's entries before the product needs 200 registers
+// tile (complex128 at 100^3: 186 -> 175).  Loading the tile's entries before the product needs 200 registers
 // (2 waves per SIMD): 1809 ms; kept at 3 waves it spills: 3688.
 // --------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2, 8)))
 k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
              int n_active, const int2* __restrict__ tmap, int k, int nb,
              void* ws0, void* ws1) {
@@ -1006,48 +1006,36 @@ k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const bool rowsJ = i0 >= k && i0 + GT <= k + nbf, colsJ = j0 >= k && j0 + GT <= k + nbf;
   if (rowsJ || colsJ || (i0 + GT <= k && j0 >= f.s)) return;   // uniform per block
   C* F = front_ptr<T>(ws0, ws1, f);
-  // F(i, j) -= product: every entry of the lane is loaded before the first
-  // store (one latency for the group instead of a load-store chain per entry)
-  auto subtract = [&](const auto& acc, auto out) {
-    using O = decltype(out);
-    const O o;
-    auto outside = [&](int gi, int gj) {
-      return gi < n && gj < n && (gi < k || gi >= k + nbf) && (gj < k || gj >= k + nbf) &&
-             !(gi < k && gj >= f.s);
-    };
-    C cv[O::NR][O::NC];
-#pragma unroll
-    for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-      for (int j = 0; j < O::NC; ++j) {
-        const int gi = i0 + o.c[j], gj = j0 + o.r[i];
-        cv[i][j] = ld_or_zero(outside(gi, gj), F + (long long)gi + (long long)gj * n);
-      }
-#pragma unroll
-    for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-      for (int j = 0; j < O::NC; ++j) {
-        const int gi = i0 + o.c[j], gj = j0 + o.r[i];
-        if (outside(gi, gj))
-          st(F + (long long)gi + (long long)gj * n, csub(cv[i][j], acc_at(acc, i, j)));
-      }
-  };
   // P rows = C columns j: B^T(j, q) = F[(k + q) + j n]
   // Q columns = C rows i: A^T(q, i) = F[i + (k + q) n]
-  if constexpr (sizeof(T) == 4) {
-    __shared__ SplitSmem<64> sm;
-    SplitAcc<64, 64> acc;
-    split_tile<64, 64, true, false>(sm, acc, SplitP{F + k, n, n},
-                                    SplitQ{F + (long long)k * n, n, n, nullptr}, j0, i0, 0, nbf);
-    subtract(acc, SplitOut<64, 64>());
-  } else {
-    __shared__ GemmSmem<T, 64, 64> sm;
-    WaveAcc<T, 64, 64> acc;
-    gemm_tile<T, 64, false, true>(sm, acc, View<T>{F + k, (long long)n, 1, n, nbf},
-                                  View<T>{F + (long long)k * n, 1, (long long)n, n, nbf}, j0, i0,
-                                  0, nbf);
-    subtract(acc, LaneOut<T, 64, 64>());
-  }
+  __shared__ TileSmem<T, 64> sm;
+  TileAcc<T, 64, 64> acc;
+  tile_gemm<T, 64, 64, true, false>(sm, acc, TileP<T>{F + k, n, n},
+                                    TileQ<T>{F + (long long)k * n, n, n, nullptr}, j0, i0, 0, nbf);
+  // F(i, j) -= product: every entry of the lane is loaded before the first
+  // store (one latency for the group instead of a load-store chain per entry)
+  using O = TileOut<T, 64, 64>;
+  const O o;
+  auto outside = [&](int gi, int gj) {
+    return gi < n && gj < n && (gi < k || gi >= k + nbf) && (gj < k || gj >= k + nbf) &&
+           !(gi < k && gj >= f.s);
+  };
+  C cv[O::NR][O::NC];
+#pragma unroll
+  for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+    for (int j = 0; j < O::NC; ++j) {
+      const int gi = i0 + o.c[j], gj = j0 + o.r[i];
+      cv[i][j] = ld_or_zero(outside(gi, gj), F + (long long)gi + (long long)gj * n);
+    }
+#pragma unroll
+  for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+    for (int j = 0; j < O::NC; ++j) {
+      const int gi = i0 + o.c[j], gj = j0 + o.r[i];
+      if (outside(gi, gj))
+        st(F + (long long)gi + (long long)gj * n, csub(cv[i][j], acc_at(acc, i, j)));
+    }
 }
 
 // --------------------------------------------------------------------------

@@ -13,7 +13,7 @@
 
 #include "kernels.h"
 #include "kernels_common.h"
-#include "kernels_split.h"
+#include "kernels_tile.h"
 
 namespace helm {
 namespace kern {
@@ -162,53 +162,45 @@ __device__ __forceinline__ void fwd_epilogue(const Acc& acc, const SolveFront& f
     }
 }
 
+// Occupancy asked of the compiler (waves per SIMD) for a tile of BN columns:
+// 4 for the complex64 tiles of 16 and 32 columns (128 registers), 3 for the
+// 64-column one (168); complex128 2.
+template <typename T> constexpr int tile_waves(int bn) {
+  return sizeof(T) == 4 ? (bn == 64 ? 3 : 4) : 2;
+}
+
 // forward, step 2: [X(S); Ub] = [F11^-1 w_S; Ub - F21 F11^-1 w_S], the K
 // (pivot) dimension optionally split into chunks (partials to scratch).
-// complex128 on the FP64 matrix cores, complex64 on the split tile.
-template <typename T> constexpr bool split_form() { return sizeof(T) == 4; }
-
 template <typename T, int BN>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(split_form<T>() ? 3 : 1, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tile_waves<T>(BN), 8)))
 k_fwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
            const LayerDev* __restrict__ layers, int k, void* scratch) {
   using C = C_t<T>;
   constexpr int BM = FWD_BM;
+  using O = TileOut<T, BM, BN>;
+  __shared__ TileSmem<T, BN> sm;
   const int ntn = (k + BN - 1) / BN;
   const int mt = blockIdx.x / ntn, nt = blockIdx.x % ntn;
   const int2 tm = tmap[mt];
   const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int n = f.s + f.b;
-  const int local = tm.y;
-  const int chunk = local % f.nch;
-  const int m0 = (local / f.nch) * BM, n0 = nt * BN;
+  const int chunk = tm.y % f.nch;
+  const int m0 = (tm.y / f.nch) * BM, n0 = nt * BN;
   const int kb = chunk * f.kc;
   const int ke = min(f.s, kb + f.kc);
   // P = FT (col-major, rows m), Q = X(S) (rows = pivots, columns = RHS)
   const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
   const C* X = reinterpret_cast<const C*>(L.X) + (long long)f.off * k;
-  auto finish = [&](const auto& acc, auto out) {
-    using O = decltype(out);
-    if (f.nch > 1)
-      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * n, m0,
-                          n0, n, k);
-    else
-      fwd_epilogue<T, O>(acc, f, ChildSum<T>(f, L), reinterpret_cast<C*>(L.Wt),
-                         ub_ptr<T>(L, f.ub_parity), m0, n0, k);
-  };
-  if constexpr (split_form<T>()) {
-    __shared__ SplitSmem<BN> sm;
-    SplitAcc<BM, BN> acc;
-    split_tile<BM, BN, false, false>(sm, acc, SplitP{FT, n, n}, SplitQ{X, k, k, nullptr}, m0, n0,
-                                     kb, ke);
-    finish(acc, SplitOut<BM, BN>());
-  } else {
-    __shared__ GemmSmem<T, BM, BN, true> sm;
-    WaveAcc<T, BM, BN> acc;
-    gemm_tile<T, BM, true, true>(sm, acc, View<T>{FT, 1, (long long)n, n, f.s},
-                                 View<T>{X, 1, (long long)k, k, f.s}, m0, n0, kb, ke);
-    finish(acc, LaneOut<T, BM, BN>());
-  }
+  TileAcc<T, BM, BN> acc;
+  tile_gemm<T, BM, BN, false, false>(sm, acc, TileP<T>{FT, n, n}, TileQ<T>{X, k, k, nullptr}, m0,
+                                     n0, kb, ke);
+  if (f.nch > 1)
+    store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * n, m0, n0,
+                        n, k);
+  else
+    fwd_epilogue<T, O>(acc, f, ChildSum<T>(f, L), reinterpret_cast<C*>(L.Wt),
+                       ub_ptr<T>(L, f.ub_parity), m0, n0, k);
 }
 
 // elements per thread and pass of the split-K reductions
@@ -258,68 +250,55 @@ k_fwd_reduce(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
 // through the front's boundary index list, the K (boundary) dimension
 // optionally split.  Fronts without boundary (roots) just copy Z(S).
 template <typename T, int BM, int BN>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(split_form<T>() ? 3 : 1, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tile_waves<T>(BN), 8)))
 k_bwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
            const LayerDev* __restrict__ layers, int k, void* scratch) {
   using C = C_t<T>;
+  using O = TileOut<T, BM, BN>;
+  __shared__ TileSmem<T, BN> sm;
   const int ntn = (k + BN - 1) / BN;
   const int mt = blockIdx.x / ntn, nt = blockIdx.x % ntn;
   const int2 tm = tmap[mt];
   const SolveFront f = list[tm.x];
   const LayerDev& L = layers[f.layer];
   const int n = f.s + f.b;
-  const int local = tm.y;
-  const int chunk = local % f.nch;
-  const int m0 = (local / f.nch) * BM, n0 = nt * BN;
+  const int chunk = tm.y % f.nch;
+  const int m0 = (tm.y / f.nch) * BM, n0 = nt * BN;
   const int kb = chunk * f.kc;
   const int ke = min(f.b, kb + f.kc);
   // P(m, q) = FT[(s + q) + m n]  (transposed lower block, contiguous in q),
   // Q(q, c) = X[B[q] k + c]
   const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac + f.s;
   C* X = reinterpret_cast<C*>(L.X);
-  auto finish = [&](const auto& acc, auto out) {
-    using O = decltype(out);
-    if (f.nch > 1) {
-      store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * f.s,
-                          m0, n0, f.s, k);
-      return;
-    }
-    // X(S) = Z(S) + product: every Z value of the lane is loaded before the
-    // first store (X and Z are distinct buffers, but the compiler cannot tell)
-    const O o;
-    const C* Z = reinterpret_cast<const C*>(L.Wt);
-    C zv[O::NR][O::NC];
-#pragma unroll
-    for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-      for (int j = 0; j < O::NC; ++j) {
-        const int gm = m0 + o.r[i], gc = n0 + o.c[j];
-        zv[i][j] = ld_or_zero(gm < f.s && gc < k && !f.zero_z,
-                              Z + (long long)(f.off + gm) * k + gc);
-      }
-#pragma unroll
-    for (int i = 0; i < O::NR; ++i)
-#pragma unroll
-      for (int j = 0; j < O::NC; ++j) {
-        const int gm = m0 + o.r[i], gc = n0 + o.c[j];
-        if (gm < f.s && gc < k)
-          st(X + (long long)(f.off + gm) * k + gc, cadd(zv[i][j], acc_at(acc, i, j)));
-      }
-  };
-  if constexpr (split_form<T>()) {
-    __shared__ SplitSmem<BN> sm;
-    SplitAcc<BM, BN> acc;
-    split_tile<BM, BN, true, true>(sm, acc, SplitP{FT, n, f.s}, SplitQ{X, k, k, L.bidx + f.bidx},
-                                   m0, n0, kb, ke);
-    finish(acc, SplitOut<BM, BN>());
-  } else {
-    __shared__ GemmSmem<T, BM, BN, false> sm;
-    WaveAcc<T, BM, BN> acc;
-    gemm_tile<T, BM, false, true>(sm, acc, View<T>{FT, (long long)n, 1, f.s, f.b},
-                                  View<T>{X, 1, (long long)k, k, f.b, L.bidx + f.bidx}, m0, n0,
-                                  kb, ke);
-    finish(acc, LaneOut<T, BM, BN>());
+  TileAcc<T, BM, BN> acc;
+  tile_gemm<T, BM, BN, true, true>(sm, acc, TileP<T>{FT, n, f.s},
+                                   TileQ<T>{X, k, k, L.bidx + f.bidx}, m0, n0, kb, ke);
+  if (f.nch > 1) {
+    store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * f.s, m0,
+                        n0, f.s, k);
+    return;
   }
+  // X(S) = Z(S) + product: every Z value of the lane is loaded before the
+  // first store (X and Z are distinct buffers, but the compiler cannot tell)
+  const O o;
+  const C* Z = reinterpret_cast<const C*>(L.Wt);
+  C zv[O::NR][O::NC];
+#pragma unroll
+  for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+    for (int j = 0; j < O::NC; ++j) {
+      const int gm = m0 + o.r[i], gc = n0 + o.c[j];
+      zv[i][j] = ld_or_zero(gm < f.s && gc < k && !f.zero_z,
+                            Z + (long long)(f.off + gm) * k + gc);
+    }
+#pragma unroll
+  for (int i = 0; i < O::NR; ++i)
+#pragma unroll
+    for (int j = 0; j < O::NC; ++j) {
+      const int gm = m0 + o.r[i], gc = n0 + o.c[j];
+      if (gm < f.s && gc < k)
+        st(X + (long long)(f.off + gm) * k + gc, cadd(zv[i][j], acc_at(acc, i, j)));
+    }
 }
 
 template <typename T, int NT>
@@ -444,18 +423,25 @@ k_fwd_gemv(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
       for (int i = 0; i < EPT; ++i) w[t + 256 * i] = cadd(v[i], cadd(u0[i], u1[i]));
     }
     __syncthreads();
+    // two batches in turn, the loads of one (past the end: the last column
+    // again) issued before the products of the other
     const int nbatch = (nq + U * NKP - 1) / (U * NKP);
-    for (int b = 0; b < nbatch; ++b) {
-      if (b + 1 < nbatch) load(pn, b + 1);
+    auto use = [&](const C (&x)[U], int b) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const C* wq = &w[((b * U + u) * NKP + kp) * KC];
 #pragma unroll
-        for (int c = 0; c < KC; ++c) cfma(acc[c], p[u], wq[c]);
+        for (int c = 0; c < KC; ++c) cfma(acc[c], x[u], wq[c]);
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) p[u] = pn[u];
+    };
+    int b = 0;
+    for (; b + 2 <= nbatch; b += 2) {
+      load(pn, b + 1);
+      use(p, b);
+      load(p, b + 2);
+      use(pn, b + 1);
     }
+    if (b < nbatch) use(p, b);
   }
   // the row's partial sums: the lanes of a wave, then the 4 waves, in order
 #pragma unroll
@@ -549,24 +535,27 @@ k_fwd_gemv_wave(const SolveFront* __restrict__ list, const int2* __restrict__ tm
       const C u1 = ld_or_zero(iq[1][i] >= 0, cs.Uc + (cs.cub[1] + iq[1][i]) * KC + c);
       w[i][c] = cadd(x, cadd(u0, u1));
     }
-  // pivots in groups of U (past the last one the right-hand side is zero)
+  // pivots in groups of U, two in turn (past the last pivot the right-hand
+  // side is zero and the loads repeat the last column)
+  auto use = [&](const C (&x)[U], const C (&wi)[KC], int q0) {
 #pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    for (int q0 = 64 * i; q0 < 64 * (i + 1) && q0 < f.s; q0 += U) {
-      if (q0 + U < f.s) load(pn, q0 + U);
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int c = 0; c < KC; ++c) {
+        C v;
+        v.x = lane_read(wi[c].x, q0 + u);
+        v.y = lane_read(wi[c].y, q0 + u);
+        cfma(acc[c], x[u], v);
+      }
+  };
 #pragma unroll
-        for (int c = 0; c < KC; ++c) {
-          C x;
-          x.x = lane_read(w[i][c].x, q0 - 64 * i + u);
-          x.y = lane_read(w[i][c].y, q0 - 64 * i + u);
-          cfma(acc[c], p[u], x);
-        }
-#pragma unroll
-      for (int u = 0; u < U; ++u) p[u] = pn[u];
+  for (int i = 0; i < NS; ++i)
+    for (int q0 = 0; q0 < 64 && 64 * i + q0 < f.s; q0 += 2 * U) {
+      load(pn, 64 * i + q0 + U);
+      use(p, w[i], q0);
+      load(p, 64 * i + q0 + 2 * U);
+      use(pn, w[i], q0 + U);
     }
-  }
   if (m >= n) return;
   C* Z = reinterpret_cast<C*>(L.Wt);
   C* Uo = ub_ptr<T>(L, f.ub_parity);
@@ -745,12 +734,14 @@ void launch_fwd_gather(const SolveFront* list, const int2* tmap, int total,
 }
 template <typename T>
 void launch_fwd_gemm(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
-                     int k, void* scratch, int bn, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+                     int k, void* scratch, int bn, hipStream_t st, hipEvent_t t0,
+                     hipEvent_t t1) {
   if (total <= 0) return;
   const int grid = total * ((k + bn - 1) / bn);
-  if (bn == 16) HELM_SOLVE_LAUNCH((k_fwd_gemm<T, 16>), grid, list, tmap, layers, k, scratch);
-  else if (bn == 32) HELM_SOLVE_LAUNCH((k_fwd_gemm<T, 32>), grid, list, tmap, layers, k, scratch);
-  else HELM_SOLVE_LAUNCH((k_fwd_gemm<T, 64>), grid, list, tmap, layers, k, scratch);
+#define HELM_FWD(BN_) \
+  HELM_SOLVE_LAUNCH((k_fwd_gemm<T, BN_>), grid, list, tmap, layers, k, scratch)
+  if (bn == 16) HELM_FWD(16); else if (bn == 32) HELM_FWD(32); else HELM_FWD(64);
+#undef HELM_FWD
 }
 template <typename T>
 void launch_fwd_reduce(const SolveFront* list, const int2* tmap, int total,
