@@ -629,12 +629,12 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
   // Split a front's K dimension when the depth has too few output tiles to
   // fill the device: aim at `target` workgroups, chunks of >= kmin.  The
   // partial products cost 2 k / kc of the factor bytes, their reduction a
-  // launch.  Pruned layer solves in us, (kmin, target) = (64, 512), (64, 768),
-  // (128, 1024), (256, 2048): complex128 97^3 at 21 columns 1051, 1045, 1066,
-  // 1113, at 64 columns 1954, 1940, 1989, 2107; complex64 60^3 at 64 columns
-  // 605, 623, 565, 624, 96^3 996, 1026, 999, 964, 160^3 at 32 columns 1503,
-  // 1461, 1464, 1467, 25^3 at 32 columns 199, 202, 208, 218.
-  const int target = prec == HELM_FP64 ? 768 : 1024, kmin = prec == HELM_FP64 ? 64 : 128;
+  // launch.  Pruned layer solves in us, (kmin, target) = (64, 512), (64, 1024),
+  // (128, 1024), (128, 2048): complex128 97^3 at 21 columns 1015, 1027, -,
+  // 1042, at 64 columns 1882, 1928, -, 1929; complex64 25^3 at 32 columns 183,
+  // 185, 199, 197, 96^3 at 64 columns 904, 946, 911, 920, 160^3 at 32 columns
+  // 1486, 1446, 1428, 1487.
+  const int target = 768, kmin = 64;
   auto split = [&](long long tiles, int K, int& nch, int& kc) {
     nch = 1;
     if (K > 0 && tiles < target / 2) {

@@ -13,6 +13,18 @@ struct ReadTerms {
   double ca[3], cb[3];
   int planes;
 };
+// Up to two read-outs of one layer's solution in one launch: out (a|b) =
+// sx R(X)(a|b) + terms, R the bottom or the top pair of planes.
+struct ReadOut {
+  int bottom;
+  double sx;
+  ReadTerms terms;
+  double2* out;
+};
+struct ReadOuts {
+  ReadOut r[2];
+  int n;
+};
 
 // --- factorization (kernels_factor.hip) -------------------------------------
 // Device record of a factorization: flag set on an exact-zero or non-finite
@@ -115,9 +127,14 @@ struct JumpTerms {
 template <typename T>
 void launch_jump(const LayerDev& L, const JumpTerms& t, const double2* B, int bottom, int nx,
                  int ny, int k, hipStream_t st);
+// X = the interface sources of the layer's top and bottom (no terms: none),
+// zero elsewhere
 template <typename T>
-void launch_readout(const LayerDev& L, int bottom, double sx, const ReadTerms& terms,
-                    double2* out, int nx, int ny, int k, hipStream_t st);
+void launch_sources(const LayerDev& L, const JumpTerms& top, const JumpTerms& bot,
+                    const double2* B, int nx, int ny, int k, hipStream_t st);
+template <typename T>
+void launch_readout(const LayerDev& L, const ReadOuts& ro, int nx, int ny, int k,
+                    hipStream_t st);
 
 void launch_dot(const double2* x, const double2* y, long long V, int k,
                 double2* partial, double2* out, hipStream_t st);

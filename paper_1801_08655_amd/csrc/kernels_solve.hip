@@ -39,16 +39,6 @@ template <typename T> struct ChildSum {
       inv[slot] = f.inv[slot] >= 0 ? L.inv + f.inv[slot] : nullptr;
     }
   }
-  __device__ __forceinline__ C_t<T> operator()(int row, int col, int k) const {
-    C_t<T> v = czero<C_t<T>>();
-#pragma unroll
-    for (int slot = 0; slot < 2; ++slot)
-      if (inv[slot]) {
-        const int q = ld(inv[slot] + row);
-        if (q >= 0) v = cadd(v, ld(Uc + (cub[slot] + q) * k + col));
-      }
-    return v;
-  }
 };
 
 // forward, step 1 (fronts with children): X(S) += children's updates on the
@@ -203,8 +193,33 @@ k_fwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
                        ub_ptr<T>(L, f.ub_parity), m0, n0, k);
 }
 
-// elements per thread and pass of the split-K reductions
-constexpr int RED_EPT = 4;
+// elements per thread and pass of the split-K reductions, and chunks whose
+// partial products are loaded together (one latency for the group)
+constexpr int RED_EPT = 4, RED_CH = 4;
+
+// z[j] += the partial products of element gm[j], gc[j] (gm < 0: none), in
+// order of the chunks; `rows` partial rows per chunk from row0.
+template <typename T>
+__device__ __forceinline__ void add_partials(C_t<T> (&z)[RED_EPT], const int (&gm)[RED_EPT],
+                                             const int (&gc)[RED_EPT], const C_t<T>* S,
+                                             long long row0, int rows, int nch, int k) {
+  using C = C_t<T>;
+  for (int c0 = 0; c0 < nch; c0 += RED_CH) {
+    C v[RED_CH][RED_EPT];
+#pragma unroll
+    for (int i = 0; i < RED_CH; ++i)
+#pragma unroll
+      for (int j = 0; j < RED_EPT; ++j) {
+        const bool ok = gm[j] >= 0 && c0 + i < nch;
+        v[i][j] = ld_or_zero(ok, S + (ok ? (row0 + (long long)(c0 + i) * rows + gm[j]) * k + gc[j]
+                                         : 0));
+      }
+#pragma unroll
+    for (int i = 0; i < RED_CH; ++i)
+#pragma unroll
+      for (int j = 0; j < RED_EPT; ++j) z[j] = cadd(z[j], v[i][j]);
+  }
+}
 
 // forward, step 3 (split fronts only): sum the chunk partials in order
 template <typename T, int NT>
@@ -224,24 +239,30 @@ k_fwd_reduce(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
   const ChildSum<T> cs(f, L);
   // RED_EPT elements per thread at a time: all their loads, then the stores
   for (int e0 = 0; e0 < rows * k; e0 += NT * RED_EPT) {
-    C z[RED_EPT];
+    int gm[RED_EPT], gc[RED_EPT], q[2][RED_EPT];
+    C z[RED_EPT], u[2][RED_EPT];
 #pragma unroll
     for (int j = 0; j < RED_EPT; ++j) {
       const int e = e0 + (int)threadIdx.x + j * NT;
+      gm[j] = e < rows * k ? r0 + e / k : -1;
+      gc[j] = e % k;
       z[j] = czero<C>();
-      if (e >= rows * k) continue;
-      const int gm = r0 + e / k, gc = e % k;
-      for (int ch = 0; ch < f.nch; ++ch)
-        z[j] = cadd(z[j], ld(S + (f.scr + (long long)ch * n + gm) * k + gc));
-      if (gm >= f.s) z[j] = cadd(z[j], cs(gm, gc, k));
+      // (a boundary row takes its children's updates)
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+        q[sl][j] = (gm[j] >= f.s && cs.inv[sl]) ? ld(cs.inv[sl] + gm[j]) : -1;
     }
 #pragma unroll
+    for (int j = 0; j < RED_EPT; ++j)
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+        u[sl][j] = ld_or_zero(q[sl][j] >= 0, cs.Uc + (cs.cub[sl] + q[sl][j]) * k + gc[j]);
+    add_partials<T>(z, gm, gc, S, f.scr, n, f.nch, k);
+#pragma unroll
     for (int j = 0; j < RED_EPT; ++j) {
-      const int e = e0 + (int)threadIdx.x + j * NT;
-      if (e >= rows * k) continue;
-      const int gm = r0 + e / k, gc = e % k;
-      if (gm < f.s) st(Z + (long long)(f.off + gm) * k + gc, z[j]);
-      else st(Uo + (f.ub + gm - f.s) * k + gc, z[j]);
+      if (gm[j] < 0) continue;
+      if (gm[j] < f.s) st(Z + (long long)(f.off + gm[j]) * k + gc[j], z[j]);
+      else st(Uo + (f.ub + gm[j] - f.s) * k + gc[j], cadd(z[j], cadd(u[0][j], u[1][j])));
     }
   }
 }
@@ -315,24 +336,20 @@ k_bwd_reduce(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
   C* X = reinterpret_cast<C*>(L.X);
   const C* Z = reinterpret_cast<const C*>(L.Wt);
   for (int e0 = 0; e0 < rows * k; e0 += NT * RED_EPT) {
+    int gm[RED_EPT], gc[RED_EPT];
     C z[RED_EPT];
 #pragma unroll
     for (int j = 0; j < RED_EPT; ++j) {
       const int e = e0 + (int)threadIdx.x + j * NT;
-      z[j] = czero<C>();
-      if (e >= rows * k) continue;
-      const int gm = r0 + e / k, gc = e % k;
-      z[j] = ld_or_zero(!f.zero_z, Z + (long long)(f.off + gm) * k + gc);
-      for (int ch = 0; ch < f.nch; ++ch)
-        z[j] = cadd(z[j], ld(S + (f.scr + (long long)ch * f.s + gm) * k + gc));
+      gm[j] = e < rows * k ? r0 + e / k : -1;
+      gc[j] = e % k;
+      const bool ok = gm[j] >= 0 && !f.zero_z;
+      z[j] = ld_or_zero(ok, Z + (ok ? (long long)(f.off + gm[j]) * k + gc[j] : 0));
     }
+    add_partials<T>(z, gm, gc, S, f.scr, f.s, f.nch, k);
 #pragma unroll
-    for (int j = 0; j < RED_EPT; ++j) {
-      const int e = e0 + (int)threadIdx.x + j * NT;
-      if (e >= rows * k) continue;
-      const int gm = r0 + e / k, gc = e % k;
-      st(X + (long long)(f.off + gm) * k + gc, z[j]);
-    }
+    for (int j = 0; j < RED_EPT; ++j)
+      if (gm[j] >= 0) st(X + (long long)(f.off + gm[j]) * k + gc[j], z[j]);
   }
 }
 

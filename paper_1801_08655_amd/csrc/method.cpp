@@ -83,11 +83,29 @@ void Method::jump(int l, const double2* a, const double2* b, int bottom, double 
   if (H.prec == HELM_FP64) jump_t<double>(l, t, bottom); else jump_t<float>(l, t, bottom);
 }
 
-void Method::readout(int l, int bottom, double sx, const kern::ReadTerms& t, double2* out) {
+void Method::sources(int l, const kern::JumpTerms& top, const kern::JumpTerms& bot) {
+  const LayerDev& L = H.layers_h[l];
+  const double2* B = H.Bcoef.as<double2>();
   if (H.prec == HELM_FP64)
-    kern::launch_readout<double>(H.layers_h[l], bottom, sx, t, out, H.G.nx, H.G.ny, k, H.st);
+    kern::launch_sources<double>(L, top, bot, B, H.G.nx, H.G.ny, k, H.st);
   else
-    kern::launch_readout<float>(H.layers_h[l], bottom, sx, t, out, H.G.nx, H.G.ny, k, H.st);
+    kern::launch_sources<float>(L, top, bot, B, H.G.nx, H.G.ny, k, H.st);
+}
+
+void Method::readouts(int l, const kern::ReadOuts& ro) {
+  if (H.prec == HELM_FP64)
+    kern::launch_readout<double>(H.layers_h[l], ro, H.G.nx, H.G.ny, k, H.st);
+  else
+    kern::launch_readout<float>(H.layers_h[l], ro, H.G.nx, H.G.ny, k, H.st);
+}
+
+void Method::readout(int l, int bottom, double sx, const kern::ReadTerms& t, double2* out) {
+  readouts(l, kern::ReadOuts{{{bottom, sx, t, out}, {}}, 1});
+}
+
+void Method::readout_both(int l, const kern::ReadTerms& tb, double2* ob,
+                          const kern::ReadTerms& tt, double2* ot) {
+  readouts(l, kern::ReadOuts{{{1, 1.0, tb, ob}, {0, 1.0, tt, ot}}, 2});
 }
 
 kern::ReadTerms Method::planes(kern::ReadTerms t, int mask) {
@@ -125,15 +143,12 @@ void Method::apply_P(const double2* vd, const double2* vu, double2* od, double2*
   readout(0, 1, 0.0, terms(pair(vd, 0), -1, -1), pair(od, 0));
   constexpr int T = kPruneTop, B = kPruneBottom;
   for (int l = 1; l <= L - 2; ++l) {
-    zero_X(l);
-    jump(l, pair(od, l - 1), nullptr, 0);
+    sources(l, jt(pair(od, l - 1)), jt());
     solve_planes(l, T, T | B);
-    readout(l, 1, 1.0, terms(pair(vd, l), -1, -1), pair(od, l));
-    readout(l, 0, 1.0, terms(), pair(kp, l - 1));
+    readout_both(l, terms(pair(vd, l), -1, -1), pair(od, l), terms(), pair(kp, l - 1));
   }
   // last layer: only the reflection term is needed
-  zero_X(L - 1);
-  jump(L - 1, pair(od, L - 2), nullptr, 0);
+  sources(L - 1, jt(pair(od, L - 2)), jt());
   solve_planes(L - 1, T, T);
   readout(L - 1, 0, 1.0, terms(), pair(kp, L - 2));
   // upward: z_up_{L-2} = keep_{L-1} - (0, z_down_{L-2,b}) - v_up_{L-2}
@@ -142,8 +157,7 @@ void Method::apply_P(const double2* vd, const double2* vu, double2* od, double2*
                 vu ? pair(vu, L - 2) : nullptr, -1, -1),
           pair(ou, L - 2));
   for (int j = L - 3; j >= 0; --j) {
-    zero_X(j + 1);
-    jump(j + 1, pair(ou, j + 1), pair(od, j + 1), 1);
+    sources(j + 1, jt(), jt(pair(ou, j + 1), 1.0, pair(od, j + 1), 1.0));
     solve_planes(j + 1, B, T);
     readout(j + 1, 0, 1.0,
             terms(pair(kp, j), 1, 1, pair(od, j), 0, -1, vu ? pair(vu, j) : nullptr, -1, -1),
@@ -155,9 +169,7 @@ void Method::apply_P(const double2* vd, const double2* vu, double2* od, double2*
 void Method::apply_U(const double2* xu, double2* out) {
   const int L = H.G.L;
   for (int l = 0; l <= L - 2; ++l) {
-    zero_X(l);
-    if (l >= 1) jump(l, pair(xu, l - 1), nullptr, 0);
-    jump(l, pair(xu, l), nullptr, 1);
+    sources(l, l >= 1 ? jt(pair(xu, l - 1)) : jt(), jt(pair(xu, l)));
   }
   H.solve_layers(*set_lower, k);
   for (int l = 0; l <= L - 2; ++l)
@@ -185,29 +197,24 @@ void Method::apply_A(const double2* x, double2* out) {
   if (L >= 2) {
     // z_down_0 = -(U x_up)_0
     constexpr int T = kPruneTop, B = kPruneBottom;
-    zero_X(0);
-    jump(0, pair(xu, 0), nullptr, 1, -1.0);
+    sources(0, jt(), jt(pair(xu, 0), -1.0));
     solve_planes(0, B, B);
     readout(0, 1, 1.0, terms(pair(xu, 0), 1, 0), pair(od, 0));
     for (int l = 1; l <= L - 2; ++l) {
-      zero_X(l);
-      jump(l, pair(od, l - 1), pair(xu, l - 1), 0, 1.0, -1.0);
-      jump(l, pair(xu, l), nullptr, 1, -1.0);
+      sources(l, jt(pair(od, l - 1), 1.0, pair(xu, l - 1), -1.0), jt(pair(xu, l), -1.0));
       solve_planes(l, T | B, T | B);
-      readout(l, 1, 1.0, terms(pair(xu, l), 1, 0), pair(od, l));
-      readout(l, 0, 1.0, terms(), pair(kp, l - 1));      // keep_{l-1} - V_{l-1}
+      // (the top read-out is keep_{l-1} - V_{l-1})
+      readout_both(l, terms(pair(xu, l), 1, 0), pair(od, l), terms(), pair(kp, l - 1));
     }
-    zero_X(L - 1);
-    jump(L - 1, pair(od, L - 2), nullptr, 0);
+    sources(L - 1, jt(pair(od, L - 2)), jt());
     solve_planes(L - 1, T, T);
     readout(L - 1, 0, 1.0, terms(), pair(kp, L - 2));    // keep_{L-2}
     // upward: z_up_{L-2} = keep_{L-2} - (0, z_down_{L-2,b})
     readout(L - 1, 0, 0.0, terms(pair(kp, L - 2), 1, 1, pair(od, L - 2), 0, -1),
             pair(ou, L - 2));
     for (int j = L - 3; j >= 0; --j) {
-      zero_X(j + 1);
-      jump(j + 1, pair(ou, j + 1), pair(od, j + 1), 1, 1.0, 1.0, pair(xu, j + 1), 1.0);
-      jump(j + 1, pair(xu, j), nullptr, 0);
+      sources(j + 1, jt(pair(xu, j)),
+              jt(pair(ou, j + 1), 1.0, pair(od, j + 1), 1.0, pair(xu, j + 1), 1.0));
       solve_planes(j + 1, T | B, T);
       readout(j + 1, 0, 1.0, terms(pair(kp, j), 1, 1, pair(od, j), 0, -1), pair(ou, j));
     }
@@ -256,13 +263,14 @@ void Method::precondition_source(const double2* f, double2* od, double2* ou) {
       kern::launch_scatter_source<float>(H.layers_h[l], f, H.G.nx, H.G.ny, N, k, H.st);
     if (l >= 1) jump(l, pair(od, l - 1), nullptr, 0);
     solve_planes(l, kPruneAll, T | B);   // volume source: every front forward
-    if (l <= L - 2) readout(l, 1, 1.0, terms(), pair(od, l));
-    if (l >= 1) readout(l, 0, 1.0, terms(), pair(kp, l - 1));   // keep_{l-1} - f_up_{l-1}
+    // (the top read-out is keep_{l-1} - f_up_{l-1})
+    if (l >= 1 && l <= L - 2) readout_both(l, terms(), pair(od, l), terms(), pair(kp, l - 1));
+    else if (l == 0) readout(l, 1, 1.0, terms(), pair(od, l));
+    else readout(l, 0, 1.0, terms(), pair(kp, l - 1));
   }
   readout(L - 1, 0, 0.0, terms(pair(kp, L - 2), 1, 1, pair(od, L - 2), 0, -1), pair(ou, L - 2));
   for (int j = L - 3; j >= 0; --j) {
-    zero_X(j + 1);
-    jump(j + 1, pair(ou, j + 1), pair(od, j + 1), 1);
+    sources(j + 1, jt(), jt(pair(ou, j + 1), 1.0, pair(od, j + 1), 1.0));
     solve_planes(j + 1, B, T);
     readout(j + 1, 0, 1.0, terms(pair(kp, j), 1, 1, pair(od, j), 0, -1), pair(ou, j));
   }
@@ -699,9 +707,7 @@ int Method::bicgstab(const KrylovSystem& S, const double2* b, double2* x,
 void Method::apply_sie(const double2* x, double2* out) {
   const int L = H.G.L;
   for (int l = 0; l < L; ++l) {
-    zero_X(l);
-    if (l >= 1) jump(l, pair(x, l - 1), nullptr, 0);
-    if (l <= L - 2) jump(l, pair(x, l), nullptr, 1);
+    sources(l, l >= 1 ? jt(pair(x, l - 1)) : jt(), l <= L - 2 ? jt(pair(x, l)) : jt());
   }
   H.solve_layers(*set_all, k);
   for (int l = 0; l < L; ++l) {

@@ -51,7 +51,18 @@ struct Method {
   // X^l += J_top or J_bot (bottom) of ca a + cb b + cc c (b, c may be null)
   void jump(int l, const double2* a, const double2* b, int bottom, double ca = 1.0,
             double cb = 1.0, const double2* c = nullptr, double cc = 1.0);
+  // X^l = J_top of `top` + J_bot of `bot` (empty terms: none)
+  void sources(int l, const kern::JumpTerms& top, const kern::JumpTerms& bot);
+  static kern::JumpTerms jt(const double2* a = nullptr, double ca = 1.0,
+                            const double2* b = nullptr, double cb = 1.0,
+                            const double2* c = nullptr, double cc = 1.0) {
+    return kern::JumpTerms{{a, b, c}, {ca, cb, cc}};
+  }
   void readout(int l, int bottom, double sx, const kern::ReadTerms& t, double2* out);
+  // the bottom read-out to `ob` and the top one to `ot` in one launch
+  void readout_both(int l, const kern::ReadTerms& tb, double2* ob, const kern::ReadTerms& tt,
+                    double2* ot);
+  void readouts(int l, const kern::ReadOuts& ro);
   // the same terms with only the read-out planes of `mask` written (1: a, 2: b)
   static kern::ReadTerms planes(kern::ReadTerms t, int mask);
   static kern::ReadTerms terms(const double2* a = nullptr, double ca = 0, double cb = 0,
