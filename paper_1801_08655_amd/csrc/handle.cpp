@@ -722,7 +722,10 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
       r.scr = scr_f;
       if (r.nch > 1) scr_f += (long long)r.nch * (r.s + r.b);
       const bool kids = r.inv[0] >= 0 || r.inv[1] >= 0;
-      if (kids) { D->fs_s += r.s; D->fs_b += r.b; }
+      if (kids) {
+        D->fs_s += r.s; D->fs_b += r.b;
+        D->gather_rows += (double)r.s * tiles64(r.s + r.b);
+      }
       pS[a + 1] = pS[a] + (kids ? tiles16(r.s) : 0);
       pF[a + 1] = pF[a] + tiles64(r.s + r.b) * r.nch;
       rF[a + 1] = rF[a] + (r.nch > 1 ? tiles16(r.s + r.b) : 0);
@@ -828,6 +831,18 @@ void Handle::solve_layers(const LayerSet& set, int k) {
 static int mfma_bn(int k) { return k <= 16 ? 16 : (k <= 32 ? 32 : 64); }
 static int width_bn(int k) { return k <= 4 ? 1 : mfma_bn(k); }
 
+// Whether a depth's forward GEMM adds the children's updates while it reads
+// its right-hand side (each row tile of a front again) or a gather launch has
+// added them to X: the launch costs about 5 us, the repeated reads their
+// bytes, so the line lies at 16 MB of them.  Pruned layer solves in us,
+// never / 3 MB / 16 MB / always: complex64 25^3 at 8 columns 165 / 148 / 147 /
+// 147, 60^3 at 16 columns 332 / 322 / 307 / 307, 96^3 at 16 columns 528 / 522 /
+// 503 / 501, at 64 columns 924 / 920 / 910 / 979, 160^3 at 32 columns 1452 /
+// 1457 / 1462 / 1532; complex128 97^3 at 21 columns 1023 / 1024 / 1018 / 1023.
+bool Handle::gathers(const DepthList& D, int k) const {
+  return D.tS > 0 && D.gather_rows * k * (double)elem <= 16e6;
+}
+
 // One depth's forward / backward GEMM launch with column width bn (1: the
 // vector path).
 template <typename T>
@@ -836,7 +851,7 @@ void Handle::launch_fwd(const DepthList& D, const LayerDev* ld, int k, void* scr
   if (bn == 1)
     kern::launch_fwd_gemv<T>(D.fwd, D.vF, D.tVF, ld, k, D.vec_rows, st, t0, t1);
   else
-    kern::launch_fwd_gemm<T>(D.fwd, D.pF, D.tF, ld, k, scr, bn, st, t0, t1);
+    kern::launch_fwd_gemm<T>(D.fwd, D.pF, D.tF, ld, k, scr, bn, gathers(D, k), st, t0, t1);
 }
 template <typename T>
 void Handle::launch_bwd(const DepthList& D, const LayerDev* ld, int k, void* scr, int bn,
@@ -962,7 +977,7 @@ void Handle::run_layers_t(const LayerSet& set, int k, const LayerDev* ld, void* 
     if (D.nL == 0) continue;   // (a pruned set may run a front forward only)
     const int bn = fwd_bn(d);
     hipEvent_t a = nullptr;
-    if (bn != 1 && D.tS > 0) {
+    if (bn != 1 && D.tS > 0 && !gathers(D, k)) {
       a = prof_begin(K_FWD_GATHER);
       kern::launch_fwd_gather<T>(D.fwd, D.pS, D.tS, ld, k, st);
       prof_end(K_FWD_GATHER, a, 0, 3.0 * D.fs_s * kk * e);

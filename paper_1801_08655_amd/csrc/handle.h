@@ -54,7 +54,8 @@ struct DepthList {
   // at most 64, 128 pivots), backward rows per lane group
   int vec_rows = 64, vec_rpg = 8;
   double sum_s = 0, sum_b = 0, sum_sbs = 0, sum_bs = 0;  // work counts, all fronts
-  double fs_s = 0, fs_b = 0, fs_sbs = 0;    // fronts with children
+  double fs_s = 0, fs_b = 0;                // fronts with children
+  double gather_rows = 0;                   // their s times their 64-row tiles
   double fl_s = 0, fl_b = 0, fl_sbs = 0;    // all fronts (forward GEMM)
   long long scratch_rows = 0;
 };
@@ -154,6 +155,7 @@ struct Handle {
   const std::vector<TileChoice>& tile_plan(const LayerSet& set, int k);
   template <typename T> void autotune_t(const LayerSet& set, int k,
                                         std::vector<TileChoice>& plan);
+  bool gathers(const DepthList& D, int k) const;
   template <typename T> void launch_fwd(const DepthList& D, const LayerDev* ld, int k,
                                         void* scr, int bn, hipEvent_t t0 = nullptr,
                                         hipEvent_t t1 = nullptr);

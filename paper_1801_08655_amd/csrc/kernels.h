@@ -81,10 +81,12 @@ void launch_store_factor(const FrontDev* fronts, const int* ids, int n_ids,
 template <typename T>
 void launch_fwd_gather(const SolveFront* list, const int2* tmap, int total,
                        const LayerDev* layers, int k, hipStream_t st);
+// gather: the children's updates of the pivot rows are added as the right-hand
+// side is read (else launch_fwd_gather has added them to X)
 template <typename T>
 void launch_fwd_gemm(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
-                     int k, void* scratch, int bn, hipStream_t st, hipEvent_t t0 = nullptr,
-                     hipEvent_t t1 = nullptr);
+                     int k, void* scratch, int bn, bool gather, hipStream_t st,
+                     hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 template <typename T>
 void launch_fwd_reduce(const SolveFront* list, const int2* tmap, int total,
                        const LayerDev* layers, int k, const void* scratch, hipStream_t st);

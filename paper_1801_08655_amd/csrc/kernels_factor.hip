@@ -1010,8 +1010,8 @@ k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   // Q columns = C rows i: A^T(q, i) = F[i + (k + q) n]
   __shared__ TileSmem<T, 64> sm;
   TileAcc<T, 64, 64> acc;
-  tile_gemm<T, 64, 64, true, false>(sm, acc, TileP<T>{F + k, n, n},
-                                    TileQ<T>{F + (long long)k * n, n, n, nullptr}, j0, i0, 0, nbf);
+  tile_gemm<T, 64, 64, true, kDirect>(sm, acc, TileP<T>{F + k, n, n},
+                                      TileQ<T>{F + (long long)k * n, n, n}, j0, i0, 0, nbf);
   // F(i, j) -= product: every entry of the lane is loaded before the first
   // store (one latency for the group instead of a load-store chain per entry)
   using O = TileOut<T, 64, 64>;

@@ -161,8 +161,8 @@ template <typename T> constexpr int tile_waves(int bn) {
 
 // forward, step 2: [X(S); Ub] = [F11^-1 w_S; Ub - F21 F11^-1 w_S], the K
 // (pivot) dimension optionally split into chunks (partials to scratch).
-template <typename T, int BN>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tile_waves<T>(BN), 8)))
+template <typename T, int BN, bool GATHER>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tile_waves<T>(BN) - (GATHER && sizeof(T) == 4 && BN > 16), 8)))
 k_fwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
            const LayerDev* __restrict__ layers, int k, void* scratch) {
   using C = C_t<T>;
@@ -183,14 +183,21 @@ k_fwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
   const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac;
   const C* X = reinterpret_cast<const C*>(L.X) + (long long)f.off * k;
   TileAcc<T, BM, BN> acc;
-  tile_gemm<T, BM, BN, false, false>(sm, acc, TileP<T>{FT, n, n}, TileQ<T>{X, k, k, nullptr}, m0,
-                                     n0, kb, ke);
+  const ChildSum<T> cs(f, L);
+  TileQ<T> Q{X, k, k};
+  if (GATHER)
+    for (int sl = 0; sl < 2; ++sl) {
+      Q.U[sl] = cs.Uc + cs.cub[sl] * k;
+      Q.inv[sl] = cs.inv[sl];
+    }
+  tile_gemm<T, BM, BN, false, GATHER ? kGather : kDirect>(sm, acc, TileP<T>{FT, n, n}, Q, m0, n0,
+                                                          kb, ke);
   if (f.nch > 1)
     store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * n, m0, n0,
                         n, k);
   else
-    fwd_epilogue<T, O>(acc, f, ChildSum<T>(f, L), reinterpret_cast<C*>(L.Wt),
-                       ub_ptr<T>(L, f.ub_parity), m0, n0, k);
+    fwd_epilogue<T, O>(acc, f, cs, reinterpret_cast<C*>(L.Wt), ub_ptr<T>(L, f.ub_parity), m0,
+                       n0, k);
 }
 
 // elements per thread and pass of the split-K reductions, and chunks whose
@@ -292,7 +299,7 @@ k_bwd_gemm(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
   const C* FT = reinterpret_cast<const C*>(L.fac) + f.fac + f.s;
   C* X = reinterpret_cast<C*>(L.X);
   TileAcc<T, BM, BN> acc;
-  tile_gemm<T, BM, BN, true, true>(sm, acc, TileP<T>{FT, n, f.s},
+  tile_gemm<T, BM, BN, true, kMap>(sm, acc, TileP<T>{FT, n, f.s},
                                    TileQ<T>{X, k, k, L.bidx + f.bidx}, m0, n0, kb, ke);
   if (f.nch > 1) {
     store_partial<T, O>(acc, reinterpret_cast<C*>(scratch), f.scr + (long long)chunk * f.s, m0,
@@ -751,13 +758,16 @@ void launch_fwd_gather(const SolveFront* list, const int2* tmap, int total,
 }
 template <typename T>
 void launch_fwd_gemm(const SolveFront* list, const int2* tmap, int total, const LayerDev* layers,
-                     int k, void* scratch, int bn, hipStream_t st, hipEvent_t t0,
+                     int k, void* scratch, int bn, bool gather, hipStream_t st, hipEvent_t t0,
                      hipEvent_t t1) {
   if (total <= 0) return;
   const int grid = total * ((k + bn - 1) / bn);
-#define HELM_FWD(BN_) \
-  HELM_SOLVE_LAUNCH((k_fwd_gemm<T, BN_>), grid, list, tmap, layers, k, scratch)
-  if (bn == 16) HELM_FWD(16); else if (bn == 32) HELM_FWD(32); else HELM_FWD(64);
+#define HELM_FWD(BN_)                                                                          \
+  if (gather)                                                                                  \
+    HELM_SOLVE_LAUNCH((k_fwd_gemm<T, BN_, true>), grid, list, tmap, layers, k, scratch);       \
+  else                                                                                         \
+    HELM_SOLVE_LAUNCH((k_fwd_gemm<T, BN_, false>), grid, list, tmap, layers, k, scratch)
+  if (bn == 16) { HELM_FWD(16); } else if (bn == 32) { HELM_FWD(32); } else { HELM_FWD(64); }
 #undef HELM_FWD
 }
 template <typename T>
@@ -804,7 +814,7 @@ void launch_bwd_reduce(const SolveFront* list, const int2* tmap, int total,
   template void launch_fwd_gather<T>(const SolveFront*, const int2*, int, const LayerDev*,     \
                                      int, hipStream_t);                                        \
   template void launch_fwd_gemm<T>(const SolveFront*, const int2*, int, const LayerDev*, int,  \
-                                   void*, int, hipStream_t, hipEvent_t, hipEvent_t);           \
+                                   void*, int, bool, hipStream_t, hipEvent_t, hipEvent_t);     \
   template void launch_fwd_reduce<T>(const SolveFront*, const int2*, int, const LayerDev*,     \
                                      int, const void*, hipStream_t);                           \
   template void launch_bwd_gemm<T>(const SolveFront*, const int2*, int, const LayerDev*, int,  \

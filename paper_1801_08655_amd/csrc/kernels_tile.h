@@ -185,7 +185,10 @@ __device__ __forceinline__ C_t<T> acc_at(const TileAcc<T, BM, BN>& acc, int i, i
 // Row operand: element (r, k) at base[r ld + k] when CONTIG (a lane's k are
 // contiguous), else at base[k ld + r]; r < rows.
 // Column operand: element (k, c) at base[row(k) ld + c], c < cols, with
-// row(k) = k, or kmap[k] when MAP.
+// row(k) = k, or kmap[k] when QMODE is kMap; with kGather the children's
+// updates landing on row k are added, U[i][inv[i][k] ldu + c] where inv[i] is
+// given and its entry is not negative.
+enum QMode { kDirect, kMap, kGather };
 template <typename T> struct TileP {
   const C_t<T>* base;
   long long ld;
@@ -196,6 +199,8 @@ template <typename T> struct TileQ {
   long long ld;
   int cols;
   const int* kmap;
+  const C_t<T>* U[2];
+  const int* inv[2];
 };
 
 // One K step of MFMAs of a wave on the lane's row values p (lane l: row
@@ -252,7 +257,7 @@ __device__ __forceinline__ void tile_mfma(const TileSmem<double, BN>& sm, int bu
 // load the compiler merges their registers by copies right after the loads,
 // each waiting for its load, and nothing is ahead any more (a pruned layer
 // solve of 160^3, 32 columns: 1528 us with the branch, 1467 without).
-template <typename T, int BM, int BN, bool CONTIG, bool MAP>
+template <typename T, int BM, int BN, bool CONTIG, QMode QM>
 __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN>& acc,
                                           const TileP<T>& P, const TileQ<T>& Q, int r0, int c0,
                                           int kbeg, int kend) {
@@ -281,12 +286,32 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
   const unsigned qoff = (unsigned)qk * qld + (unsigned)qc * E;
   const SplitSel sel;
 
-  C p[KP], q[KPT];
-  int ki[KPT];
-  auto load_index = [&](int k0) {   // rows of the column operand (MAP), clamped
+  constexpr bool MAP = QM == kMap, GAT = QM == kGather;
+  C p[KP], q[KPT], u0[GAT ? KPT : 1], u1[GAT ? KPT : 1];
+  int ki[KPT], kj[GAT ? KPT : 1];
+  // rows of the column operand (kMap) or of the children's updates (kGather),
+  // loaded one step before the values they address
+  auto load_index = [&](int k0) {
     if constexpr (MAP) {
 #pragma unroll
       for (int i = 0; i < KPT; ++i) ki[i] = ld(Q.kmap + min(k0 + qk + i, kend - 1));
+    }
+    if constexpr (GAT) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        const int kk = min(k0 + qk + i, kend - 1);
+        ki[i] = Q.inv[0] ? ld(Q.inv[0] + kk) : -1;
+        kj[i] = Q.inv[1] ? ld(Q.inv[1] + kk) : -1;
+      }
+    }
+  };
+  auto load_updates = [&] {
+    if constexpr (GAT) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        u0[i] = ld_or_zero(ki[i] >= 0, Q.U[0] + (long long)ki[i] * Q.ld + c0 + qc);
+        u1[i] = ld_or_zero(kj[i] >= 0, Q.U[1] + (long long)kj[i] * Q.ld + c0 + qc);
+      }
     }
   };
   auto load_mapped = [&] {
@@ -309,6 +334,7 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
 #pragma unroll
       for (int i = 0; i < KPT; ++i) q[i] = ld_at<C>(c + (long long)i * Q.ld * E, qoff);
     }
+    load_updates();
   };
   auto load_part = [&](int k0) {    // k0 < kend: clamped to the last k
 #pragma unroll
@@ -323,10 +349,20 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
       for (int i = 0; i < KPT; ++i)
         q[i] = ld(reinterpret_cast<const C*>(qb) + (long long)min(k0 + qk + i, kend - 1) * Q.ld + qc);
     }
+    load_updates();
   };
   // the loaded columns to LDS and the rows to the operand form; then the next
   // loads (ahead), the barrier and the MFMAs
-  auto step = [&](int buf, auto&& ahead) {
+  auto step = [&](int buf, int kleft, auto&& ahead) {
+    if constexpr (GAT) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) q[i] = cadd(q[i], cadd(u0[i], u1[i]));
+    }
+    if (kleft < K) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i)
+        if (qk + i >= kleft) q[i] = czero<C>();
+    }
     if constexpr (sizeof(T) == 4) {
       float x[KPT], y[KPT];
 #pragma unroll
@@ -373,19 +409,15 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
   load_index(kbeg + K);
   int k0 = kbeg, buf = 0;
   for (; k0 + 2 * K <= kend; k0 += K, buf ^= 1)
-    step(buf, [&] {
+    step(buf, K, [&] {
       load_whole(k0 + K);
       load_index(k0 + 2 * K);
     });
   // the last whole step and a partial one
-  for (; k0 < kend; k0 += K, buf ^= 1) {
-#pragma unroll
-    for (int i = 0; i < KPT; ++i)
-      if (k0 + qk + i >= kend) q[i] = czero<C>();
-    step(buf, [&] {
+  for (; k0 < kend; k0 += K, buf ^= 1)
+    step(buf, kend - k0, [&] {
       if (k0 + K < kend) load_part(k0 + K);
     });
-  }
   acc.finish();
 }
 
