@@ -324,9 +324,10 @@ int helm_set_solve_options(helm_handle* h, const helm_options* opt);
  *   lu_flops     -- algorithmic real flops: an LU of every front,
  *                   sum 4 (2/3 s^3 + 2 s^2 b + 2 s b^2) over fronts with s
  *                   pivots and b boundary variables;
- *   gj_flops     -- real flops the blocked Gauss-Jordan sweep executes (it
- *                   also forms F11^-1, so that the substitutions are plain
- *                   products);
+ *   gj_flops     -- real flops of the blocked Gauss-Jordan sweep on whole
+ *                   fronts (it also forms F11^-1, so that the substitutions
+ *                   are plain products; of the symmetric boundary block,
+ *                   counted in full, only the lower tiles are computed);
  *   pivot_min / pivot_max -- smallest and largest |pivot| chosen by the
  *                   partial pivoting within the fully summed rows of each
  *                   front;

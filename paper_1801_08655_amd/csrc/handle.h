@@ -184,7 +184,7 @@ struct Handle {
   // set-up, single-layer launch lists)
   double symbolic_seconds = 0, setup_seconds = 0, lists_seconds = 0;
   double factor_flops = 0;        // LU count of every front (algorithmic)
-  double factor_gj_flops = 0;     // flops the Gauss-Jordan sweep executes
+  double factor_gj_flops = 0;     // the Gauss-Jordan sweep on whole fronts
   // pivot statistics of the last factorization (device: status flag, then
   // the bit patterns of min and max |pivot|^2 and of max |diagonal entry|^2
   // of the assembled operator)

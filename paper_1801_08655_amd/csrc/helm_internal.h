@@ -155,18 +155,19 @@ struct LayerPlan {
   double factor_flops = 0;           // real flops of an LU of every front:
                                      // 4 (2/3 s^3 + 2 s^2 b + 2 s b^2)
   double gj_flops = 0;               // real flops the blocked Gauss-Jordan
-                                     // sweep executes (skipped tiles excluded)
+                                     // sweep (gj_front_flops)
   double solve_elems = 0;            // factor elements read by one solve
 };
 
 // Pivot block of the factorization's Gauss-Jordan sweep (columns per step).
 constexpr int kPivotBlock = 64;
 
-// Real flops the sweep of one front (s pivots, b boundary variables)
-// executes: per block step of nbf pivots, the rank-nbf update of every
-// 64 x 64 tile it does not skip (tiles inside the pivot rows or columns, and
-// tiles of eliminated rows x boundary columns, whose values are never read
-// again), plus the two products with the inverted pivot block.
+// Real flops of the sweep of one whole front (s pivots, b boundary variables):
+// per block step of nbf pivots, the rank-nbf update of every 64 x 64 tile
+// except those inside the pivot rows or columns and those of eliminated rows
+// x boundary columns, whose values are never read again, plus the two products
+// with the inverted pivot block.  (The symmetric boundary block counts in
+// full; its tiles above the diagonal are not executed.)
 double gj_front_flops(int s, int b, int nb);
 
 struct Geometry {

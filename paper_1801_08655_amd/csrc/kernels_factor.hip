@@ -28,9 +28,22 @@ __device__ __forceinline__ C_t<T>* front_ptr(void* ws0, void* ws1, const FrontDe
   return base + f.ws;
 }
 
+// The Schur complement of a complex-symmetric front is symmetric whatever
+// rows the pivoting of F11 exchanged, so of the boundary x boundary block only
+// the 64 x 64 tiles on and below the diagonal are assembled and updated: a
+// tile of rows i0.. and columns j0.. is left out when this holds, and whoever
+// reads the block takes the lower of the two mirror entries.  28% of the
+// sweep's tiles at 100^3: complex64 sweep 80 -> 58 ms, complex128 175 -> 127.
+__device__ __forceinline__ bool mirrored(const FrontDev& f, int i0, int j0) {
+  return i0 >= f.s && j0 >= i0 + GT;
+}
+
 // --------------------------------------------------------------------------
 // front assembly: frontal matrix = extend-add of the children's Schur
 // complements (pull form: every entry is written once) ...
+// The front-row -> child-boundary maps increase, so a tile above the diagonal
+// reads the children's mirror entries: its columns' lanes walk their
+// contiguous rows, and the tile is turned in LDS.
 // --------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -45,7 +58,9 @@ k_extend_add(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const int nt = (n + GT - 1) / GT;
   const int tile = tm.y;
   const int i0 = (tile % nt) * GT, j0 = (tile / nt) * GT;
+  if (mirrored(f, i0, j0)) return;   // uniform per block
   __shared__ int inv_r[2][GT], inv_c[2][GT];
+  __shared__ C turn[GT][GT + 1];
   const LayerDev& L = layers[f.layer];
   const int t = threadIdx.x;
   if (t < 2 * GT) {
@@ -70,24 +85,37 @@ k_extend_add(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
       sc[slot] = c.s;
     }
   }
-  // the lane's 16 entries are all gathered before the first store
+  // the lane's 16 entries are all gathered before the first store; lanes
+  // walk the tile's rows, above the diagonal its columns
+  const bool upper = j0 > i0;
   constexpr int NJ = GT / (256 / GT);
-  const int i = t % GT, gi = i0 + i;
+  const int p = t % GT;
   C v[NJ];
 #pragma unroll
   for (int u = 0; u < NJ; ++u) {
-    const int jj = t / GT + u * (256 / GT), gj = j0 + jj;
+    const int q = t / GT + u * (256 / GT);
+    const int ii = upper ? q : p, jj = upper ? p : q;
+    const int gi = i0 + ii, gj = j0 + jj;
     C acc = czero<C>();
 #pragma unroll
     for (int slot = 0; slot < 2; ++slot) {
-      const int ri = inv_r[slot][i], cj = inv_c[slot][jj];
+      const int ri = inv_r[slot][ii], cj = inv_c[slot][jj];
       const bool hit = gi < n && gj < n && S[slot] && ri >= 0 && cj >= 0;
-      acc = cadd(acc, ld_or_zero(hit, S[slot] + (hit ? (long long)(sc[slot] + ri) +
-                                                         (long long)(sc[slot] + cj) * ldc[slot]
+      const int lo = min(ri, cj), hi = max(ri, cj);
+      acc = cadd(acc, ld_or_zero(hit, S[slot] + (hit ? (long long)(sc[slot] + hi) +
+                                                         (long long)(sc[slot] + lo) * ldc[slot]
                                                      : 0)));
     }
     v[u] = acc;
   }
+  if (upper) {   // uniform per block
+#pragma unroll
+    for (int u = 0; u < NJ; ++u) turn[t / GT + u * (256 / GT)][p] = v[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NJ; ++u) v[u] = turn[p][t / GT + u * (256 / GT)];
+  }
+  const int gi = i0 + p;
 #pragma unroll
   for (int u = 0; u < NJ; ++u) {
     const int gj = j0 + t / GT + u * (256 / GT);
@@ -980,7 +1008,8 @@ k_swap_JO(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // would accumulate F11^-1 F12, which neither the factor store (the
 // symmetric operator's backward step uses the transpose of -F21 F11^-1) nor
 // the parent's extend-add (the Schur block) ever reads.  Tiles that lie
-// wholly in J or in that block return at once.
+// wholly in J or in that block, and the mirrored ones of the Schur block,
+// return at once.
 // Bound: the trailing entries streamed from and to HBM once per pivot block
 // (complex64 at 200^3: 5.7 TB; 3.5 TB/s) and the latency of a two-step
 // product between them.  complex64 runs on the split bf16 tile: 1916 -> 1604
@@ -1004,7 +1033,8 @@ k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const int i0 = (tile % nt) * GT;   // rows of F
   const int j0 = (tile / nt) * GT;   // columns of F
   const bool rowsJ = i0 >= k && i0 + GT <= k + nbf, colsJ = j0 >= k && j0 + GT <= k + nbf;
-  if (rowsJ || colsJ || (i0 + GT <= k && j0 >= f.s)) return;   // uniform per block
+  if (rowsJ || colsJ || (i0 + GT <= k && j0 >= f.s) || mirrored(f, i0, j0))
+    return;   // uniform per block
   C* F = front_ptr<T>(ws0, ws1, f);
   // P rows = C columns j: B^T(j, q) = F[(k + q) + j n]
   // Q columns = C rows i: A^T(q, i) = F[i + (k + q) n]
