@@ -106,6 +106,18 @@ template <> __device__ __forceinline__ float2 from_d2<float2>(double2 a) {
 }
 template <> __device__ __forceinline__ double2 from_d2<double2>(double2 a) { return a; }
 
+// v of one lane (the same lane for the whole wave)
+template <typename T> __device__ __forceinline__ T lane_read(T v, int lane);
+template <> __device__ __forceinline__ float lane_read<float>(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+template <> __device__ __forceinline__ double lane_read<double>(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // Launches over variable-size items (fronts, their tiles and chunks) index
 // their blocks through a tile map built on the host: entry t holds the item
 // of block t and the block's index within that item, so a block finds its

@@ -225,69 +225,121 @@ k_orig_entries(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // --------------------------------------------------------------------------
 constexpr int NBMAX = 64;
 constexpr int PB = 8;   // column block of the panel LU
-template <typename T> constexpr int panel_lds_rows() { return sizeof(T) == 4 ? 192 : 64; }
+
+// The largest v of a wave and the smallest index among the lanes that hold it
+// (both uniform; v must not be NaN in the winning lane): the maximum through
+// DPP moves, ties by a ballot.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_max(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
+  const int l2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+  const int h2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+  return fmax(v, __longlong_as_double(((long long)h2 << 32) | (unsigned)l2));
+}
+__device__ __forceinline__ void wave_argmax(double& v, int& idx) {
+  double m = dpp_max<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8: lane 15 of each row
+  m = dpp_max<0x112, 0xf>(m);
+  m = dpp_max<0x114, 0xf>(m);
+  m = dpp_max<0x118, 0xf>(m);
+  m = dpp_max<0x142, 0xa>(m);          // row_bcast 15, 31: lane 63
+  m = dpp_max<0x143, 0xc>(m);
+  const long long b = __double_as_longlong(m);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), 63);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+  m = __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+  unsigned long long who = __ballot(v == m);
+  int best = 0x7fffffff;
+  while (who) {   // one lane but for ties
+    const int l = __ffsll((long long)who) - 1;
+    best = min(best, __builtin_amdgcn_readlane(idx, l));
+    who &= who - 1;
+  }
+  v = m;
+  idx = best;
+}
 
 // D = U^-1 L^-1 of the leading nbf x nbf block of the factored panel P
-// (R rows, column-major, in LDS when LDSP), in LDS: X = L^-1 by eliminating
-// below each unit pivot, then D = U^-1 X from the last row up.  Every step
-// updates all entries it touches in parallel.
+// (R rows, column-major, in LDS when LDSP): X = L^-1 by eliminating below each
+// unit pivot, then D = U^-1 X from the last row up.  Wave w of the first four
+// holds rows 16 w .. 16 w + 15 in registers, lane = column; each step passes
+// one row of X through LDS (one barrier) and updates the rows it touches.
+// With X in LDS and its entries dealt to the threads one by one (an integer
+// division each), this was half of a tall panel's time.
 template <typename T, int NT, bool LDSP>
 __device__ __forceinline__ void panel_inverse(const C_t<T>* P, int R, int nbf, int nb,
                                               C_t<T>* D) {
   using C = C_t<T>;
-  const int t = threadIdx.x;
-  // (the factors are read in place when the panel is in LDS)
-  __shared__ C LUs[LDSP ? 1 : NBMAX][LDSP ? 1 : NBMAX + 1];
-  __shared__ C X[NBMAX][NBMAX + 1];
-  __shared__ C uinv[NBMAX];
-  auto LU = [&](int r, int c) -> C { return LDSP ? P[r + c * R] : LUs[r][c]; };
-  if (!LDSP) {
-    // the factors from the global panel, every load before the first store
+  static_assert(NT >= 256, "four waves hold the rows");
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  __shared__ C LU[NBMAX][NBMAX + 2];   // LU[c][r]: a column's rows are contiguous
+  __shared__ C row[2][NBMAX];
+  {
+    // the factors, every load before the first store
     constexpr int PER = (NBMAX * NBMAX + NT - 1) / NT;
-    C w[PER];
+    C v[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = t + NT * i, r = e % NBMAX, c = e / NBMAX;
       const bool ok = r < nbf && c < nbf;
-      w[i] = ld_or_zero(ok, P + (ok ? r + (long long)c * R : 0));
+      if (LDSP) v[i] = ok ? P[r + c * R] : czero<C>();
+      else v[i] = ld_or_zero(ok, P + (ok ? r + (long long)c * R : 0));
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = t + NT * i, r = e % NBMAX, c = e / NBMAX;
-      if (r < nbf && c < nbf) LUs[r][c] = w[i];
+      if (NT * PER == NBMAX * NBMAX || e < NBMAX * NBMAX) LU[c][r] = v[i];
     }
   }
-  for (int e = t; e < nbf * nbf; e += NT) {
-    int r = e % nbf, c = e / nbf;
-    X[r][c] = cmake<C>(r == c ? 1.0 : 0.0, 0.0);
-  }
+  const bool mine = w < 4;
+  const int r0 = 16 * w;
+  C x[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = cmake<C>(r0 + i == lane ? 1.0 : 0.0, 0.0);
   __syncthreads();
-  if (t < nbf) {
-    C u = LU(t, t);
-    if (cabs2(u) == 0.0) u = cmake<C>(1.0, 0.0);
-    uinv[t] = cdiv(cmake<C>(1.0, 0.0), u);
+  // X[i][:] -= L[i][q] X[q][:] for i > q
+  for (int qg = 0; 16 * qg < nbf; ++qg) {
+#pragma unroll
+    for (int qi = 0; qi < 16; ++qi) {
+      const int q = 16 * qg + qi;
+      if (q + 1 >= nbf) break;
+      if (w == qg) row[qi & 1][lane] = x[qi];
+      __syncthreads();
+      if (mine && w >= qg) {
+        const C xq = row[qi & 1][lane];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (w > qg || i > qi) cfms(x[i], LU[q][r0 + i], xq);
+      }
+    }
   }
+  // rows from the last one up: D[q] = X[q] / U[q][q], X[i] -= U[i][q] D[q]
   __syncthreads();
-  // X[i][j] -= L[i][q] X[q][j] for i > q, j <= q
-  for (int q = 0; q + 1 < nbf; ++q) {
-    const int rows = nbf - 1 - q, cols = q + 1;
-    for (int e = t; e < rows * cols; e += NT) {
-      const int i = q + 1 + e % rows, j = e / rows;
-      cfms(X[i][j], LU(i, q), X[q][j]);
+  for (int qg = (nbf - 1) / 16; qg >= 0; --qg) {
+#pragma unroll
+    for (int qi = 15; qi >= 0; --qi) {
+      const int q = 16 * qg + qi;
+      if (q >= nbf) continue;
+      if (w == qg) {
+        C u = LU[q][q];
+        if (cabs2(u) == 0.0) u = cmake<C>(1.0, 0.0);
+        x[qi] = cmul(x[qi], cdiv(cmake<C>(1.0, 0.0), u));
+        row[qi & 1][lane] = x[qi];
+      }
+      __syncthreads();
+      if (mine && w <= qg) {
+        const C xq = row[qi & 1][lane];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (w < qg || i < qi) cfms(x[i], LU[q][r0 + i], xq);
+      }
     }
-    __syncthreads();
   }
-  // X[i][j] -= U[i][q] / U[q][q] X[q][j] for i < q; rows scaled at the end
-  for (int q = nbf - 1; q > 0; --q) {
-    for (int e = t; e < q * nbf; e += NT) {
-      const int i = e % q, j = e / q;
-      cfms(X[i][j], cmul(LU(i, q), uinv[q]), X[q][j]);
-    }
-    __syncthreads();
-  }
-  for (int e = t; e < nbf * nbf; e += NT) {
-    int r = e % nbf, c = e / nbf;
-    st(D + r + c * nb, cmul(X[r][c], uinv[r]));
+  if (mine && lane < nbf) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (r0 + i < nbf) st(D + (r0 + i) + (long long)lane * nb, x[i]);
   }
 }
 
@@ -343,11 +395,7 @@ k_panel(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
         double v = cabs2(P[r + (long long)c * R]);
         if (v > best) { best = v; bi = r; }
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        double ov = __shfl_down(best, off);
-        int oi = __shfl_down(bi, off);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-      }
+      wave_argmax(best, bi);
       if (NW > 1) {
         if ((t & 63) == 0) { red_v[t >> 6] = best; red_i[t >> 6] = bi; }
         __syncthreads();
@@ -437,111 +485,120 @@ k_panel(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   panel_inverse<T, NT, LDSP>(P, R, nbf, nb, D);
 }
 
-// Panels of at most 64 NW rows, complex64: NW waves per front, thread r
-// holding row r of the panel in registers.  Gauss-Jordan elimination with
-// partial pivoting turns the panel into the inverse of its pivoted diagonal
-// block in place: at column c the chosen row is scaled by the pivot's
-// inverse and removed from every other row, and column c's slot, no longer
-// needed, takes column c of the inverse (the eliminated unit column carried
-// along).  Rows never leave their threads; each thread tracks the index its
-// row would have if rows were exchanged as in the LU, which gives the pivot
-// choice of the LU with partial pivoting (largest |entry| among the rows not
-// yet chosen, ties to the smallest index), the same exchange record ipiv and
-// the same permutation.  One wave broadcasts the pivot row with lane reads;
-// several exchange the wave maxima and the pivot row through LDS (two
-// barriers per column).
-template <typename T, int NW>
-__global__ void __launch_bounds__(64 * NW)
+// Panels of at most 64 RW rows: the panel in registers, a row per lane (its
+// 64 columns in CH parts over as many waves, so that complex128 fits).
+// Gauss-Jordan elimination with partial pivoting turns the panel into the
+// inverse of its pivoted diagonal block in place: at column c the chosen row
+// is scaled by the pivot's inverse and removed from every other row, and
+// column c's slot, no longer needed, takes column c of the inverse (the
+// eliminated unit column carried along).  The slots of the part that holds
+// column c move down by one in the same step, so that the current column is
+// always slot 0 and no register is chosen at run time.  Rows never leave their
+// lanes; each tracks the index its row would have if rows were exchanged as in
+// the LU, which gives the pivot choice of the LU with partial pivoting
+// (largest |entry| among the rows not yet chosen, ties to the smallest index),
+// the same exchange record ipiv and the same permutation.  With one wave of
+// rows the pivot row comes by lane reads, with several through LDS (two
+// barriers per column; one, or none, otherwise).  Bound: the chain of column
+// steps (5 us each at 512 rows).  Panels of a 100^3 factorization 65 -> 43 ms
+// in complex64 (512 rows 577 -> 318 us a launch; 768 rows were the taller
+// kernel's 690) and 93 -> 65 ms in complex128 (whose 64-row panels took an LDS
+// copy of 130 KB, one block per compute unit); 200^3 complex64 448 -> 350 ms.
+template <typename T, int RW, int CH>
+__global__ void __launch_bounds__(64 * RW * CH)
 k_panel_regs(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
              int k, int nb, void* ws0, void* ws1, void* D_base, int* ipiv_base,
              int* perm_base, const long long* __restrict__ perm_off,
              const long long* __restrict__ panel_off, FactorStatus* status) {
   using C = C_t<T>;
+  constexpr int NC = NBMAX / CH;
   const int a = blockIdx.x;
   const FrontDev f = fronts[ids[a]];
   const int n = f.s + f.b;
   const int R = f.s - k;
   if (R <= 0) return;
   const int nbf = R < nb ? R : nb;
-  const int t = threadIdx.x, lane = t & 63;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int part = wave / RW, rw = wave % RW;
+  const int t = rw * 64 + lane;   // this thread's panel row
   const bool row = t < R;
   const C* F = front_ptr<T>(ws0, ws1, f);
   C* D = reinterpret_cast<C*>(D_base) + panel_off[a];
   int* ipiv = ipiv_base + perm_off[a];
   int* perm = perm_base + perm_off[a];
-  __shared__ double red_v[NW];
-  __shared__ int red_i[NW];
-  __shared__ C prow[NW > 1 ? NBMAX : 1];
-  C x[NBMAX];
+  __shared__ double red_v[2][RW];
+  __shared__ int red_i[2][RW];
+  __shared__ C gcol[2][CH > 1 ? 64 * RW : 1];          // column c of every row
+  __shared__ C prow[RW > 1 ? CH : 1][RW > 1 ? NC : 1];  // the pivot row
+  __shared__ C piv_s;
+  C x[NC];
 #pragma unroll
-  for (int j = 0; j < NBMAX; ++j)
-    x[j] = ld_or_zero(row && j < nbf,
-                      F + (long long)(k + (row ? t : 0)) + (long long)(k + (j < nbf ? j : 0)) * n);
+  for (int j = 0; j < NC; ++j) {
+    const int c = part * NC + j;
+    const bool ok = row && c < nbf;
+    x[j] = ld_or_zero(ok, F + (ok ? (long long)(k + t) + (long long)(k + c) * n : 0));
+  }
   // the permutation entry of this thread's row, read before any is written
   const int pold = k == 0 ? t : (row ? ld(perm + k + t) : 0);
+  if (RW * CH > 1) __syncthreads();
   int pos = t;           // the row's index were rows exchanged as in the LU
   bool chosen = false;   // the row is the pivot row of an earlier column
   double pv_min = INFINITY, pv_max = 0.0;
   for (int c = 0; c < nbf; ++c) {
-    C xc = x[0];
-#pragma unroll
-    for (int j = 1; j < NBMAX; ++j)
-      if (j == c) xc = x[j];
-    // arg max over the rows not yet chosen, the key (|x|^2, smallest
-    // index): within the wave, then over the waves' maxima
+    const bool owner = CH == 1 || c / NC == part;
+    const int buf = c & 1;
     const bool cand = row && !chosen;
-    double v = cand ? cabs2(xc) : -1.0;
-    int bi = cand ? pos : R;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const double ov = __shfl_xor(v, off, 64);
-      const int oi = __shfl_xor(bi, off, 64);
-      if (ov > v || (ov == v && oi < bi)) { v = ov; bi = oi; }
+    C g = x[0];
+    double bv = -1.0;
+    int P = R;
+    if (owner) {
+      bv = cand ? cabs2(g) : -1.0;
+      P = cand ? pos : R;
+      wave_argmax(bv, P);
+      if (RW * CH > 1 && lane == 0) {
+        red_v[buf][rw] = bv;
+        red_i[buf][rw] = P;
+      }
+      if (CH > 1) gcol[buf][t] = g;
     }
-    double bv;
-    int P;
-    if (NW == 1) {
-      bv = __shfl(v, 0, 64);
-      P = __builtin_amdgcn_readfirstlane(bi);
-    } else {
-      if (lane == 0) { red_v[t >> 6] = v; red_i[t >> 6] = bi; }
+    if (RW * CH > 1) {
       __syncthreads();
-      bv = red_v[0];
-      P = red_i[0];
+      bv = red_v[buf][0];
+      P = red_i[buf][0];
 #pragma unroll
-      for (int w = 1; w < NW; ++w)
-        if (red_v[w] > bv || (red_v[w] == bv && red_i[w] < P)) {
-          bv = red_v[w];
-          P = red_i[w];
+      for (int w = 1; w < RW; ++w)
+        if (red_v[buf][w] > bv || (red_v[buf][w] == bv && red_i[buf][w] < P)) {
+          bv = red_v[buf][w];
+          P = red_i[buf][w];
         }
+      if (CH > 1) g = gcol[buf][t];
     }
     // a zero or non-finite maximum: flagged, the row at index c taken
     const bool bad = !(bv > 0.0) || !isfinite(bv);
     if (bad) {
       P = c;
-      if (t == 0) atomicExch(&status->flag, 1);
+      if (threadIdx.x == 0) atomicExch(&status->flag, 1);
     } else {
       pv_min = fmin(pv_min, bv);
       pv_max = fmax(pv_max, bv);
     }
-    if (t == 0) ipiv[c] = P;
+    if (threadIdx.x == 0) ipiv[c] = P;
     const bool win = cand && pos == P;
-    C w_c;   // the pivot row's entries come from its lane (one wave) or LDS
+    C piv;
     int pl = 0;
-    if (NW == 1) {
+    if (RW == 1) {
       pl = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(win)) - 1);
-      w_c.x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xc.x), pl));
-      w_c.y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xc.y), pl));
+      piv.x = lane_read(g.x, pl);
+      piv.y = lane_read(g.y, pl);
     } else {
-      if (win)
+      if (win) {
 #pragma unroll
-        for (int j = 0; j < NBMAX; ++j)
-          if (j < nbf) prow[j] = x[j];
+        for (int j = 0; j < NC; ++j) prow[part][j] = x[j];
+        if (owner) piv_s = g;
+      }
       __syncthreads();
-      w_c = xc;
-#pragma unroll
-      for (int j = 0; j < NBMAX; ++j)
-        if (j == c) w_c = prow[j];
+      piv = piv_s;
     }
     // exchange of indices c and P: the row at c moves to P, the pivot row to c
     if (pos == c) pos = P;
@@ -549,39 +606,44 @@ k_panel_regs(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
       pos = c;
       chosen = true;
     }
-    C piv = w_c;
     if (cabs2(piv) == 0.0) piv = cmake<C>(1.0, 0.0);
     const C ipv = cdiv(cmake<C>(1.0, 0.0), piv);
-    // pivot row w (column c read as 1) scaled by ipv; every other row loses
-    // g w' with g its column-c entry (that slot read as 0)
-    const C g = win ? czero<C>() : xc;
-#pragma unroll
-    for (int j = 0; j < NBMAX; ++j) {
-      if (j < nbf) {
-        C w;
-        if (NW == 1) {
-          w.x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[j].x), pl));
-          w.y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[j].y), pl));
-        } else {
-          w = prow[j];
-        }
-        if (j == c) w = cmake<C>(1.0, 0.0);
-        const C ws = cmul(w, ipv);
-        C y = win ? ws : (j == c ? czero<C>() : x[j]);
-        cfms(y, g, ws);
-        x[j] = y;
+    // row -= gw w with w the pivot row: gw = g / piv, and for the pivot row
+    // itself (read as zero) -1 / piv; column c of the inverse is -gw
+    const C gw = win ? cneg(ipv) : cmul(g, ipv);
+    auto reduced = [&](int j) {
+      C w;
+      if (RW == 1) {
+        w.x = lane_read(x[j].x, pl);
+        w.y = lane_read(x[j].y, pl);
+      } else {
+        w = prow[part][j];
       }
+      C y = win ? czero<C>() : x[j];
+      cfms(y, gw, w);
+      return y;
+    };
+    if (owner) {
+#pragma unroll
+      for (int j = 1; j < NC; ++j) x[j - 1] = reduced(j);
+      x[NC - 1] = cneg(gw);
+    } else {
+#pragma unroll
+      for (int j = 0; j < NC; ++j) x[j] = reduced(j);
     }
   }
-  if (t == 0 && pv_max > 0.0) {
+  if (threadIdx.x == 0 && pv_max > 0.0) {
     atomicMin(&status->pmin, (unsigned long long)__double_as_longlong(pv_min));
     atomicMax(&status->pmax, (unsigned long long)__double_as_longlong(pv_max));
   }
-  if (row) perm[k + pos] = pold;
+  if (row && part == 0) perm[k + pos] = pold;
   if (row && pos < nbf) {
+    const int turned = min(max(nbf - part * NC, 0), NC);   // steps its slots moved
 #pragma unroll
-    for (int j = 0; j < NBMAX; ++j)
-      if (j < nbf) st(D + pos + (long long)j * nb, x[j]);
+    for (int j = 0; j < NC; ++j) {
+      const int c = part * NC + (j + turned) % NC;
+      if (c < nbf) st(D + pos + (long long)c * nb, x[j]);
+    }
   }
 }
 
@@ -678,11 +740,7 @@ k_panel_rb(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
           if (v > best) { best = v; bi = r; }
         }
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        double ov = __shfl_down(best, off);
-        int oi = __shfl_down(bi, off);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-      }
+      wave_argmax(best, bi);
       if ((t & 63) == 0) { red_v[t >> 6] = best; red_i[t >> 6] = bi; }
       __syncthreads();
       double bv = red_v[0];
@@ -1206,34 +1264,38 @@ void launch_panel(const FrontDev* fronts, const int* ids, int n_active, int max_
   hipLaunchKernelGGL((k_panel_rb<T, NT, RPT, BW>), dim3(n_active), dim3(NT), 0, st, \
                      fronts, ids, k, nb, ws0, ws1, panel, panel_off, D, ipiv, perm, \
                      perm_off, status)
-  // complex64 up to 512 rows: a row per thread, the panel in registers;
-  // taller than the LDS holds: the column block in registers, 4 rows per
-  // thread at most (complex128 at 512 threads: at 1024 a lane's register
-  // share of 128 would spill), else the global copy alone
+  // up to 768 rows (complex128: 256) the panel in registers; above, the column
+  // block in registers, 4 rows per thread at most (complex128 at 512 threads:
+  // at 1024 a lane's register share of 128 would spill), else the global copy
+  // alone
   constexpr bool C64 = sizeof(T) == 4;
-#define HELM_PANEL_REGS(NW)                                                         \
-  hipLaunchKernelGGL((k_panel_regs<T, NW>), dim3(n_active), dim3(64 * NW), 0, st,  \
-                     fronts, ids, k, nb, ws0, ws1, D, ipiv, perm, perm_off, panel_off, status)
+#define HELM_PANEL_REGS(RW, CH)                                                        \
+  hipLaunchKernelGGL((k_panel_regs<T, RW, CH>), dim3(n_active), dim3(64 * RW * CH), 0, \
+                     st, fronts, ids, k, nb, ws0, ws1, D, ipiv, perm, perm_off,        \
+                     panel_off, status)
   if constexpr (C64) {
-    if (max_rows <= 512) {
-      if (max_rows <= 64) HELM_PANEL_REGS(1);
-      else if (max_rows <= 128) HELM_PANEL_REGS(2);
-      else if (max_rows <= 192) HELM_PANEL_REGS(3);
-      else if (max_rows <= 256) HELM_PANEL_REGS(4);
-      else HELM_PANEL_REGS(8);
-      return;
-    }
-  }
-  if (max_rows <= 64) HELM_PANEL(64, 64);
-  else if (max_rows <= panel_lds_rows<T>()) HELM_PANEL(256, panel_lds_rows<T>());
-  else if (max_rows <= 1024) HELM_PANEL_RB(256, 4, PB);
-  else if constexpr (C64) {
-    if (max_rows <= 2048) HELM_PANEL_RB(1024, 2, PB);
+    // (few small fronts: four waves share a panel's columns, 25^3 2.7 -> 2.4 ms;
+    // thousands: a wave each, without a barrier, 100^3 51 -> 47 ms)
+    if (max_rows <= 64 && n_active < 256) HELM_PANEL_REGS(1, 4);
+    else if (max_rows <= 64) HELM_PANEL_REGS(1, 1);
+    else if (max_rows <= 128) HELM_PANEL_REGS(2, 1);
+    else if (max_rows <= 192) HELM_PANEL_REGS(3, 1);
+    else if (max_rows <= 256) HELM_PANEL_REGS(4, 1);
+    else if (max_rows <= 384) HELM_PANEL_REGS(6, 1);
+    else if (max_rows <= 512) HELM_PANEL_REGS(8, 1);
+    else if (max_rows <= 768) HELM_PANEL_REGS(12, 1);
+    else if (max_rows <= 1024) HELM_PANEL_RB(256, 4, PB);
+    else if (max_rows <= 2048) HELM_PANEL_RB(1024, 2, PB);
     else if (max_rows <= 4096) HELM_PANEL_RB(1024, 4, PB);
     else if (max_rows <= 6144) HELM_PANEL_RB(1024, 6, PB / 2);
     else HELM_PANEL(1024, 0);
   } else {
-    if (max_rows <= 2048) HELM_PANEL_RB(512, 4, PB);
+    if (max_rows <= 64) HELM_PANEL_REGS(1, 4);
+    else if (max_rows <= 128) HELM_PANEL_REGS(2, 4);
+    else if (max_rows <= 192) HELM_PANEL_REGS(3, 4);
+    else if (max_rows <= 256) HELM_PANEL_REGS(4, 4);
+    else if (max_rows <= 1024) HELM_PANEL_RB(256, 4, PB);
+    else if (max_rows <= 2048) HELM_PANEL_RB(512, 4, PB);
     else HELM_PANEL(1024, 0);
   }
 #undef HELM_PANEL_REGS

@@ -497,17 +497,6 @@ k_fwd_gemv(const SolveFront* __restrict__ list, const int2* __restrict__ tmap,
 // holds the gathered right-hand side of pivots q, q + 64, ..., broadcast by
 // lane reads, so nothing waits at a barrier: the gather's two dependent loads
 // overlap the first U factor columns.
-template <typename T> __device__ __forceinline__ T lane_read(T v, int lane);
-template <> __device__ __forceinline__ float lane_read<float>(float v, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-template <> __device__ __forceinline__ double lane_read<double>(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 template <typename T, int KC, int NS>
 __global__ void __launch_bounds__(256)
 k_fwd_gemv_wave(const SolveFront* __restrict__ list, const int2* __restrict__ tmap, int total,
