@@ -96,20 +96,30 @@ __device__ __forceinline__ Split3<W> split3(const float (&x)[W], const SplitSel&
 template <typename C> __device__ __forceinline__ C ld_at(const char* base, unsigned off) {
   return ld(reinterpret_cast<const C*>(base + off));
 }
-// Consecutive values at such an offset, aligned to one complex value: two
-// complex64 per 16-byte load.
-__device__ __forceinline__ void ld_run(const char* base, unsigned off, float2 (&x)[8]) {
+// The K order of a step.  Lane group kg = l / 16 of the row operand holds KP
+// values of k; which ones is free as long as the column operand agrees.  Value
+// j of group kg is k = 8 (j / 2) + 2 kg + j % 2 in complex64 and 4 j + kg in
+// complex128: the four groups' 16-byte loads of one instruction then cover 64
+// contiguous bytes of each row, where consecutive k per group would touch four
+// times the cache lines per instruction (97^3 complex128: 21 columns 1016 ->
+// 967 us, 64 columns 1870 -> 1781; the 100^3 sweep 126 -> 118 ms).
+template <typename T> __device__ __forceinline__ constexpr int tile_kk(int kg, int j) {
+  return sizeof(T) == 4 ? 8 * (j / 2) + 2 * kg + j % 2 : 4 * j + kg;
+}
+// A lane's values of a row with contiguous k (base and offset at the step's
+// k = 0 of the row), aligned to one complex value: two complex64 per load.
+__device__ __forceinline__ void ld_run(const char* base, unsigned off, int kg, float2 (&x)[8]) {
   typedef float V __attribute__((ext_vector_type(4), aligned(8)));
 #pragma unroll
   for (int i = 0; i < 8; i += 2) {
-    const V v = *(const HELM_AS1 V*)(const HELM_AS1 char*)(base + off + 8 * i);
+    const V v = *(const HELM_AS1 V*)(const HELM_AS1 char*)(base + (off + 16u * kg) + 32 * i);
     x[i] = make_float2(v.x, v.y);
     x[i + 1] = make_float2(v.z, v.w);
   }
 }
-__device__ __forceinline__ void ld_run(const char* base, unsigned off, double2 (&x)[4]) {
+__device__ __forceinline__ void ld_run(const char* base, unsigned off, int kg, double2 (&x)[4]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) x[i] = ld_at<double2>(base, off + 16 * i);
+  for (int i = 0; i < 4; ++i) x[i] = ld_at<double2>(base + 64 * i, off + 16u * kg);
 }
 
 template <typename T, int BM, int BN> struct TileShape {
@@ -123,14 +133,14 @@ template <typename T, int BM, int BN> struct TileShape {
 // LDS of the column operand: per buffer
 //  complex64: [plane: re h m l, im h m l][8 k][column] of 8 bf16, so that
 //   stores and reads of 16 lanes are 256 contiguous bytes;
-//  complex128: [re, im][k][column], rows padded by 4 elements, which puts the
-//   two halves of a read (k rows 4 apart) on different halves of the banks.
+//  complex128: [re, im][k][column], rows padded so that the four k rows of a
+//   read start on different quarters of the banks.
 template <typename T, int BN> struct TileSmem;
 template <int BN> struct TileSmem<float, BN> {
   bf8 q[2][6][4][BN];
 };
 template <int BN> struct TileSmem<double, BN> {
-  double q[2][2][16][BN + 4];
+  double q[2][2][16][BN + 8];
 };
 
 // Accumulators of one wave: 16 rows x NB 16-column blocks (complex64 keeps
@@ -204,7 +214,7 @@ template <typename T> struct TileQ {
 };
 
 // One K step of MFMAs of a wave on the lane's row values p (lane l: row
-// l % 16, k = KP (l / 16) + 0..KP-1) and the block's staged columns.
+// l % 16, k in the step's order) and the block's staged columns.
 template <int BM, int BN>
 __device__ __forceinline__ void tile_mfma(const TileSmem<float, BN>& sm, int buf,
                                           TileAcc<float, BM, BN>& acc, const Split3<8>& ar,
@@ -242,7 +252,7 @@ __device__ __forceinline__ void tile_mfma(const TileSmem<double, BN>& sm, int bu
     for (int b = 0; b < NB; ++b) {
       if (b >= nbv) break;
       const int c = (wc * NB + b) * 16 + (lane & 15);
-      const double qr = sm.q[buf][0][4 * kg + j][c], qi = sm.q[buf][1][4 * kg + j][c];
+      const double qr = sm.q[buf][0][4 * j + kg][c], qi = sm.q[buf][1][4 * j + kg][c];
       acc.re[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[j].x, qr, acc.re[b], 0, 0, 0);
       acc.im[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[j].x, qi, acc.im[b], 0, 0, 0);
       acc.re[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-p[j].y, qi, acc.re[b], 0, 0, 0);
@@ -278,12 +288,16 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
                                                         : P.base + r0);
   const unsigned pld = (unsigned)P.ld * E;
   const unsigned prow = (unsigned)row * (CONTIG ? pld : E);
-  const unsigned poff = prow + (unsigned)(kg * KP) * (CONTIG ? E : pld);
   const int qc = min(t % BN, Q.cols - 1 - c0);
-  const int qk = (t / BN) * KPT;                  // this thread's k within a step
+  // this thread's values of k within a step: positions qk.. of the order in
+  // complex64 (8 per group), rows qk.. in complex128
+  const int qk = (t / BN) * KPT;
+  auto kof = [&](int i) {
+    return sizeof(T) == 4 ? tile_kk<T>(qk / 8, qk % 8 + i) : qk + i;
+  };
   const char* qb = reinterpret_cast<const char*>(Q.base + c0);
   const unsigned qld = (unsigned)Q.ld * E;
-  const unsigned qoff = (unsigned)qk * qld + (unsigned)qc * E;
+  const unsigned qoff = (unsigned)kof(0) * qld + (unsigned)qc * E;
   const SplitSel sel;
 
   constexpr bool MAP = QM == kMap, GAT = QM == kGather;
@@ -294,12 +308,12 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
   auto load_index = [&](int k0) {
     if constexpr (MAP) {
 #pragma unroll
-      for (int i = 0; i < KPT; ++i) ki[i] = ld(Q.kmap + min(k0 + qk + i, kend - 1));
+      for (int i = 0; i < KPT; ++i) ki[i] = ld(Q.kmap + min(k0 + kof(i), kend - 1));
     }
     if constexpr (GAT) {
 #pragma unroll
       for (int i = 0; i < KPT; ++i) {
-        const int kk = min(k0 + qk + i, kend - 1);
+        const int kk = min(k0 + kof(i), kend - 1);
         ki[i] = Q.inv[0] ? ld(Q.inv[0] + kk) : -1;
         kj[i] = Q.inv[1] ? ld(Q.inv[1] + kk) : -1;
       }
@@ -322,24 +336,27 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
   auto load_whole = [&](int k0) {   // k0 + K <= kend
     const char* b = pb + (long long)k0 * (CONTIG ? (long long)E : P.ld * (long long)E);
     if constexpr (CONTIG) {
-      ld_run(b, poff, p);
+      ld_run(b, prow, kg, p);
     } else {
 #pragma unroll
-      for (int i = 0; i < KP; ++i) p[i] = ld_at<C>(b + (long long)i * P.ld * E, poff);
+      for (int i = 0; i < KP; ++i)
+        p[i] = ld_at<C>(b + (long long)tile_kk<T>(0, i) * P.ld * E,
+                        prow + (unsigned)tile_kk<T>(kg, 0) * pld);
     }
     if constexpr (MAP) {
       load_mapped();
     } else {
       const char* c = qb + (long long)k0 * Q.ld * E;
 #pragma unroll
-      for (int i = 0; i < KPT; ++i) q[i] = ld_at<C>(c + (long long)i * Q.ld * E, qoff);
+      for (int i = 0; i < KPT; ++i)
+        q[i] = ld_at<C>(c + (long long)(sizeof(T) == 4 ? tile_kk<T>(0, i) : i) * Q.ld * E, qoff);
     }
     load_updates();
   };
   auto load_part = [&](int k0) {    // k0 < kend: clamped to the last k
 #pragma unroll
     for (int i = 0; i < KP; ++i) {
-      const long long kk = min(k0 + kg * KP + i, kend - 1);
+      const long long kk = min(k0 + tile_kk<T>(kg, i), kend - 1);
       p[i] = ld(reinterpret_cast<const C*>(pb + prow) + kk * (CONTIG ? 1LL : P.ld));
     }
     if constexpr (MAP) {
@@ -347,7 +364,7 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
     } else {
 #pragma unroll
       for (int i = 0; i < KPT; ++i)
-        q[i] = ld(reinterpret_cast<const C*>(qb) + (long long)min(k0 + qk + i, kend - 1) * Q.ld + qc);
+        q[i] = ld(reinterpret_cast<const C*>(qb) + (long long)min(k0 + kof(i), kend - 1) * Q.ld + qc);
     }
     load_updates();
   };
@@ -361,7 +378,7 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
     if (kleft < K) {
 #pragma unroll
       for (int i = 0; i < KPT; ++i)
-        if (qk + i >= kleft) q[i] = czero<C>();
+        if (kof(i) >= kleft) q[i] = czero<C>();
     }
     if constexpr (sizeof(T) == 4) {
       float x[KPT], y[KPT];
