@@ -263,28 +263,47 @@ __global__ void __launch_bounds__(256) k_readout(LayerDev L, ReadOuts ro, int nx
 // ----------------------------------------------------------------------------
 // FP64 column-batched vector kernels; vectors are V x k with k fastest.
 // ----------------------------------------------------------------------------
-constexpr int DOT_COLS = 32, DOT_ROWS = 8, DOT_BLOCKS = 256;
+constexpr int DOT_BLOCKS = 256;
 
-// partial[c][blk] = sum_v conj(x[v, c]) y[v, c] over this block's rows
+// partial[c][blk] = sum_v conj(x[v, c]) y[v, c] over this block's rows: COLS
+// columns (the power of two that holds a narrow batch, at most 32) by
+// 256 / COLS rows at a time.  Bound by memory once every lane has a column:
+// with 32 columns at every width one column used one lane in 32.  Kernel times:
+// 100^3, 1 column 37.6 -> 4.2 us; 97^3, 21 columns 42.6 -> 26.8 (two loads in
+// flight); 25^3, 1 column, no gain (3 us, a launch's own time).
+template <int COLS>
 __global__ void __launch_bounds__(256)
 k_dot_partial(const double2* __restrict__ x, const double2* __restrict__ y,
               long long V, int k, double2* __restrict__ partial) {
-  const int tx = threadIdx.x % DOT_COLS, ty = threadIdx.x / DOT_COLS;
-  const int c = blockIdx.y * DOT_COLS + tx;
+  constexpr int ROWS = 256 / COLS;
+  const int tx = threadIdx.x % COLS, ty = threadIdx.x / COLS;
+  const int c = blockIdx.y * COLS + tx;
   double re = 0, im = 0;
   if (c < k) {
-    for (long long v = blockIdx.x * DOT_ROWS + ty; v < V; v += (long long)gridDim.x * DOT_ROWS) {
+#pragma unroll 2
+    for (long long v = blockIdx.x * ROWS + ty; v < V; v += (long long)gridDim.x * ROWS) {
       const double2 a = x[v * k + c], b = y[v * k + c];
       re += a.x * b.x + a.y * b.y;
       im += a.x * b.y - a.y * b.x;
     }
   }
-  __shared__ double sre[DOT_ROWS][DOT_COLS], sim[DOT_ROWS][DOT_COLS];
-  sre[ty][tx] = re;
-  sim[ty][tx] = im;
+  // the rows of a wave by a butterfly, then the four waves in order
+  for (int o = COLS; o < 64; o <<= 1) {
+    re += __shfl_xor(re, o);
+    im += __shfl_xor(im, o);
+  }
+  __shared__ double sre[4][COLS], sim[4][COLS];
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) < COLS) {
+    sre[wave][tx] = re;
+    sim[wave][tx] = im;
+  }
   __syncthreads();
-  if (ty == 0 && c < k) {
-    for (int q = 1; q < DOT_ROWS; ++q) { re += sre[q][tx]; im += sim[q][tx]; }
+  if (threadIdx.x < COLS && c < k) {
+    for (int q = 1; q < 4; ++q) {
+      re += sre[q][tx];
+      im += sim[q][tx];
+    }
     partial[(long long)c * gridDim.x + blockIdx.x] = make_double2(re, im);
   }
 }
@@ -554,8 +573,16 @@ void launch_readout(const LayerDev& L, const ReadOuts& ro, int nx, int ny, int k
 
 void launch_dot(const double2* x, const double2* y, long long V, int k,
                 double2* partial, double2* out, hipStream_t st) {
-  dim3 grid(DOT_BLOCKS, (k + DOT_COLS - 1) / DOT_COLS);
-  hipLaunchKernelGGL(k_dot_partial, grid, dim3(256), 0, st, x, y, V, k, partial);
+#define HELM_DOT(COLS)                                                                      \
+  hipLaunchKernelGGL(k_dot_partial<COLS>, dim3(DOT_BLOCKS, (k + COLS - 1) / COLS), dim3(256), 0, \
+                     st, x, y, V, k, partial)
+  if (k == 1) HELM_DOT(1);
+  else if (k == 2) HELM_DOT(2);
+  else if (k <= 4) HELM_DOT(4);
+  else if (k <= 8) HELM_DOT(8);
+  else if (k <= 16) HELM_DOT(16);
+  else HELM_DOT(32);
+#undef HELM_DOT
   hipLaunchKernelGGL(k_dot_final, dim3(k), dim3(64), 0, st, partial, DOT_BLOCKS, out);
 }
 void launch_axpy_cols(double2* y, const double2* x, const double2* alpha,
