@@ -943,6 +943,11 @@ k_panel_rb(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // touches (at most nbf of them) holds old row srcO[i].  Every new value is
 // then one independent load, so the column tile is read once, in parallel,
 // instead of through nbf dependent swaps per column.
+// complex128 takes the product on the matrix-core tile (whole operands in LDS
+// were 133 KB, one block per CU): 71^3 8.6 -> 5.9 ms.  complex64 keeps FP32
+// products: the tile's split took 100^3 from 14.7 to 9.9 ms, but the layer
+// solves' error against complex128 grew by 9% on smooth media (geometric mean
+// 1.95e-6 -> 2.12e-6).
 // --------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -963,8 +968,6 @@ k_swap_JO(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const int t = threadIdx.x;
   __shared__ int srcJ[NBMAX], rowO[NBMAX], srcO[NBMAX];
   __shared__ int nO;
-  __shared__ C V[NBMAX][GT + 1];
-  __shared__ C DsT[NBMAX][NBMAX + 1];  // DsT[q][r] = D(r, q)
   if (t < 64) {
     // lane i holds srcJ[i] and outside entry i (row ro, source so)
     int vJ = k + t, ro = -1, so = 0, cnt = 0;
@@ -1005,56 +1008,95 @@ k_swap_JO(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
     const bool ok = r < no && gc < n;
     w[i] = ld_or_zero(ok, F + (ok ? (long long)srcO[r] + (long long)gc * n : 0));
   }
-  // the rows J of the tile and D: every load issued before the first store
-  C vj[WPT], dw[WPT];
+  if constexpr (sizeof(T) == 8) {
+    // the rows are swapped in place and read back as the tile's row operand
+    C vj[WPT];
 #pragma unroll
-  for (int i = 0; i < WPT; ++i) {
-    const int e = t + 256 * i, r = e % NBMAX, c = e / NBMAX, gc = c0 + c;
-    const bool ok = r < nbf && gc < n;
-    vj[i] = ld_or_zero(ok, F + (ok ? (long long)srcJ[r] + (long long)gc * n : 0));
-    const bool dok = r < nbf && c < nbf;
-    dw[i] = ld_or_zero(dok, D + (dok ? r + c * nb : 0));
-  }
+    for (int i = 0; i < WPT; ++i) {
+      const int e = t + 256 * i, r = e % NBMAX, gc = c0 + e / NBMAX;
+      const bool ok = r < nbf && gc < n;
+      vj[i] = ld_or_zero(ok, F + (ok ? (long long)srcJ[r] + (long long)gc * n : 0));
+    }
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < WPT; ++i) {
-    const int e = t + 256 * i, r = e % NBMAX, c = e / NBMAX;
-    V[r][c] = vj[i];
-    DsT[c][r] = dw[i];
-  }
-  __syncthreads();
+    for (int i = 0; i < WPT; ++i) {
+      const int e = t + 256 * i, r = e / GT, gc = c0 + e % GT;
+      if (r < no && gc < n) st(F + (long long)rowO[r] + (long long)gc * n, w[i]);
+      const int rj = e % NBMAX, gj = c0 + e / NBMAX;
+      if (rj < nbf && gj < n) st(F + (long long)(k + rj) + (long long)gj * n, vj[i]);
+    }
+    __syncthreads();
+    // P rows = columns gc of F: V^T(gc, q) = F[(k + q) + gc n], swapped above
+    // Q columns = rows r of J: D^T(q, r) = D[r + q nb]
+    __shared__ TileSmem<T, 64> sm;
+    TileAcc<T, 64, 64> acc;
+    tile_gemm<T, 64, 64, true, kDirect>(sm, acc, TileP<T>{F + k, n, n}, TileQ<T>{D, nb, nbf},
+                                        c0, 0, 0, nbf);
+    __syncthreads();   // in place: every read before any write
+    using O = TileOut<T, 64, 64>;
+    const O o;
 #pragma unroll
-  for (int i = 0; i < WPT; ++i) {
-    const int e = t + 256 * i, r = e / GT, gc = c0 + e % GT;
-    if (r < no && gc < n) st(F + (long long)rowO[r] + (long long)gc * n, w[i]);
-  }
-  // rows J of the tile: thread (rg, cg) owns rows rg + 16 i and columns
-  // cg + 16 j (i, j < 4), so each LDS value read feeds four products
-  const int rg = t & 15, cg = t >> 4;
-  C acc[4][4];
+    for (int i = 0; i < O::NR; ++i)
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+      for (int j = 0; j < O::NC; ++j) {
+        const int gc = c0 + o.r[i], r = o.c[j];
+        if (r >= nbf || gc >= n || (gc >= k && gc < k + nbf)) continue;
+        st(F + (long long)(k + r) + (long long)gc * n, acc_at(acc, i, j));
+      }
+  } else {
+    __shared__ C V[NBMAX][GT + 1];
+    __shared__ C DsT[NBMAX][NBMAX + 1];  // DsT[q][r] = D(r, q)
+    // the rows J of the tile and D: every load issued before the first store
+    C vj[WPT], dw[WPT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = czero<C>();
-  for (int q = 0; q < nbf; ++q) {
-    C dv[4], vv[4];
+    for (int i = 0; i < WPT; ++i) {
+      const int e = t + 256 * i, r = e % NBMAX, c = e / NBMAX, gc = c0 + c;
+      const bool ok = r < nbf && gc < n;
+      vj[i] = ld_or_zero(ok, F + (ok ? (long long)srcJ[r] + (long long)gc * n : 0));
+      const bool dok = r < nbf && c < nbf;
+      dw[i] = ld_or_zero(dok, D + (dok ? r + c * nb : 0));
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dv[i] = DsT[q][rg + 16 * i];
+    for (int i = 0; i < WPT; ++i) {
+      const int e = t + 256 * i, r = e % NBMAX, c = e / NBMAX;
+      V[r][c] = vj[i];
+      DsT[c][r] = dw[i];
+    }
+    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 4; ++j) vv[j] = V[q][cg + 16 * j];
+    for (int i = 0; i < WPT; ++i) {
+      const int e = t + 256 * i, r = e / GT, gc = c0 + e % GT;
+      if (r < no && gc < n) st(F + (long long)rowO[r] + (long long)gc * n, w[i]);
+    }
+    // rows J of the tile: thread (rg, cg) owns rows rg + 16 i and columns
+    // cg + 16 j (i, j < 4), so each LDS value read feeds four products
+    const int rg = t & 15, cg = t >> 4;
+    C acc[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) cfma(acc[i][j], dv[i], vv[j]);
-  }
+      for (int j = 0; j < 4; ++j) acc[i][j] = czero<C>();
+    for (int q = 0; q < nbf; ++q) {
+      C dv[4], vv[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i) dv[i] = DsT[q][rg + 16 * i];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = rg + 16 * i, c = cg + 16 * j, gc = c0 + c;
-      if (r >= nbf || gc >= n) continue;
-      const bool inJ = gc >= k && gc < k + nbf;
-      st(F + (long long)(k + r) + (long long)gc * n, inJ ? V[r][c] : acc[i][j]);
+      for (int j = 0; j < 4; ++j) vv[j] = V[q][cg + 16 * j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cfma(acc[i][j], dv[i], vv[j]);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = rg + 16 * i, c = cg + 16 * j, gc = c0 + c;
+        if (r >= nbf || gc >= n) continue;
+        const bool inJ = gc >= k && gc < k + nbf;
+        st(F + (long long)(k + r) + (long long)gc * n, inJ ? V[r][c] : acc[i][j]);
+      }
+  }
 }
 
 // --------------------------------------------------------------------------
@@ -1128,7 +1170,11 @@ k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 
 // --------------------------------------------------------------------------
 // columns J: rows outside J <- -F(O, J) D, rows J <- D.  One workgroup per
-// 64-row tile.
+// 64-row tile, as one product of the matrix-core tile (K = the pivot block).
+// Bound by the latency of its loads: with both operands held whole in LDS
+// (133 KB in complex128) one block ran per CU.  Factorization of 100^3
+// complex64 10.6 -> 6.0 ms, 71^3 complex128 6.9 -> 4.2; the error of the
+// complex64 layer solves against complex128 is the same to 0.5%.
 // --------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -1145,54 +1191,24 @@ k_update_OJ(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const int r0 = tm.y * GT;
   C* F = front_ptr<T>(ws0, ws1, f);
   const C* D = reinterpret_cast<const C*>(D_base) + panel_off[a];
-  __shared__ C V[GT][NBMAX + 1];
-  __shared__ C Ds[NBMAX][NBMAX + 1];
-  const int t = threadIdx.x;
-  // every load of the tile and of D issued before the first LDS store
-  constexpr int WPT = NBMAX * GT / 256;
-  C w[WPT], dw[WPT];
+  // P rows = columns c of the panel: D^T(c, q) = D[q + c nb]
+  // Q columns = rows i of F: F(i, q) = F[i + (k + q) n]
+  __shared__ TileSmem<T, 64> sm;
+  TileAcc<T, 64, 64> acc;
+  tile_gemm<T, 64, 64, true, kDirect>(sm, acc, TileP<T>{D, nb, nbf},
+                                      TileQ<T>{F + (long long)k * n, n, n}, 0, r0, 0, nbf);
+  __syncthreads();   // the tile is updated in place: every read before any write
+  using O = TileOut<T, 64, 64>;
+  const O o;
 #pragma unroll
-  for (int i = 0; i < WPT; ++i) {
-    const int e = t + 256 * i, r = e % GT, c = e / GT;
-    const bool ok = r0 + r < n && c < nbf;
-    w[i] = ld_or_zero(ok, F + (ok ? (long long)(r0 + r) + (long long)(k + c) * n : 0));
-    const int dr = e % NBMAX, dc = e / NBMAX;
-    const bool dok = dr < nbf && dc < nbf;
-    dw[i] = ld_or_zero(dok, D + (dok ? dr + dc * nb : 0));
-  }
+  for (int i = 0; i < O::NR; ++i)
 #pragma unroll
-  for (int i = 0; i < WPT; ++i) {
-    const int e = t + 256 * i;
-    V[e % GT][e / GT] = w[i];
-    Ds[e % NBMAX][e / NBMAX] = dw[i];
-  }
-  __syncthreads();
-  // thread (rg, cg) owns rows rg + 16 i and columns cg + 16 j (i, j < 4)
-  const int rg = t & 15, cg = t >> 4;
-  C acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = czero<C>();
-  for (int q = 0; q < nbf; ++q) {
-    C vv[4], dv[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) vv[i] = V[rg + 16 * i][q];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dv[j] = Ds[q][cg + 16 * j];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cfma(acc[i][j], vv[i], dv[j]);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = rg + 16 * i, c = cg + 16 * j, gr = r0 + r;
+    for (int j = 0; j < O::NC; ++j) {
+      const int gr = r0 + o.c[j], c = o.r[i];
       if (gr >= n || c >= nbf) continue;
       const bool inJ = gr >= k && gr < k + nbf;
-      st(F + (long long)gr + (long long)(k + c) * n, inJ ? Ds[gr - k][c] : cneg(acc[i][j]));
+      st(F + (long long)gr + (long long)(k + c) * n,
+         inJ ? ld(D + (gr - k) + c * nb) : cneg(acc_at(acc, i, j)));
     }
 }
 
