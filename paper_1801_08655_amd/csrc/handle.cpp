@@ -634,8 +634,7 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
   // 1042, at 64 columns 1882, 1928, -, 1929; complex64 25^3 at 32 columns 183,
   // 185, 199, 197, 96^3 at 64 columns 904, 946, 911, 920, 160^3 at 32 columns
   // 1486, 1446, 1428, 1487.
-  const int target = 768, kmin = 64;
-  auto split = [&](long long tiles, int K, int& nch, int& kc) {
+  auto split_at = [](int target, int kmin, long long tiles, int K, int& nch, int& kc) {
     nch = 1;
     if (K > 0 && tiles < target / 2) {
       long long want = (target + tiles - 1) / tiles;
@@ -645,6 +644,16 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
     kc = (K + nch - 1) / nch;
     kc = (kc + 15) / 16 * 16;
     nch = (K + kc - 1) / kc;
+  };
+  auto split = [&](long long tiles, int K, int& nch, int& kc) {
+    split_at(768, 64, tiles, K, nch, kc);
+  };
+  // Rows of partials at chunks of at least 256 and 2048 workgroups: what the
+  // allocation-free solve's limit counts, whatever the launches really take.
+  auto limit = [&](long long tiles, int K, int rows) -> long long {
+    int nch, kc;
+    split_at(2048, 256, tiles, K, nch, kc);
+    return nch > 1 ? (long long)nch * rows : 0;
   };
   auto fwd_on = [&](int f) { return !pr || pr->fwd[f]; };
   auto bwd_on = [&](int f) { return !pr || pr->bwd[f]; };
@@ -700,7 +709,7 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
     const int bm = mean_s <= 40 ? 32 : 64;
     D->bwd_bm = bm;
     auto tiles = [](long long rows, int t) { return (int)((rows + t - 1) / t); };
-    long long tb = 0, scr_b = 0;
+    long long tb = 0, scr_b = 0, lim_b = 0;
     for (const auto& r : bw) tb += tiles(r.s, bm);
     std::vector<int> pB(n + 1, 0), rB(n + 1, 0);
     for (size_t a = 0; a < n; ++a) {
@@ -708,12 +717,13 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
       split(tb, r.b, r.nch, r.kc);
       r.scr = scr_b;
       if (r.nch > 1) scr_b += (long long)r.nch * r.s;
+      lim_b += limit(tb, r.b, r.s);
       pB[a + 1] = pB[a] + tiles(r.s, bm) * r.nch;
       rB[a + 1] = rB[a] + (r.nch > 1 ? tiles16(r.s) : 0);
     }
     // forward: every front takes the GEMM; only fronts with children need
     // the extend-add gather (leaves read their pivots straight from X)
-    long long tf = 0, scr_f = 0;
+    long long tf = 0, scr_f = 0, lim_f = 0;
     for (const auto& r : fw) tf += tiles64(r.s + r.b);
     std::vector<int> pS(nl + 1, 0), pF(nl + 1, 0), rF(nl + 1, 0);
     for (size_t a = 0; a < nl; ++a) {
@@ -721,6 +731,7 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
       split(tf, r.s, r.nch, r.kc);
       r.scr = scr_f;
       if (r.nch > 1) scr_f += (long long)r.nch * (r.s + r.b);
+      lim_f += limit(tf, r.s, r.s + r.b);
       const bool kids = r.inv[0] >= 0 || r.inv[1] >= 0;
       if (kids) {
         D->fs_s += r.s; D->fs_b += r.b;
@@ -762,6 +773,7 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
     map(D->vB, D->tVB, vB);
     D->scratch_rows = std::max(scr_f, scr_b);
     S->scratch_rows = std::max(S->scratch_rows, D->scratch_rows);
+    S->limit_rows = std::max({S->limit_rows, lim_f, lim_b});
     S->depth.push_back(std::move(D));
   }
   upload(S->lists, pack, st);

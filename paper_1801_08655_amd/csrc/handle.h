@@ -84,6 +84,7 @@ struct LayerSet {
   int max_depth = 0;
   double elems = 0;             // factor elements one solve reads
   long long scratch_rows = 0;   // max over depths
+  long long limit_rows = 0;     // the rows that the allocation-free solve's limit counts
   std::vector<std::unique_ptr<DepthList>> depth;
   DevMem lists;                 // every depth's lists and tile maps
 };

@@ -9,10 +9,11 @@
 //   - X (the solve vector, n_loc x k), Z (the forward results, n_loc x k),
 //   - the two depth-parity update buffers (ub_rows[0] x k, ub_rows[1] x k),
 //   - the split-K partial products (scratch_rows x k),
-// in the precision of the factors.  Every byte that the kernels read is
+// in the precision of the factors, k being the columns of one pass.  Every byte that the kernels read is
 // written earlier in the same call (X by the copy-in, Z and the update
 // buffers by the forward pass, the partials by the GEMM chunks), so nothing
 // has to start at zero and the previous call's contents never matter.
+#include <algorithm>
 #include <mutex>
 
 #include "api_common.h"
@@ -64,34 +65,46 @@ template <typename T>
 void solve_noalloc(Handle& H, int l, int k, const double2* r, double2* w, unsigned char* base) {
   const LayerPlan& P = H.G.layers[l];
   const LayerSet& S = *H.single_sets[l];
-  const size_t e = H.elem, kk = (size_t)k;
+  const size_t e = H.elem, cap = HELM_NOALLOC_SCRATCH_BYTES;
   const size_t table = round256((size_t)H.G.L * sizeof(LayerDev));
-  const size_t x_b = round256((size_t)P.n_loc * kk * e);
-  const size_t u0_b = round256((size_t)std::max<long long>(P.ub_rows[0], 1) * kk * e);
-  const size_t u1_b = round256((size_t)std::max<long long>(P.ub_rows[1], 1) * kk * e);
-  const size_t sk_b = round256((size_t)std::max<long long>(S.scratch_rows, 1) * kk * e);
-  const size_t need = table + 2 * x_b + u0_b + u1_b + sk_b;
-  HELM_REQUIRE(need <= (size_t)HELM_NOALLOC_SCRATCH_BYTES, HELM_ENOMEM,
-               "local solve needs " + std::to_string(need) +
-                   " bytes of workspace, more than the static scratch of " +
-                   std::to_string((size_t)HELM_NOALLOC_SCRATCH_BYTES) +
+  const size_t u0 = std::max<long long>(P.ub_rows[0], 1), u1 = std::max<long long>(P.ub_rows[1], 1);
+  auto bytes = [&](size_t rows, size_t cols) { return round256(rows * cols * e); };
+  auto need = [&](size_t cols, long long split_rows) {
+    return table + 2 * bytes((size_t)P.n_loc, cols) + bytes(u0, cols) + bytes(u1, cols) +
+           bytes((size_t)std::max<long long>(split_rows, 1), cols);
+  };
+  const size_t asked = need((size_t)k, S.limit_rows);
+  HELM_REQUIRE(asked <= cap, HELM_ENOMEM,
+               "local solve needs " + std::to_string(asked) +
+                   " bytes of workspace, more than the static scratch of " + std::to_string(cap) +
                    " bytes (use fewer columns or helm_layer_solve_dev)");
+  // The launches' own partials can take more than the limit counts: then the
+  // columns go in passes of equal width.  Up to 4 columns (the vector kernels)
+  // have no partials, so a pass always fits.
+  int cols = k;
+  while (cols > 4 && need((size_t)cols, S.scratch_rows) > cap) --cols;
+  const int passes = (k + cols - 1) / cols;
+  cols = (k + passes - 1) / passes;
   LayerDev* tab = reinterpret_cast<LayerDev*>(base);
   LayerDev v = H.layers_h[l];
   unsigned char* p = base + table;
   v.X = p;
-  p += x_b;
+  p += bytes((size_t)P.n_loc, cols);
   v.Wt = p;
-  p += x_b;
+  p += bytes((size_t)P.n_loc, cols);
   v.Ub[0] = p;
-  p += u0_b;
+  p += bytes(u0, cols);
   v.Ub[1] = p;
-  p += u1_b;
+  p += bytes(u1, cols);
   void* splitk = p;
   hipLaunchKernelGGL(k_put_layer, dim3(1), dim3(64), 0, H.st, tab + l, v);
-  kern::launch_local_to_X<T>(v, r, k, H.st);
-  H.run_layers_t<T>(S, k, tab, splitk, nullptr, false);
-  kern::launch_X_to_local<T>(v, w, k, H.st);
+  for (int c = 0; c < k; c += cols) {
+    const int n = std::min(cols, k - c);
+    const long long at = (long long)c * P.n_loc;
+    kern::launch_local_to_X<T>(v, r + at, n, H.st);
+    H.run_layers_t<T>(S, n, tab, splitk, nullptr, false);
+    kern::launch_X_to_local<T>(v, w + at, n, H.st);
+  }
 }
 
 }  // namespace
