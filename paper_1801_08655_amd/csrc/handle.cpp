@@ -633,7 +633,8 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
   // (128, 1024), (128, 2048): complex128 97^3 at 21 columns 1015, 1027, -,
   // 1042, at 64 columns 1882, 1928, -, 1929; complex64 25^3 at 32 columns 183,
   // 185, 199, 197, 96^3 at 64 columns 904, 946, 911, 920, 160^3 at 32 columns
-  // 1486, 1446, 1428, 1487.
+  // 1486, 1446, 1428, 1487 (all before the tile's K order, which took 97^3 at
+  // 21 columns to 967 and at 64 to 1781 with the values below).
   auto split_at = [](int target, int kmin, long long tiles, int K, int& nch, int& kc) {
     nch = 1;
     if (K > 0 && tiles < target / 2) {
