@@ -1029,7 +1029,7 @@ k_swap_JO(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
     // P rows = columns gc of F: V^T(gc, q) = F[(k + q) + gc n], swapped above
     // Q columns = rows r of J: D^T(q, r) = D[r + q nb]
     __shared__ TileSmem<T, 64> sm;
-    TileAcc<T, 64, 64> acc;
+    TileAcc<T, 64, 64, true> acc;
     tile_gemm<T, 64, 64, true, kDirect>(sm, acc, TileP<T>{F + k, n, n}, TileQ<T>{D, nb, nbf},
                                         c0, 0, 0, nbf);
     __syncthreads();   // in place: every read before any write
@@ -1139,7 +1139,7 @@ k_sweep_gemm(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   // P rows = C columns j: B^T(j, q) = F[(k + q) + j n]
   // Q columns = C rows i: A^T(q, i) = F[i + (k + q) n]
   __shared__ TileSmem<T, 64> sm;
-  TileAcc<T, 64, 64> acc;
+  TileAcc<T, 64, 64, true> acc;
   tile_gemm<T, 64, 64, true, kDirect>(sm, acc, TileP<T>{F + k, n, n},
                                       TileQ<T>{F + (long long)k * n, n, n}, j0, i0, 0, nbf);
   // F(i, j) -= product: every entry of the lane is loaded before the first
@@ -1194,7 +1194,7 @@ k_update_OJ(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   // P rows = columns c of the panel: D^T(c, q) = D[q + c nb]
   // Q columns = rows i of F: F(i, q) = F[i + (k + q) n]
   __shared__ TileSmem<T, 64> sm;
-  TileAcc<T, 64, 64> acc;
+  TileAcc<T, 64, 64, true> acc;
   tile_gemm<T, 64, 64, true, kDirect>(sm, acc, TileP<T>{D, nb, nbf},
                                       TileQ<T>{F + (long long)k * n, n, n}, 0, r0, 0, nbf);
   __syncthreads();   // the tile is updated in place: every read before any write

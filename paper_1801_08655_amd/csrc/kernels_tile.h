@@ -13,24 +13,38 @@
 // results are never stored); past the K range the column operand is zero and
 // the row operand clamped, so no out-of-range value is read.
 //
-// complex64: on the bf16 matrix cores, at (better than) FP32 accuracy.  A
-// float x is split exactly into three bf16 numbers, x = h + m + l: h is x
-// rounded to bf16, m the rounded rest, l what is left (24 = 3 x 8 significant
-// bits).  A real product is then formed from the six bf16 products
+// complex64: on the bf16 matrix cores, at FP32 accuracy (the three-way split of
+// Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence
+// Datatype For Higher-Precision Computations", ARITH 2019).  A float x is split
+// into three bf16 numbers, x = h + m + l: h is x rounded to bf16, m the rounded
+// rest, l what is left (24 = 3 x 8 significant bits).  The split is exact for
+// 2^-110 <= |x| < 2^128 (1 - 2^-9); below, l ends on bf16's smallest
+// subnormal (an error of 2^-134), above, h rounds to infinity.  A real product
+// is then formed from the six bf16 products
 //   h h' + h m' + m h' + h l' + l h' + m m',
 // accumulated in FP32 by the matrix cores, smallest first; the dropped ones
-// (m l', l m', l l') are below 2^-24 of |x||x'|.  Measured against FP64 on
-// normal data, the error of a length-K product is 0.37 (K = 32), 0.79 (256)
-// and 0.85 (1024) of the v_mfma_f32_16x16x4f32 chain's: an MFMA of K = 32
-// rounds once where the FP32 instruction rounds 32 times.  Why: on gfx950 the
-// FP32 matrix instructions run at 134 TFLOP/s (measured loop) and the bf16
-// ones at 2100, so six products per real one still leave 350.  What bounds the
-// tile then is the latency of its operand loads, not the matrix cores.
-// Against the FP32 tile it replaced (three real products, both operands in
-// LDS): one interior layer of 100^3 with 64 columns 1.75 -> 1.57 ms, a whole
-// refined solve of 64 sources on 96^3 419 -> 362 ms; the local solve's error
-// against complex128 2.15e-6 -> 2.05e-6 (25^3: 8.8e-7 -> 7.7e-7), smaller at
-// every width.
+// (m l', l m', l l') are below 2^-24 of |x||x'| (with them the errors below
+// are the same).  Root mean square error of a length-K product against FP64,
+// normal data, K = 32 / 64 / 256 / 1024, in 1e-7:
+//   v_mfma_f32_16x16x4f32     1.02 / 1.45 / 2.86 / 5.72
+//   sums running through      0.38 / 0.93 / 2.28 / 4.88
+//   a sum per K step (STEP)   0.38 / 0.47 / 0.69 / 1.18
+// Running sums are rounded by every one of a step's six instructions, a step's
+// own sum only once at the size of the whole.  STEP costs the substitutions 2 to
+// 4% (96^3, 64 columns 882 -> 906 us a pruned layer solve) without any effect
+// on their error, which the factors' decides, so they let the sums run; the
+// factorization takes STEP at the same time (160^3 754 and 755 ms): at 200^3
+// (layered) the layer solves' error against complex128 has geometric mean
+// 0.97e-5 and largest value 1.2e-4, with running sums 1.03e-5 and 2.2e-4, with
+// the FP32 tile of three real products before 1.13e-5 and 1.8e-4.  The largest
+// values belong to four nearly singular layers and move by a factor 2 with any
+// change of rounding.  Why the split: on gfx950 the FP32 matrix instructions
+// run at 134 TFLOP/s (measured loop) and the bf16 ones at 2100, so six products
+// per real one still leave 350.  What bounds the tile then is the latency of
+// its operand loads, not the matrix cores.  Against the FP32 tile it replaced
+// (three real products, both operands in LDS): one interior layer of 100^3 with
+// 64 columns 1.75 -> 1.57 ms, a whole refined solve of 64 sources on 96^3 419
+// -> 362 ms.
 //
 // complex128: v_mfma_f64_16x16x4f64 on the real and imaginary parts, four
 // real products per complex one, in 144 to 165 registers at 64 columns where
@@ -143,10 +157,11 @@ template <int BN> struct TileSmem<double, BN> {
   double q[2][2][16][BN + 8];
 };
 
-// Accumulators of one wave: 16 rows x NB 16-column blocks (complex64 keeps
-// Pi Qi apart until finish()).
-template <typename T, int BM, int BN> struct TileAcc;
-template <int BM, int BN> struct TileAcc<float, BM, BN> {
+// Accumulators of one wave: 16 rows x NB 16-column blocks.  STEP (complex64):
+// every K step is summed from zero on the matrix cores and then added to the
+// rest; else the sums run through (complex64 keeps Pi Qi apart until finish()).
+template <typename T, int BM, int BN, bool STEP = false> struct TileAcc;
+template <int BM, int BN> struct TileAcc<float, BM, BN, false> {
   static constexpr int NB = TileShape<float, BM, BN>::NB;
   f4 re[NB], im[NB], ii[NB];
   __device__ __forceinline__ void zero() {
@@ -158,7 +173,16 @@ template <int BM, int BN> struct TileAcc<float, BM, BN> {
     for (int b = 0; b < NB; ++b) re[b] -= ii[b];
   }
 };
-template <int BM, int BN> struct TileAcc<double, BM, BN> {
+template <int BM, int BN> struct TileAcc<float, BM, BN, true> {
+  static constexpr int NB = TileShape<float, BM, BN>::NB;
+  f4 re[NB], im[NB];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) re[b] = im[b] = f4{0, 0, 0, 0};
+  }
+  __device__ __forceinline__ void finish() {}
+};
+template <int BM, int BN, bool STEP> struct TileAcc<double, BM, BN, STEP> {
   static constexpr int NB = TileShape<double, BM, BN>::NB;
   d4 re[NB], im[NB];
   __device__ __forceinline__ void zero() {
@@ -184,8 +208,8 @@ template <typename T, int BM, int BN> struct TileOut {
     for (int b = 0; b < NC; ++b) c[b] = ((wave % G::WC) * NC + b) * 16 + (lane & 15);
   }
 };
-template <typename T, int BM, int BN>
-__device__ __forceinline__ C_t<T> acc_at(const TileAcc<T, BM, BN>& acc, int i, int j) {
+template <typename T, int BM, int BN, bool STEP>
+__device__ __forceinline__ C_t<T> acc_at(const TileAcc<T, BM, BN, STEP>& acc, int i, int j) {
   C_t<T> z;
   z.x = acc.re[j][i];
   z.y = acc.im[j][i];
@@ -215,9 +239,9 @@ template <typename T> struct TileQ {
 
 // One K step of MFMAs of a wave on the lane's row values p (lane l: row
 // l % 16, k in the step's order) and the block's staged columns.
-template <int BM, int BN>
+template <int BM, int BN, bool STEP>
 __device__ __forceinline__ void tile_mfma(const TileSmem<float, BN>& sm, int buf,
-                                          TileAcc<float, BM, BN>& acc, const Split3<8>& ar,
+                                          TileAcc<float, BM, BN, STEP>& acc, const Split3<8>& ar,
                                           const Split3<8>& ai, int wc, int lane, int nbv) {
   constexpr int NB = TileShape<float, BM, BN>::NB;
   const int kg = lane >> 4;
@@ -231,19 +255,42 @@ __device__ __forceinline__ void tile_mfma(const TileSmem<float, BN>& sm, int buf
       bi[s] = sm.q[buf][3 + s][kg][(wc * NB + b) * 16 + (lane & 15)];
     }
     constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pc[6] = {0, 2, 1, 0, 1, 0};
+    if constexpr (STEP) {
+      // two chains at a time
+      f4 u = {0, 0, 0, 0}, v = u;
 #pragma unroll
-    for (int s = 0; s < 6; ++s) {
-      acc.re[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar.p[pa[s]], br[pc[s]], acc.re[b], 0, 0, 0);
-      acc.im[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar.p[pa[s]], bi[pc[s]], acc.im[b], 0, 0, 0);
-      acc.ii[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai.p[pa[s]], bi[pc[s]], acc.ii[b], 0, 0, 0);
-      acc.im[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai.p[pa[s]], br[pc[s]], acc.im[b], 0, 0, 0);
+      for (int s = 0; s < 6; ++s) {
+        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai.p[pa[s]], bi[pc[s]], u, 0, 0, 0);
+        v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai.p[pa[s]], br[pc[s]], v, 0, 0, 0);
+      }
+      acc.re[b] -= u;
+      acc.im[b] += v;
+      u = v = f4{0, 0, 0, 0};
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar.p[pa[s]], br[pc[s]], u, 0, 0, 0);
+        v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar.p[pa[s]], bi[pc[s]], v, 0, 0, 0);
+      }
+      acc.re[b] += u;
+      acc.im[b] += v;
+      // the sums are formed here: moved past the branch they keep every
+      // block's chains alive, which spills
+      asm("" : "+v"(acc.re[b]), "+v"(acc.im[b]));
+    } else {
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        acc.re[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar.p[pa[s]], br[pc[s]], acc.re[b], 0, 0, 0);
+        acc.im[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar.p[pa[s]], bi[pc[s]], acc.im[b], 0, 0, 0);
+        acc.ii[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai.p[pa[s]], bi[pc[s]], acc.ii[b], 0, 0, 0);
+        acc.im[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai.p[pa[s]], br[pc[s]], acc.im[b], 0, 0, 0);
+      }
     }
   }
 }
-template <int BM, int BN>
+template <int BM, int BN, bool STEP>
 __device__ __forceinline__ void tile_mfma(const TileSmem<double, BN>& sm, int buf,
-                                          TileAcc<double, BM, BN>& acc, const double2 (&p)[4],
-                                          int wc, int lane, int nbv) {
+                                          TileAcc<double, BM, BN, STEP>& acc,
+                                          const double2 (&p)[4], int wc, int lane, int nbv) {
   constexpr int NB = TileShape<double, BM, BN>::NB;
   const int kg = lane >> 4;
 #pragma unroll
@@ -267,8 +314,8 @@ __device__ __forceinline__ void tile_mfma(const TileSmem<double, BN>& sm, int bu
 // load the compiler merges their registers by copies right after the loads,
 // each waiting for its load, and nothing is ahead any more (a pruned layer
 // solve of 160^3, 32 columns: 1528 us with the branch, 1467 without).
-template <typename T, int BM, int BN, bool CONTIG, QMode QM>
-__device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN>& acc,
+template <typename T, int BM, int BN, bool CONTIG, QMode QM, bool STEP>
+__device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN, STEP>& acc,
                                           const TileP<T>& P, const TileQ<T>& Q, int r0, int c0,
                                           int kbeg, int kend) {
   using C = C_t<T>;
@@ -405,7 +452,7 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
       const Split3<8> ar = split3<8>(u, sel), ai = split3<8>(v, sel);
       ahead();
       __syncthreads();
-      tile_mfma<BM, BN>(sm, buf, acc, ar, ai, wc, lane, nbv);
+      tile_mfma(sm, buf, acc, ar, ai, wc, lane, nbv);
     } else {
 #pragma unroll
       for (int i = 0; i < KPT; ++i) {
@@ -417,7 +464,7 @@ __device__ __forceinline__ void tile_gemm(TileSmem<T, BN>& sm, TileAcc<T, BM, BN
       for (int i = 0; i < 4; ++i) a[i] = p[i];
       ahead();
       __syncthreads();
-      tile_mfma<BM, BN>(sm, buf, acc, a, wc, lane, nbv);
+      tile_mfma(sm, buf, acc, a, wc, lane, nbv);
     }
   };
   if (kbeg >= kend) return;   // an empty product
