@@ -140,7 +140,9 @@ typedef struct {
                               second solve (the estimate then rests on one
                               measured contraction) or at most half of it
                               from the third on (a factor 4 / 2 margin
-                              against the estimate; <= 0: off)              */
+                              against the estimate, here without the residual
+                              term of est_error_max, which has to be within
+                              err_target itself; <= 0: off)                 */
   size_t hbm_budget_bytes; /* 0 = 90% of free device memory                  */
   int    device;           /* HIP device ordinal                             */
   void*  stream;           /* hipStream_t for the *_dev entry points (NULL = default) */
@@ -179,7 +181,9 @@ typedef struct {
                                 (one after the second step) and of 4 times
                                 the relative residual the step's GMRES
                                 reached; 1 (unknown) after a single step or
-                                when q > 1/2                                 */
+                                when q > 1/2; no less than the same with q
+                                twice the contraction of the FP64 residual
+                                in the last step (at most 1/2)               */
   int    ir_gmres_iters[8];  /* GMRES iterations of each refinement step     */
   /* Per right-hand side: arrays of n_rhs entries owned by the caller, each
    * may be NULL; set them before the call (they survive the call's reset of

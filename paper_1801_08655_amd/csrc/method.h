@@ -125,18 +125,22 @@ struct Method {
 struct RefineTrack {
   double dprev = 0;   // |d| of the previous step
   double qprev = 0;   // contraction ratio measured at the previous step
+  double rprev = 1;   // relative FP64 residual before the step
   double est = 1;     // estimated error after the last step (1: unknown)
 };
 // Estimated relative error |u - H^-1 f| / |u| after a step whose correction
-// has norm dcur and whose GMRES ran to tolerance tol (see method.cpp);
-// updates the record.
-double refinement_error(int step, RefineTrack& tr, double dcur, double unorm, double tol);
+// has norm dcur, whose GMRES ran to tolerance tol and which left the relative
+// residual rel (see method.cpp); updates the record, whose est steers the
+// refinement (the value returned, and reported, is no smaller).
+double refinement_error(int step, RefineTrack& tr, double dcur, double unorm, double tol,
+                        double rel);
 // GMRES tolerance of a column's next step (0-based step index).
 double refinement_tol(int step, const RefineTrack& tr, const helm_options& o);
 // Whether a column may stop after step `step` (0-based): FP64 residual at
 // ir_tol, or estimated error at most a quarter of err_target after the
 // second solve (the estimate rests on one measured contraction) and at most
-// half of it from the third on.
-bool refinement_met(int step, double rel, double est, const helm_options& o);
+// half of it from the third on, the reported estimate within err_target.
+bool refinement_met(int step, double rel, const RefineTrack& tr, double reported,
+                    const helm_options& o);
 
 }  // namespace helm

@@ -131,7 +131,7 @@ void Server::run_lane(Lane& ln) {
         const double rel = nm.rel[s];
         const double teff = M.last_resid.size() > (size_t)s ? M.last_resid[s] : tol[s];
         const double est =
-            fp64 ? 0.0 : refinement_error(st, sl.track, nm.dn[s], nm.un[s], teff);
+            fp64 ? 0.0 : refinement_error(st, sl.track, nm.dn[s], nm.un[s], teff, rel);
         bool f;
         int status = HELM_OK;
         if (fp64) {
@@ -140,7 +140,7 @@ void Server::run_lane(Lane& ln) {
           if (H.G.L > 1 && !(M.last_resid.size() > (size_t)s && M.last_resid[s] <= H.opt.gmres_tol))
             status = HELM_ENOCONV;
         } else {
-          const bool ok = refinement_met(st, rel, est, H.opt);
+          const bool ok = refinement_met(st, rel, sl.track, est, H.opt);
           f = ok || sl.steps >= std::max(1, H.opt.ir_max_steps);
           if (!ok) status = HELM_ENOCONV;
         }
