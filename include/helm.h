@@ -379,7 +379,8 @@ int helm_layer_info(const helm_handle* h, int l, int* s, int* e, int* lo,
  * (the forward and backward substitutions over the layer's front tree).
  * r_dev, w_dev: device arrays of k local volumes, RHS-major, natural order
  * (i + nx*(j + ny*(z - lo))), complex double.  In HELM_MIXED the substitution
- * runs in complex64. */
+ * runs in complex64, on columns scaled by a power of two where their magnitude
+ * is below about 1e-18 or above 1e18 (as every mixed entry point's). */
 int helm_layer_solve_dev(helm_handle* h, int l, int k, const double* r_dev,
                          double* w_dev);
 

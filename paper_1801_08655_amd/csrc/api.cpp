@@ -436,13 +436,9 @@ int helm_layer_solve_dev(helm_handle* h, int l, int k, const double* r_dev, doub
     const LayerSet& S = H.layer_set({l});
     const double2* r = reinterpret_cast<const double2*>(r_dev);
     double2* w = reinterpret_cast<double2*>(w_dev);
-    if (H.prec == HELM_FP64) kern::launch_local_to_X<double>(H.layers_h[l], r, k, H.st);
-    else kern::launch_local_to_X<float>(H.layers_h[l], r, k, H.st);
-    H.solve_layers(S, k);
-    if (H.prec == HELM_FP64) kern::launch_X_to_local<double>(H.layers_h[l], w, k, H.st);
-    else kern::launch_X_to_local<float>(H.layers_h[l], w, k, H.st);
-    HELM_HIP(hipGetLastError());
-    HELM_HIP(hipStreamSynchronize(H.st));
+    auto run = [&](int n) { H.solve_layers(S, n); };
+    if (H.prec == HELM_FP64) H.local_solve<double>(H.layers_h[l], r, w, k, k, run);
+    else H.local_solve<float>(H.layers_h[l], r, w, k, k, run);
     return HELM_OK;
   });
 }
@@ -473,12 +469,37 @@ int helm_polarized_op_dev(helm_handle* h, int op, int k, const double* in_dev,
     Method& M = method_for(h, k);
     const double2* in = reinterpret_cast<const double2*>(in_dev);
     double2* out = reinterpret_cast<double2*>(out_dev);
+    // complex64: columns too small or too large for it go in scaled
+    const long long n_in = op >= 3 ? M.N * k : (op == 2 ? M.Vp : 2 * M.Vp);
+    const long long n_out = op == 2 ? M.Vp : 2 * M.Vp;
+    std::vector<double> sc;
+    DevMem scaled;
+    if (H.prec != HELM_FP64) {
+      std::vector<double> n2;
+      if (op >= 3) M.norms2(in, n2);
+      else M.pair_norms2(in, n_in, n2);
+      sc = Method::column_scales(n2);
+    }
+    if (!sc.empty()) {
+      scaled.alloc((size_t)n_in * sizeof(double2));
+      M.put_scales(sc);
+      if (op >= 3)
+        kern::launch_scale_volumes(scaled.as<double2>(), in, M.scale.as<double>(), M.N, k, H.st);
+      else
+        kern::launch_scale_cols(scaled.as<double2>(), in, M.scale.as<double>(), n_in / k, k, H.st);
+      in = scaled.as<double2>();
+    }
     switch (op) {
       case 0: M.apply_P(in, in + M.Vp, out, out + M.Vp); break;
       case 1: M.apply_A(in, out); break;
       case 2: M.apply_U(in, out); break;
       case 3: M.polarized_rhs(in, out, out + M.Vp); break;
       case 4: M.precondition_source(in, out, out + M.Vp); break;
+    }
+    if (!sc.empty()) {
+      for (double& v : sc) v = 1.0 / v;
+      M.put_scales(sc);
+      kern::launch_scale_cols(out, out, M.scale.as<double>(), n_out / k, k, H.st);
     }
     HELM_HIP(hipGetLastError());
     HELM_HIP(hipStreamSynchronize(H.st));

@@ -97,6 +97,7 @@ Handle::~Handle() {
   for (auto& p : pending) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
   for (auto e : ev_free) (void)hipEventDestroy(e);
   sets.clear();
+  if (range_h) (void)hipHostFree(range_h);
   if (cap_st) (void)hipStreamDestroy(cap_st);
   if (own_stream && st) (void)hipStreamDestroy(st);
 }
@@ -114,6 +115,7 @@ void Handle::init_device(const helm_options& o) {
   }
   prec = o.precision == HELM_FP64 ? HELM_FP64 : HELM_MIXED;
   elem = prec == HELM_FP64 ? 16 : 8;
+  if (prec != HELM_FP64) HELM_HIP(hipHostMalloc((void**)&range_h, 2 * sizeof(int)));
   set_profile(o.flags);
 }
 

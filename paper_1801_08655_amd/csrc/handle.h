@@ -1,6 +1,7 @@
 // The factorization handle: resident factors, plans and launch lists.
 #pragma once
 
+#include <algorithm>
 #include <map>
 #include <memory>
 #include <vector>
@@ -214,6 +215,45 @@ struct Handle {
   // multi-RHS solve of the layers in `set` on their X buffers (k columns)
   void solve_layers(const LayerSet& set, int k);
   template <typename T> void solve_layers_t(const LayerSet& set, int k);
+  // One layer's solves w = (H^l)^-1 r on FP64 local volumes, `cols` of the k
+  // columns at a time, view L, substitutions by run(columns); returns when
+  // they have ended.  In complex64 a column whose values are too small or too
+  // large for the substitutions' products (1e-18 and 1e18, see
+  // launch_column_scale) is solved again scaled by a power of two, found
+  // afterwards through range_h, so that other calls pay nothing for it.
+  template <typename T, class Run>
+  void local_solve(const LayerDev& L, const double2* r, double2* w, int k, int cols, Run&& run) {
+    constexpr bool c64 = sizeof(T) == 4;
+    // (the forward results' memory is free before and after the substitutions)
+    double* scale = static_cast<double*>(L.Wt);
+    auto each = [&](auto&& f) {
+      for (int c = 0; c < k; c += cols) f((long long)c * L.n_loc, std::min(cols, k - c));
+    };
+    auto solve = [&](bool scaled) {
+      each([&](long long at, int n) {
+        if (scaled) kern::launch_column_scale(r + at, L.n_loc, n, scale, range_h + 1, st);
+        kern::launch_local_to_X<T>(L, r + at, n, scaled ? scale : nullptr,
+                                   c64 && !scaled ? range_h : nullptr, st);
+        run(n);
+        if (scaled) kern::launch_column_scale(r + at, L.n_loc, n, scale, range_h + 1, st);
+        kern::launch_X_to_local<T>(L, w + at, n, scaled ? scale : nullptr, st);
+      });
+      HELM_HIP(hipGetLastError());
+      HELM_HIP(hipStreamSynchronize(st));
+    };
+    const long long n = (long long)L.n_loc * k;
+    const bool overlap = r < w + n && w < r + n;   // r is gone afterwards
+    if (c64) range_h[0] = range_h[1] = 0;
+    solve(c64 && overlap);
+    if (!c64 || overlap || !range_h[0]) return;
+    each([&](long long at, int m) {
+      kern::launch_column_scale(r + at, L.n_loc, m, scale, range_h + 1, st);
+    });
+    HELM_HIP(hipGetLastError());
+    HELM_HIP(hipStreamSynchronize(st));
+    if (range_h[1]) solve(true);
+  }
+  int* range_h = nullptr;   // host memory that local_solve's kernels write (complex64)
   template <typename T> void run_layers_t(const LayerSet& set, int k, const LayerDev* ld,
                                           void* scr, const TileChoice* tp, bool timing);
   // the single-layer sets, built with the factors (used without allocation

@@ -116,10 +116,15 @@ void launch_scatter_source(const LayerDev& L, const double2* f, int nx, int ny,
 template <typename T>
 void launch_gather_volume(const LayerDev& L, double2* u, int nx, int ny,
                           long long N, int k, hipStream_t st);
+// whole extended layer, natural order <-> ND order.  scale (may be null): a
+// power of two per column, multiplied on the way in and divided out on the way
+// out; odd (may be null): set to 1 when a value is nonzero and outside the
+// magnitudes that complex64 substitutions take as they are (host memory).
 template <typename T>
-void launch_local_to_X(const LayerDev& L, const double2* r, int k, hipStream_t st);
+void launch_local_to_X(const LayerDev& L, const double2* r, int k, const double* scale,
+                       int* odd, hipStream_t st);
 template <typename T>
-void launch_X_to_local(const LayerDev& L, double2* w, int k, hipStream_t st);
+void launch_X_to_local(const LayerDev& L, double2* w, int k, const double* scale, hipStream_t st);
 // Interface source sum c0 in0 + c1 in1 + c2 in2 of pair vectors (null
 // entries skipped).
 struct JumpTerms {
@@ -156,6 +161,14 @@ void launch_scatter_cols(double2* out, const double2* in, long long V, int k, in
                          const ColMap& slot, hipStream_t st);
 void launch_scale_cols(double2* y, const double2* x, const double* s, long long V,
                        int k, hipStream_t st);
+// the same for volumes (column c's N elements contiguous)
+void launch_scale_volumes(double2* y, const double2* x, const double* s, long long N, int k,
+                          hipStream_t st);
+// scale[c] = the power of two that takes column c's largest |Re|, |Im| to [1, 2),
+// or 1 when complex64 substitutions take it as it is (x: k columns of N
+// contiguous elements); scaled (host memory) is set to 1 when one is not 1
+void launch_column_scale(const double2* x, long long N, int k, double* scale, int* scaled,
+                         hipStream_t st);
 void launch_add(double2* y, const double2* x, const double2* z, long long n,
                 hipStream_t st);
 // y = z - y in place (elementwise)

@@ -124,21 +124,37 @@ k_gather_volume(LayerDev L, double2* __restrict__ u, int nx, int ny, long long N
     }
 }
 
+// Whether complex64 substitutions take a column of largest magnitude a as it
+// is.  A float of 2^-110 and more splits exactly into three bf16 numbers, and
+// the substitutions move values by the size of H^-1 (2^-10 at 36^3 on the unit
+// cube), so both ends keep well away from the format's.
+constexpr double kScaleLow = 0x1p-60, kScaleHigh = 0x1p60;
+
 // whole extended layer, natural order <-> ND order (inspection entry point)
 template <typename T>
-__global__ void k_local_to_X(LayerDev L, const double2* __restrict__ r, int k) {
+__global__ void k_local_to_X(LayerDev L, const double2* __restrict__ r, int k,
+                             const double* __restrict__ scale, int* odd) {
   using C = C_t<T>;
   C* X = reinterpret_cast<C*>(L.X);
   const long long total = (long long)L.n_loc * k;
+  bool out = false;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
        e += (long long)gridDim.x * blockDim.x) {
     const long long sp = e % L.n_loc;
     const int c = (int)(e / L.n_loc);
-    X[(long long)L.nat2nd[sp] * k + c] = from_d2<C>(r[e]);
+    double2 v = r[e];
+    if (sizeof(T) == 4) {
+      const double a = fmax(fabs(v.x), fabs(v.y));
+      out = out || (a > 0.0 && a < kScaleLow) || a > kScaleHigh;
+      if (scale) v = make_double2(v.x * scale[c], v.y * scale[c]);
+    }
+    X[(long long)L.nat2nd[sp] * k + c] = from_d2<C>(v);
   }
+  if (sizeof(T) == 4 && odd && out) *odd = 1;
 }
 template <typename T>
-__global__ void k_X_to_local(LayerDev L, double2* __restrict__ w, int k) {
+__global__ void k_X_to_local(LayerDev L, double2* __restrict__ w, int k,
+                             const double* __restrict__ scale) {
   using C = C_t<T>;
   const C* X = reinterpret_cast<const C*>(L.X);
   const long long total = (long long)L.n_loc * k;
@@ -146,8 +162,28 @@ __global__ void k_X_to_local(LayerDev L, double2* __restrict__ w, int k) {
        e += (long long)gridDim.x * blockDim.x) {
     const long long sp = e % L.n_loc;
     const int c = (int)(e / L.n_loc);
-    w[e] = to_d2(X[(long long)L.nat2nd[sp] * k + c]);
+    double2 v = to_d2(X[(long long)L.nat2nd[sp] * k + c]);
+    if (sizeof(T) == 4 && scale) v = make_double2(v.x / scale[c], v.y / scale[c]);
+    w[e] = v;
   }
+}
+// one block per column
+__global__ void __launch_bounds__(256)
+k_column_scale(const double2* __restrict__ x, long long N, double* __restrict__ scale,
+               int* scaled) {
+  const double2* col = x + (long long)blockIdx.x * N;
+  double m = 0.0;
+  for (long long i = threadIdx.x; i < N; i += 256) m = fmax(m, fmax(fabs(col[i].x), fabs(col[i].y)));
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+  __shared__ double wm[4];
+  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x) return;
+  m = fmax(fmax(wm[0], wm[1]), fmax(wm[2], wm[3]));
+  const bool keep = !(m > 0.0) || isinf(m) || (m >= kScaleLow && m <= kScaleHigh);
+  // (an inverse power of two stays a normal number)
+  scale[blockIdx.x] = keep ? 1.0 : ldexp(1.0, -max(ilogb(m), -1000));
+  if (!keep) *scaled = 1;
 }
 
 // Interface source of a pair (a, b) = c0 in0 + c1 in1 + c2 in2 (null entries
@@ -356,6 +392,18 @@ __global__ void k_scale_cols(double2* y, const double2* x, const double* __restr
   }
 }
 
+// volumes: column c's N elements contiguous, one grid row per column
+__global__ void k_scale_volumes(double2* y, const double2* x, const double* __restrict__ s,
+                                long long N) {
+  const double a = s[blockIdx.y];
+  const long long base = blockIdx.y * N;
+  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < N;
+       e += (long long)gridDim.x * blockDim.x) {
+    const double2 b = x[base + e];
+    y[base + e] = make_double2(a * b.x, a * b.y);
+  }
+}
+
 // the columns map.col[0..m) of an interleaved batch of k into a batch of w
 __global__ void k_gather_cols(double2* __restrict__ out, const double2* __restrict__ in,
                               long long V, int k, int w, int m, ColMap map) {
@@ -542,14 +590,16 @@ void launch_gather_volume(const LayerDev& L, double2* u, int nx, int ny,
   hipLaunchKernelGGL(k_gather_volume<T>, grid, dim3(256), 0, st, L, u, nx, ny, N, k);
 }
 template <typename T>
-void launch_local_to_X(const LayerDev& L, const double2* r, int k, hipStream_t st) {
+void launch_local_to_X(const LayerDev& L, const double2* r, int k, const double* scale,
+                       int* odd, hipStream_t st) {
   hipLaunchKernelGGL(k_local_to_X<T>, dim3(grid_for((long long)L.n_loc * k)), dim3(256),
-                     0, st, L, r, k);
+                     0, st, L, r, k, scale, odd);
 }
 template <typename T>
-void launch_X_to_local(const LayerDev& L, double2* w, int k, hipStream_t st) {
+void launch_X_to_local(const LayerDev& L, double2* w, int k, const double* scale,
+                       hipStream_t st) {
   hipLaunchKernelGGL(k_X_to_local<T>, dim3(grid_for((long long)L.n_loc * k)), dim3(256),
-                     0, st, L, w, k);
+                     0, st, L, w, k, scale);
 }
 template <typename T>
 void launch_jump(const LayerDev& L, const JumpTerms& t, const double2* B, int bottom, int nx,
@@ -605,6 +655,14 @@ void launch_scale_cols(double2* y, const double2* x, const double* s, long long 
   hipLaunchKernelGGL(k_scale_cols, dim3(grid_for(V * k)), dim3(256), 0, st, y, x, s, V,
                      k);
 }
+void launch_scale_volumes(double2* y, const double2* x, const double* s, long long N, int k,
+                          hipStream_t st) {
+  hipLaunchKernelGGL(k_scale_volumes, dim3(grid_for(N), k), dim3(256), 0, st, y, x, s, N);
+}
+void launch_column_scale(const double2* x, long long N, int k, double* scale, int* scaled,
+                         hipStream_t st) {
+  hipLaunchKernelGGL(k_column_scale, dim3(k), dim3(256), 0, st, x, N, scale, scaled);
+}
 void launch_add(double2* y, const double2* x, const double2* z, long long n,
                 hipStream_t st) {
   hipLaunchKernelGGL(k_add, dim3(grid_for(n)), dim3(256), 0, st, y, x, z, n);
@@ -644,8 +702,9 @@ void launch_volume_norm2(const double2* x, long long N, int k, double* partial,
   template void launch_gather_volume<T>(const LayerDev&, double2*, int, int,         \
                                         long long, int, hipStream_t);                \
   template void launch_local_to_X<T>(const LayerDev&, const double2*, int,           \
+                                     const double*, int*, hipStream_t);              \
+  template void launch_X_to_local<T>(const LayerDev&, double2*, int, const double*,  \
                                      hipStream_t);                                   \
-  template void launch_X_to_local<T>(const LayerDev&, double2*, int, hipStream_t);   \
   template void launch_jump<T>(const LayerDev&, const JumpTerms&, const double2*, int, \
                                int, int, int, hipStream_t);                          \
   template void launch_sources<T>(const LayerDev&, const JumpTerms&, const JumpTerms&, \

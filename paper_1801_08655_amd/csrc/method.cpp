@@ -804,42 +804,77 @@ int Method::polarized_solve(const double2* f, double2* u, const std::vector<doub
   return st;
 }
 
-// per-column l2 norms of k volumes
-void Method::norms(const double2* x, std::vector<double>& out) {
+// per-column squared l2 norms of k volumes
+void Method::norms2(const double2* x, std::vector<double>& out) {
   out.resize(k);
   kern::launch_volume_norm2(x, N, k, norm_partial.as<double>(), norm_out.as<double>(), H.st);
   HELM_HIP(hipMemcpyAsync(out.data(), norm_out.p, k * sizeof(double), hipMemcpyDeviceToHost,
                           H.st));
   HELM_HIP(hipStreamSynchronize(H.st));
+}
+void Method::pair_norms2(const double2* x, long long n, std::vector<double>& out) {
+  std::vector<double2> d(k);
+  dot(x, x, n / k, hcol.as<double2>());
+  HELM_HIP(hipMemcpyAsync(d.data(), hcol.p, k * sizeof(double2), hipMemcpyDeviceToHost, H.st));
+  HELM_HIP(hipStreamSynchronize(H.st));
+  out.resize(k);
+  for (int c = 0; c < k; ++c) out[c] = d[c].x;
+}
+void Method::norms(const double2* x, std::vector<double>& out) {
+  norms2(x, out);
   for (double& v : out) v = std::sqrt(v);
+}
+
+std::vector<double> Method::column_scales(const std::vector<double>& n2) {
+  // |column| within 2^-40 .. 2^60: its elements, and what a solve makes of
+  // them, stay in the range where the complex64 products are exact (2^-110 and
+  // more, see kernels_tile.h)
+  std::vector<double> s;
+  for (size_t c = 0; c < n2.size(); ++c) {
+    if (!(n2[c] > 0) || std::isinf(n2[c]) || (n2[c] >= 0x1p-80 && n2[c] <= 0x1p120)) continue;
+    s.resize(n2.size(), 1.0);
+    s[c] = std::ldexp(1.0, -std::ilogb(n2[c]) / 2);
+  }
+  return s;
+}
+void Method::put_scales(const std::vector<double>& s) {
+  HELM_HIP(hipMemcpyAsync(scale.p, s.data(), k * sizeof(double), hipMemcpyHostToDevice, H.st));
+  HELM_HIP(hipStreamSynchronize(H.st));
 }
 
 // per-column |f - H u| / |f| in FP64; r receives the residual
 void Method::residual(const double2* f, const double2* u, double2* r,
-                      std::vector<double>& rel) {
+                      const std::vector<double>& f2, std::vector<double>& rel,
+                      std::vector<double>& r2) {
   kern::launch_residual(H.grid, f, u, r, k, H.st);
-  std::vector<double> nr(k), nf(k);
-  kern::launch_volume_norm2(r, N, k, norm_partial.as<double>(), norm_out.as<double>(), H.st);
-  HELM_HIP(hipMemcpyAsync(nr.data(), norm_out.p, k * sizeof(double), hipMemcpyDeviceToHost, H.st));
-  HELM_HIP(hipStreamSynchronize(H.st));
-  kern::launch_volume_norm2(f, N, k, norm_partial.as<double>(), norm_out.as<double>(), H.st);
-  HELM_HIP(hipMemcpyAsync(nf.data(), norm_out.p, k * sizeof(double), hipMemcpyDeviceToHost, H.st));
-  HELM_HIP(hipStreamSynchronize(H.st));
+  norms2(r, r2);
   rel.resize(k);
-  for (int c = 0; c < k; ++c) rel[c] = nf[c] > 0 ? std::sqrt(nr[c] / nf[c]) : std::sqrt(nr[c]);
+  for (int c = 0; c < k; ++c) rel[c] = f2[c] > 0 ? std::sqrt(r2[c] / f2[c]) : std::sqrt(r2[c]);
 }
 
 // One refinement step on the k columns: D = (polarized solve of R) with a
 // tolerance per column, U += D, R = F - H U in FP64, and the per-column
 // relative residual |R|/|F| and norms |D|, |U|.  With U = 0 and R = F on
-// entry this is the first solve of the column; later steps correct U.
+// entry this is the first solve of the column; later steps correct U.  (In
+// mixed precision R may be left scaled until the new residual replaces it.)
 int Method::refine_step(const double2* F, double2* U, double2* R, double2* D,
                         const std::vector<double>& tol, StepNorms& out, helm_solve_info* info) {
   const int restart = gmres_restart(H.opt.gmres_max_iter);
+  std::vector<double> sc;
+  if (H.prec != HELM_FP64) sc = column_scales(out.r2);
+  if (!sc.empty()) {
+    put_scales(sc);
+    kern::launch_scale_volumes(R, R, scale.as<double>(), N, k, H.st);
+  }
   int s = polarized_solve(R, D, tol, H.opt.gmres_max_iter, restart, info);
+  if (!sc.empty()) {
+    for (double& v : sc) v = 1.0 / v;
+    put_scales(sc);
+    kern::launch_scale_volumes(D, D, scale.as<double>(), N, k, H.st);
+  }
   kern::launch_accumulate(U, D, N * k, H.st);
   double tr = now_ms();
-  residual(F, U, R, out.rel);
+  residual(F, U, R, out.f2, out.rel, out.r2);
   norms(D, out.dn);
   norms(U, out.un);
   if (info) info->t_residual_ms += now_ms() - tr;
@@ -892,7 +927,9 @@ int Method::solve(const double2* f, double2* u, helm_solve_info* info, int col0)
     if (col_iters.size() == (size_t)k) iters_c = col_iters;
     std::fill(steps_c.begin(), steps_c.end(), 1);
     double tr = now_ms();
-    residual(f, u, r, rel);
+    std::vector<double> f2, r2;
+    norms2(f, f2);
+    residual(f, u, r, f2, rel, r2);
     if (info) {
       info->ir_steps = std::max(info->ir_steps, 1);
       info->ir_width[0] = std::max(info->ir_width[0], k);
@@ -919,6 +956,9 @@ int Method::solve(const double2* f, double2* u, helm_solve_info* info, int col0)
     rel.assign(k, 0.0);
     const size_t col = (size_t)N * sizeof(double2);
     double emx_last = 0;
+    std::vector<double> f2, r2;   // |F|^2, |R|^2 per column
+    norms2(f, f2);
+    r2 = f2;
     for (int it = 0; it < std::max(1, o.ir_max_steps); ++it) {
       int it0 = info ? info->gmres_iters : 0;
       std::vector<int> todo;
@@ -954,6 +994,12 @@ int Method::solve(const double2* f, double2* u, helm_solve_info* info, int col0)
         std::vector<double> tol_w(w, 0.0);
         for (int j = 0; j < m; ++j) tol_w[j] = tol[todo[j]];
         StepNorms nw;
+        nw.f2.assign(w, 0.0);
+        nw.r2.assign(w, 0.0);
+        for (int j = 0; j < m; ++j) {
+          nw.f2[j] = f2[todo[j]];
+          nw.r2[j] = r2[todo[j]];
+        }
         S->refine_step(fc, uc, rc, S->vd.as<double2>(), tol_w, nw, info);
         nm.rel.assign(k, 0.0);
         nm.dn.assign(k, 0.0);
@@ -964,6 +1010,7 @@ int Method::solve(const double2* f, double2* u, helm_solve_info* info, int col0)
           HELM_HIP(hipMemcpyAsync(u + dst, uc + (size_t)j * N, col, hipMemcpyDeviceToDevice, H.st));
           HELM_HIP(hipMemcpyAsync(r + dst, rc + (size_t)j * N, col, hipMemcpyDeviceToDevice, H.st));
           nm.rel[c] = nw.rel[j];
+          r2[c] = nw.r2[j];
           nm.dn[c] = nw.dn[j];
           nm.un[c] = nw.un[j];
           teff[c] = S->last_resid.size() == (size_t)w ? S->last_resid[j] : tol[c];
@@ -973,8 +1020,14 @@ int Method::solve(const double2* f, double2* u, helm_solve_info* info, int col0)
         // the final columns get a zero residual: converged at once for the
         // Krylov solver, and a zero correction
         for (int c = 0; c < k; ++c)
-          if (met[c]) HELM_HIP(hipMemsetAsync(r + (size_t)c * N, 0, col, H.st));
+          if (met[c]) {
+            HELM_HIP(hipMemsetAsync(r + (size_t)c * N, 0, col, H.st));
+            r2[c] = 0.0;
+          }
+        nm.f2 = f2;
+        nm.r2 = r2;
         refine_step(f, u, r, vd.as<double2>(), tol, nm, info);
+        r2 = nm.r2;
         for (int c : todo) {
           teff[c] = last_resid.size() == (size_t)k ? last_resid[c] : tol[c];
           citer[c] = col_iters.size() == (size_t)k ? col_iters[c] : 0;

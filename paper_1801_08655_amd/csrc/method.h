@@ -109,14 +109,24 @@ struct Method {
                       int restart, helm_solve_info* info);
   int polarized_solve(const double2* f, double2* u, const std::vector<double>& tol,
                       int max_iter, int restart, helm_solve_info* info);
+  // Per column: |R|/|F| after the step, |D|, |U|; |F|^2 and |R|^2 are given
+  // (before the first step R = F) and |R|^2 is updated.
   struct StepNorms {
-    std::vector<double> rel, dn, un;
+    std::vector<double> rel, dn, un, f2, r2;
   };
   int refine_step(const double2* F, double2* U, double2* R, double2* D,
                   const std::vector<double>& tol, StepNorms& out, helm_solve_info* info);
   void ensure_volumes();
-  void residual(const double2* f, const double2* u, double2* r, std::vector<double>& rel);
+  void residual(const double2* f, const double2* u, double2* r, const std::vector<double>& f2,
+                std::vector<double>& rel, std::vector<double>& r2);
   void norms(const double2* x, std::vector<double>& out);
+  void norms2(const double2* x, std::vector<double>& out);   // squared
+  // the same of n elements with the columns fastest
+  void pair_norms2(const double2* x, long long n, std::vector<double>& out);
+  // Powers of two that take columns of squared norms n2 to about 1 where
+  // complex64 solves would not take them as they are; empty when all are.
+  static std::vector<double> column_scales(const std::vector<double>& n2);
+  void put_scales(const std::vector<double>& s);   // to `scale`
   int solve(const double2* f, double2* u, helm_solve_info* info, int col0 = 0);
   int gmres_restart(int max_iter) const;
 };

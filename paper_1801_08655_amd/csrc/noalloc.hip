@@ -98,13 +98,8 @@ void solve_noalloc(Handle& H, int l, int k, const double2* r, double2* w, unsign
   p += bytes(u1, cols);
   void* splitk = p;
   hipLaunchKernelGGL(k_put_layer, dim3(1), dim3(64), 0, H.st, tab + l, v);
-  for (int c = 0; c < k; c += cols) {
-    const int n = std::min(cols, k - c);
-    const long long at = (long long)c * P.n_loc;
-    kern::launch_local_to_X<T>(v, r + at, n, H.st);
-    H.run_layers_t<T>(S, n, tab, splitk, nullptr, false);
-    kern::launch_X_to_local<T>(v, w + at, n, H.st);
-  }
+  H.local_solve<T>(v, r, w, k, cols,
+                   [&](int n) { H.run_layers_t<T>(S, n, tab, splitk, nullptr, false); });
 }
 
 }  // namespace
@@ -127,8 +122,6 @@ extern "C" int helm_layer_solve_noalloc_dev(helm_handle* h, int l, int k, const 
     double2* w = reinterpret_cast<double2*>(w_dev);
     if (H.prec == HELM_FP64) solve_noalloc<double>(H, l, k, r, w, base);
     else solve_noalloc<float>(H, l, k, r, w, base);
-    HELM_HIP(hipGetLastError());
-    HELM_HIP(hipStreamSynchronize(H.st));
     return HELM_OK;
   });
 }

@@ -83,7 +83,7 @@ void Server::run_lane(Lane& ln) {
       for (int s = ln.occupied(); s < ln.K && !ln.queue.empty(); ++s) {
         Request* r = ln.queue.front();
         const int c = r->next_col++;
-        ln.slots[s] = Slot{r, c, 0, RefineTrack{}};
+        ln.slots[s] = Slot{r, c, 0, RefineTrack{}, 0, 0};
         if (r->info.t_first_ms < 0) r->info.t_first_ms = wall_ms() - t0;
         ln.node_h[s] = r->nodes[c];
         ln.amp_h[s] = r->amps[c];
@@ -123,11 +123,23 @@ void Server::run_lane(Lane& ln) {
       for (int s = 0; s < w; ++s)
         tol[s] = fp64 ? H.opt.gmres_tol
                       : refinement_tol(ln.slots[s].steps, ln.slots[s].track, H.opt);
+      if (!fresh.empty()) {
+        std::vector<double> f2;
+        M.norms2(F, f2);
+        for (int s : fresh) ln.slots[s].f2 = ln.slots[s].r2 = f2[s];
+      }
+      nm.f2.assign(w, 0.0);
+      nm.r2.assign(w, 0.0);
+      for (int s = 0; s < occ; ++s) {
+        nm.f2[s] = ln.slots[s].f2;
+        nm.r2[s] = ln.slots[s].r2;
+      }
       M.refine_step(F, U, R, ln.D.as<double2>(), tol, nm, nullptr);
       std::vector<char> fin(ln.K, 0);
       for (int s = 0; s < occ; ++s) {
         Slot& sl = ln.slots[s];
         const int st = sl.steps++;
+        sl.r2 = nm.r2[s];
         const double rel = nm.rel[s];
         const double teff = M.last_resid.size() > (size_t)s ? M.last_resid[s] : tol[s];
         const double est =

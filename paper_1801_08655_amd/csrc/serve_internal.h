@@ -33,6 +33,7 @@ struct Slot {
   int col = -1;
   int steps = 0;
   RefineTrack track;
+  double f2 = 0, r2 = 0;   // |F|^2, |R|^2
 };
 
 struct Lane {
