@@ -335,9 +335,9 @@ def serve_bench(args, torch, pt):
 
 def depth_rates_bench(args, torch, pt):
     """Per-depth rates of the substitution GEMMs in one interior layer's
-    local solve of R columns: the first solve of the layer measures every
-    tile width of each depth's launches (HELM_FLAG_AUTOTUNE, start and stop
-    events recorded by each launch); the kept width's time against the
+    local solve of R columns: the first solve of the layer measures each
+    depth's pass (its gather and reduction launches included) with every tile
+    width (HELM_FLAG_AUTOTUNE); the kept width's time against the
     depth's algorithmic flops (8 real flops per complex multiply-add:
     sum (s + b) s forward, sum b s backward, times R)."""
     from helm_inputs import workload

@@ -290,7 +290,8 @@ int helm_kernel_stats(helm_handle* h, helm_kernel_stat* out, int max, int* count
  * tile kinds in use: 16, 32 or 64 for MFMA tiles of that many columns, 1
  * for the vector path (default and a candidate up to 4 columns); when
  * the choice was measured (HELM_FLAG_AUTOTUNE), t_fwd_us / t_bwd_us hold the
- * timed launch of each kind in the order 1, 16, 32, 64 (0 where a kind was
+ * time of the whole pass at that depth (gather and reduction launches
+ * included) with each kind in the order 1, 16, 32, 64 (0 where a kind was
  * not tried).  Writes up to `max` records and the total to *count. */
 typedef struct {
   int    set_layers, k, depth, fronts;

@@ -858,23 +858,64 @@ bool Handle::gathers(const DepthList& D, int k) const {
   return D.tS > 0 && D.gather_rows * k * (double)elem <= 16e6;
 }
 
-// One depth's forward / backward GEMM launch with column width bn (1: the
-// vector path).
+// One depth's forward pass with column width bn (1: the vector path): the
+// gather and the split-K reduction where the width takes them, the GEMM.
+// Timing events only when `timing` is set and the profiling flags ask for them.
 template <typename T>
-void Handle::launch_fwd(const DepthList& D, const LayerDev* ld, int k, void* scr, int bn,
-                        hipEvent_t t0, hipEvent_t t1) {
+void Handle::forward_depth(const DepthList& D, const LayerDev* ld, int k, void* scr, int bn,
+                           bool timing) {
+  const double e = (double)elem, kk = (double)k;
+  hipEvent_t a = nullptr, t0 = nullptr, t1 = nullptr;
+  const bool gather = bn != 1 && gathers(D, k);
+  if (bn != 1 && D.tS > 0 && !gather) {
+    if (timing) a = prof_begin(K_FWD_GATHER);
+    kern::launch_fwd_gather<T>(D.fwd, D.pS, D.tS, ld, k, st);
+    if (timing) prof_end(K_FWD_GATHER, a, 0, 3.0 * D.fs_s * kk * e);
+  }
+  // timed by the launch itself: its start and stop, no event commands
+  // between it and its neighbours
+  if (timing && timed(K_FWD_GEMM)) {
+    t0 = take_event();
+    t1 = take_event();
+  }
   if (bn == 1)
     kern::launch_fwd_gemv<T>(D.fwd, D.vF, D.tVF, ld, k, D.vec_rows, st, t0, t1);
   else
-    kern::launch_fwd_gemm<T>(D.fwd, D.pF, D.tF, ld, k, scr, bn, gathers(D, k), st, t0, t1);
+    kern::launch_fwd_gemm<T>(D.fwd, D.pF, D.tF, ld, k, scr, bn, gather, st, t0, t1);
+  // factor block read once; pivots read, Z written, boundary updates
+  // written and the children's updates of the boundary rows read
+  if (t0)
+    pending.push_back(PendingEvent{K_FWD_GEMM, t0, t1, 8.0 * D.fl_sbs * kk,
+                                   D.fl_sbs * e + (2.0 * D.fl_s + D.fl_b + D.fs_b) * kk * e});
+  if (bn != 1 && D.tRF > 0) {
+    if (timing) a = prof_begin(K_FWD_REDUCE);
+    kern::launch_fwd_reduce<T>(D.fwd, D.rF, D.tRF, ld, k, scr, st);
+    if (timing) prof_end(K_FWD_REDUCE, a, 0, 0);
+  }
 }
+// The same for the backward pass.
 template <typename T>
-void Handle::launch_bwd(const DepthList& D, const LayerDev* ld, int k, void* scr, int bn,
-                        hipEvent_t t0, hipEvent_t t1) {
+void Handle::backward_depth(const DepthList& D, const LayerDev* ld, int k, void* scr, int bn,
+                            bool timing) {
+  const double e = (double)elem, kk = (double)k;
+  hipEvent_t t0 = nullptr, t1 = nullptr;
+  if (timing && timed(K_BWD_GEMM)) {
+    t0 = take_event();
+    t1 = take_event();
+  }
   if (bn == 1)
     kern::launch_bwd_gemv<T>(D.bwd, D.vB, D.tVB, ld, k, D.vec_rpg, st, t0, t1);
   else
     kern::launch_bwd_gemm<T>(D.bwd, D.pB, D.tB, ld, k, scr, D.bwd_bm, bn, st, t0, t1);
+  // factor block read once; X(B) rows read, Z(S) read, X(S) written
+  if (t0)
+    pending.push_back(PendingEvent{K_BWD_GEMM, t0, t1, 8.0 * D.sum_bs * kk,
+                                   D.sum_bs * e + (D.sum_b + 2.0 * D.sum_s) * kk * e});
+  if (bn != 1 && D.tRB > 0) {
+    hipEvent_t a = timing ? prof_begin(K_BWD_REDUCE) : nullptr;
+    kern::launch_bwd_reduce<T>(D.bwd, D.rB, D.tRB, ld, k, scr, st);
+    if (timing) prof_end(K_BWD_REDUCE, a, 0, 0);
+  }
 }
 
 const std::vector<Handle::TileChoice>& Handle::tile_plan(const LayerSet& set, int k) {
@@ -890,9 +931,10 @@ const std::vector<Handle::TileChoice>& Handle::tile_plan(const LayerSet& set, in
   return tiles.emplace(key, std::move(plan)).first->second;
 }
 
-// Measured tile choice: every depth's forward and backward GEMM launched
-// alone with each admissible width (a width is tried when it is the default
-// or narrower than it), best of three launches each, on the solve workspace.
+// Measured tile choice: every depth's forward and backward pass, all of the
+// launches that a solve makes for it, alone with each admissible width (a width
+// is tried when it is the default or narrower than it), best of three each, on
+// the solve workspace.
 // The right-hand sides already in X are saved and restored around it; the
 // other buffers the launches write are rewritten by every solve before they
 // are read.
@@ -929,9 +971,15 @@ void Handle::autotune_t(const LayerSet& set, int k, std::vector<TileChoice>& pla
     const DepthList& D = *set.depth[d];
     TileChoice& c = plan[d];
     c.tuned = true;
-    if (D.n == 0) continue;
-    auto q = [](double v) { return (long long)std::lround(4.0 * std::log2(1.0 + v)); };
-    const std::vector<long long> bucket{k, D.n, q(D.sum_s / D.n), q(D.sum_b / D.n), D.bwd_bm};
+    if (D.n == 0 && D.nL == 0) continue;
+    auto q = [](double sum, int n) {
+      return n ? (long long)std::lround(4.0 * std::log2(1.0 + sum / n)) : 0LL;
+    };
+    // the fronts of each pass and whatever else decides its launches
+    const std::vector<long long> bucket{
+        k, D.n, q(D.sum_s, D.n), q(D.sum_b, D.n), D.bwd_bm, D.vec_rpg, D.tRB > 0,
+        D.nL, q(D.fl_s, D.nL), q(D.fl_b, D.nL), q(D.fs_s, D.nL), D.vec_rows, D.tRF > 0,
+        D.tS > 0, gathers(D, k)};
     auto hit = tuned.find(bucket);
     if (hit != tuned.end()) {
       c = hit->second;
@@ -942,16 +990,12 @@ void Handle::autotune_t(const LayerSet& set, int k, std::vector<TileChoice>& pla
       const int bn = widths[w];
       if (bn > widest || (bn == 1 && k > 4)) continue;
       if (D.nL > 0) {
-        double t = time_us([&] {
-          launch_fwd<T>(D, ld, k, scr, bn);
-        });
+        double t = time_us([&] { forward_depth<T>(D, ld, k, scr, bn, false); });
         c.t_fwd[w] = t;
         if (t < bf) { bf = t; c.fwd_bn = bn; }
       }
-      if (D.bwd_bm == 32 && bn == 16) continue;   // not a distinct tile
-      double t = time_us([&] {
-        launch_bwd<T>(D, ld, k, scr, bn);
-      });
+      if (D.n == 0 || (D.bwd_bm == 32 && bn == 16)) continue;   // (not a distinct tile)
+      double t = time_us([&] { backward_depth<T>(D, ld, k, scr, bn, false); });
       c.t_bwd[w] = t;
       if (t < bb) { bb = t; c.bwd_bn = bn; }
     }
@@ -982,60 +1026,14 @@ void Handle::solve_layers_t(const LayerSet& set, int k) {
 template <typename T>
 void Handle::run_layers_t(const LayerSet& set, int k, const LayerDev* ld, void* scr,
                           const TileChoice* tp, bool timing) {
-  auto prof_begin = [&](int cls) { return timing ? this->prof_begin(cls) : nullptr; };
-  const double e = (double)elem, kk = (double)k;
   const int wdef = width_bn(k);
-  auto fwd_bn = [&](int d) { return tp ? tp[d].fwd_bn : wdef; };
-  auto bwd_bn = [&](int d) { return tp ? tp[d].bwd_bn : wdef; };
   for (int d = set.max_depth; d >= 0; --d) {
-    const DepthList& D = *set.depth[d];
-    if (D.nL == 0) continue;   // (a pruned set may run a front forward only)
-    const int bn = fwd_bn(d);
-    hipEvent_t a = nullptr;
-    if (bn != 1 && D.tS > 0 && !gathers(D, k)) {
-      a = prof_begin(K_FWD_GATHER);
-      kern::launch_fwd_gather<T>(D.fwd, D.pS, D.tS, ld, k, st);
-      prof_end(K_FWD_GATHER, a, 0, 3.0 * D.fs_s * kk * e);
-    }
-    // timed by the launch itself: its start and stop, no event commands
-    // between it and its neighbours
-    hipEvent_t t0 = nullptr, t1 = nullptr;
-    if (timing && timed(K_FWD_GEMM)) {
-      t0 = take_event();
-      t1 = take_event();
-    }
-    launch_fwd<T>(D, ld, k, scr, bn, t0, t1);
-    // factor block read once; pivots read, Z written, boundary updates
-    // written and the children's updates of the boundary rows read
-    if (t0)
-      pending.push_back(PendingEvent{K_FWD_GEMM, t0, t1, 8.0 * D.fl_sbs * kk,
-                                     D.fl_sbs * e + (2.0 * D.fl_s + D.fl_b + D.fs_b) * kk * e});
-    if (bn != 1 && D.tRF > 0) {
-      a = prof_begin(K_FWD_REDUCE);
-      kern::launch_fwd_reduce<T>(D.fwd, D.rF, D.tRF, ld, k, scr, st);
-      prof_end(K_FWD_REDUCE, a, 0, 0);
-    }
+    const DepthList& D = *set.depth[d];   // (a pruned set may run a front forward only)
+    if (D.nL > 0) forward_depth<T>(D, ld, k, scr, tp ? tp[d].fwd_bn : wdef, timing);
   }
   for (int d = 0; d <= set.max_depth; ++d) {
     const DepthList& D = *set.depth[d];
-    if (D.n == 0) continue;
-    const int bn = bwd_bn(d);
-    // timed by the launch itself, as the forward GEMM
-    hipEvent_t t0 = nullptr, t1 = nullptr;
-    if (timing && timed(K_BWD_GEMM)) {
-      t0 = take_event();
-      t1 = take_event();
-    }
-    launch_bwd<T>(D, ld, k, scr, bn, t0, t1);
-    // factor block read once; X(B) rows read, Z(S) read, X(S) written
-    if (t0)
-      pending.push_back(PendingEvent{K_BWD_GEMM, t0, t1, 8.0 * D.sum_bs * kk,
-                                     D.sum_bs * e + (D.sum_b + 2.0 * D.sum_s) * kk * e});
-    if (bn != 1 && D.tRB > 0) {
-      hipEvent_t a = prof_begin(K_BWD_REDUCE);
-      kern::launch_bwd_reduce<T>(D.bwd, D.rB, D.tRB, ld, k, scr, st);
-      prof_end(K_BWD_REDUCE, a, 0, 0);
-    }
+    if (D.n > 0) backward_depth<T>(D, ld, k, scr, tp ? tp[d].bwd_bn : wdef, timing);
   }
 }
 

@@ -151,19 +151,18 @@ struct Handle {
     double t_fwd[4] = {0, 0, 0, 0}, t_bwd[4] = {0, 0, 0, 0};   // us per width 1/16/32/64
   };
   std::map<GraphKey, std::vector<TileChoice>> tiles;
-  // measured choices shared by every depth list of the same front-size
-  // bucket: (k, fronts, log2 mean s and mean b in quarter steps, bwd row tile)
+  // measured choices shared by every depth list of the same bucket: k, the
+  // fronts of each pass (count, log2 mean s and mean b in quarter steps) and
+  // what else decides its launches (see autotune_t)
   std::map<std::vector<long long>, TileChoice> tuned;
   const std::vector<TileChoice>& tile_plan(const LayerSet& set, int k);
   template <typename T> void autotune_t(const LayerSet& set, int k,
                                         std::vector<TileChoice>& plan);
   bool gathers(const DepthList& D, int k) const;
-  template <typename T> void launch_fwd(const DepthList& D, const LayerDev* ld, int k,
-                                        void* scr, int bn, hipEvent_t t0 = nullptr,
-                                        hipEvent_t t1 = nullptr);
-  template <typename T> void launch_bwd(const DepthList& D, const LayerDev* ld, int k,
-                                        void* scr, int bn, hipEvent_t t0 = nullptr,
-                                        hipEvent_t t1 = nullptr);
+  template <typename T> void forward_depth(const DepthList& D, const LayerDev* ld, int k,
+                                           void* scr, int bn, bool timing);
+  template <typename T> void backward_depth(const DepthList& D, const LayerDev* ld, int k,
+                                            void* scr, int bn, bool timing);
 
   // kernel timing (HELM_FLAG_PROFILE: every class; HELM_FLAG_PROFILE_FWD:
   // the forward substitution GEMM only), one bit per KClass
