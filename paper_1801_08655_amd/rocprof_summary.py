@@ -28,7 +28,10 @@ import re
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ["csrc/kernels_solve.hip", "csrc/kernels_common.h", "csrc/kernels.h"]
+# the substitution kernels: their file and every header it takes in, also through
+# others (helm.h, the public interface, holds nothing they are built from)
+KERNEL_SOURCES = ["csrc/kernels_solve.hip", "csrc/kernels_tile.h", "csrc/kernels_common.h",
+                  "csrc/kernels.h", "csrc/helm_internal.h"]
 
 
 def kernel_sources_hash() -> str:
