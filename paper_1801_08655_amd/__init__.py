@@ -210,7 +210,8 @@ class Solver:
               "helm_set_solve_options")
 
     def factor_info(self):
-        """Offline-stage record: LU and executed flops, pivot range and growth."""
+        """Offline-stage record: flops (LU; Gauss-Jordan sweep of whole fronts),
+        pivot range and growth."""
         fi = _lib.helm_factor_info()
         check(lib().helm_get_factor_info(self._h, ctypes.byref(fi)), "helm_get_factor_info")
         d = fi.as_dict()

@@ -493,7 +493,9 @@ void Handle::factorize_t() {
             // the LU's trailing update of this step (its share of the
             // algorithmic count 4 (2/3 s^3 + 2 s^2 b + 2 s b^2))
             sw_flops += 8.0 * (n - k - nbf) * (n - k - nbf) * nbf;
-            sw_bytes += (2.0 * n * n + 2.0 * n * nbf) * elem;
+            // the updated entries read and written, the pivot rows and columns read
+            const FrontDev& F = fronts_h[v[a]];
+            sw_bytes += (2.0 * sweep_step_elems(F.s, F.b, k, nb) + 2.0 * n * nbf) * elem;
           }
         hipEvent_t e1 = prof_begin(K_PANEL);
         kern::launch_panel<T>(fr, ids, n_act, smax - k, k, nb, ws0.p, ws1.p, panel.p,

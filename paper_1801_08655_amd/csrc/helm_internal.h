@@ -169,6 +169,10 @@ constexpr int kPivotBlock = 64;
 // with the inverted pivot block.  (The symmetric boundary block counts in
 // full; its tiles above the diagonal are not executed.)
 double gj_front_flops(int s, int b, int nb);
+// Entries of a front that the rank-nb update of one block step (pivots k and
+// on) reads and writes: the tiles that k_sweep_gemm does not skip, those above
+// the diagonal of the boundary block left out.
+double sweep_step_elems(int s, int b, int k, int nb);
 
 struct Geometry {
   int nx = 0, ny = 0, nz = 0;

@@ -131,6 +131,22 @@ double gj_front_flops(int s, int b, int nb) {
   return fl;
 }
 
+double sweep_step_elems(int s, int b, int k, int nb) {
+  const int n = s + b, T = 64, nt = (n + T - 1) / T, nbf = std::min(nb, s - k);
+  double el = 0;
+  for (int ti = 0; ti < nt; ++ti) {
+    const int i0 = ti * T, ri = std::min(T, n - i0);
+    for (int tj = 0; tj < nt; ++tj) {
+      const int j0 = tj * T, cj = std::min(T, n - j0);
+      if ((i0 >= k && i0 + T <= k + nbf) || (j0 >= k && j0 + T <= k + nbf) ||
+          (i0 + T <= k && j0 >= s) || (i0 >= s && j0 >= i0 + T))
+        continue;
+      el += (double)ri * cj;
+    }
+  }
+  return el;
+}
+
 void build_layer_plan(LayerPlan& P, int nx, int ny, int leaf) {
   const int t = P.t;
   P.n_loc = nx * ny * t;
