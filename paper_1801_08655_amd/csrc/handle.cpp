@@ -558,18 +558,25 @@ void Handle::ensure_workspace(int k) {
   HELM_HIP(hipStreamSynchronize(st));
   clear_graphs();
   const int L = G.L;
-  X.clear(); Wt.clear(); Ub0.clear(); Ub1.clear();
+  // one allocation for every layer's buffers: their 4 L separate ones were most
+  // of the first solve's time on a new handle (100^3, 64 columns, complex128:
+  // 4.3 ms of which 1.9 the solve's)
+  std::vector<std::pair<void**, size_t>> at;
+  size_t bytes = 0;
+  auto add = [&](void*& slot, long long rows) {
+    at.emplace_back(&slot, bytes);
+    bytes += ((size_t)std::max<long long>(rows, 1) * k * elem + 255) & ~(size_t)255;
+  };
   for (int l = 0; l < L; ++l) {
     const LayerPlan& P = G.layers[l];
-    X.emplace_back(new DevMem); X.back()->alloc((size_t)P.n_loc * k * elem);
-    Wt.emplace_back(new DevMem); Wt.back()->alloc((size_t)P.n_loc * k * elem);
-    Ub0.emplace_back(new DevMem); Ub0.back()->alloc(std::max<size_t>(P.ub_rows[0], 1) * k * elem);
-    Ub1.emplace_back(new DevMem); Ub1.back()->alloc(std::max<size_t>(P.ub_rows[1], 1) * k * elem);
-    layers_h[l].X = X[l]->p;
-    layers_h[l].Wt = Wt[l]->p;
-    layers_h[l].Ub[0] = Ub0[l]->p;
-    layers_h[l].Ub[1] = Ub1[l]->p;
+    add(layers_h[l].X, P.n_loc);
+    add(layers_h[l].Wt, P.n_loc);
+    add(layers_h[l].Ub[0], P.ub_rows[0]);
+    add(layers_h[l].Ub[1], P.ub_rows[1]);
   }
+  kcap = 0;
+  work.alloc(bytes);
+  for (auto& a : at) *a.first = static_cast<char*>(work.p) + a.second;
   kcap = k;
   upload_layers();
 }
@@ -789,7 +796,10 @@ std::unique_ptr<LayerSet> Handle::make_set(const std::vector<int>& layers, const
 double Handle::solve_elems(const LayerSet& set) const { return set.elems; }
 
 void Handle::solve_layers(const LayerSet& set, int k) {
-  size_t need = (size_t)std::max<long long>(set.scratch_rows, 1) * std::max(k, kcap) * elem;
+  // (up to 4 columns take the vector path, which splits nothing)
+  const bool splits = k > 4 || (opt.flags & HELM_FLAG_AUTOTUNE);
+  const size_t need =
+      splits ? (size_t)std::max<long long>(set.scratch_rows, 1) * std::max(k, kcap) * elem : 0;
   if (scratch.bytes < need) {
     HELM_HIP(hipStreamSynchronize(st));
     clear_graphs();
@@ -952,7 +962,7 @@ void Handle::autotune_t(const LayerSet& set, int k, std::vector<TileChoice>& pla
     size_t off = 0;
     for (int l : set.layers) {
       const size_t b = (size_t)G.layers[l].n_loc * k * elem;
-      HELM_HIP(hipMemcpyAsync((char*)save.p + off, X[l]->p, b, hipMemcpyDeviceToDevice, st));
+      HELM_HIP(hipMemcpyAsync((char*)save.p + off, layers_h[l].X, b, hipMemcpyDeviceToDevice, st));
       off += b;
     }
   }
@@ -1008,7 +1018,7 @@ void Handle::autotune_t(const LayerSet& set, int k, std::vector<TileChoice>& pla
     size_t off = 0;
     for (int l : set.layers) {
       const size_t b = (size_t)G.layers[l].n_loc * k * elem;
-      HELM_HIP(hipMemcpyAsync(X[l]->p, (char*)save.p + off, b, hipMemcpyDeviceToDevice, st));
+      HELM_HIP(hipMemcpyAsync(layers_h[l].X, (char*)save.p + off, b, hipMemcpyDeviceToDevice, st));
       off += b;
     }
   }
