@@ -392,7 +392,8 @@ int helm_layer_solve_dev(helm_handle* h, int l, int k, const double* r_dev,
  * the solve vector, the forward results, the update buffers and the split-K
  * partial products of layer l for k columns, plus the kernels' layer table --
  * lives in a static device array of HELM_NOALLOC_SCRATCH_BYTES per GPU (held
- * until the process ends) instead of the handle's allocations; it calls no
+ * until the process ends), the partial products near the array's limit in
+ * w_dev before the result, instead of the handle's allocations; it calls no
  * hipMalloc, hipFree or other allocating routine and never replays a graph.
  * Errors: HELM_EINVAL for bad arguments, HELM_ENOMEM (nothing launched) when
  * the workspace of k columns of this layer exceeds the array.  Every call on

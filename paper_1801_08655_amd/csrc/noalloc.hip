@@ -8,11 +8,13 @@
 //     solved layer's entry is written),
 //   - X (the solve vector, n_loc x k), Z (the forward results, n_loc x k),
 //   - the two depth-parity update buffers (ub_rows[0] x k, ub_rows[1] x k),
-//   - the split-K partial products (scratch_rows x k),
-// in the precision of the factors, k being the columns of one pass.  Every byte that the kernels read is
-// written earlier in the same call (X by the copy-in, Z and the update
-// buffers by the forward pass, the partials by the GEMM chunks), so nothing
-// has to start at zero and the previous call's contents never matter.
+//   - the split-K partial products (scratch_rows x k), or these in the caller's
+//     output,
+// in the precision of the factors, k being the columns of one pass.  Every byte
+// that the kernels read is written earlier in the same call (X by the copy-in,
+// Z and the update buffers by the forward pass, the partials by the GEMM
+// chunks), so nothing has to start at zero and the previous call's contents
+// never matter.
 #include <algorithm>
 #include <mutex>
 
@@ -78,11 +80,18 @@ void solve_noalloc(Handle& H, int l, int k, const double2* r, double2* w, unsign
                "local solve needs " + std::to_string(asked) +
                    " bytes of workspace, more than the static scratch of " + std::to_string(cap) +
                    " bytes (use fewer columns or helm_layer_solve_dev)");
-  // The launches' own partials can take more than the limit counts: then the
-  // columns go in passes of equal width.  Up to 4 columns (the vector kernels)
-  // have no partials, so a pass always fits.
+  // The launches' own partials can take more than the limit counts.  Then they
+  // go into the caller's result, which is written last (complex128, 68 x 68 x
+  // 30, 16 columns: 897 us, in two passes of 8 columns 1570); where they
+  // cannot (it is also the right-hand side), the columns go in passes of equal
+  // width.  Up to 4 columns (the vector kernels) have no partials, so a pass
+  // always fits.
+  const long long n = (long long)P.n_loc * k;
+  const bool apart = r + n <= w || w + n <= r;
   int cols = k;
   while (cols > 4 && need((size_t)cols, S.scratch_rows) > cap) --cols;
+  const bool in_w = cols < k && apart && (size_t)S.scratch_rows * e <= P.n_loc * sizeof(double2);
+  if (in_w) cols = k;
   const int passes = (k + cols - 1) / cols;
   cols = (k + passes - 1) / passes;
   LayerDev* tab = reinterpret_cast<LayerDev*>(base);
@@ -96,7 +105,7 @@ void solve_noalloc(Handle& H, int l, int k, const double2* r, double2* w, unsign
   p += bytes(u0, cols);
   v.Ub[1] = p;
   p += bytes(u1, cols);
-  void* splitk = p;
+  void* splitk = in_w ? static_cast<void*>(w) : p;
   hipLaunchKernelGGL(k_put_layer, dim3(1), dim3(64), 0, H.st, tab + l, v);
   H.local_solve<T>(v, r, w, k, cols,
                    [&](int n) { H.run_layers_t<T>(S, n, tab, splitk, nullptr, false); });
