@@ -469,37 +469,52 @@ int helm_polarized_op_dev(helm_handle* h, int op, int k, const double* in_dev,
     Method& M = method_for(h, k);
     const double2* in = reinterpret_cast<const double2*>(in_dev);
     double2* out = reinterpret_cast<double2*>(out_dev);
-    // complex64: columns too small or too large for it go in scaled
-    const long long n_in = op >= 3 ? M.N * k : (op == 2 ? M.Vp : 2 * M.Vp);
-    const long long n_out = op == 2 ? M.Vp : 2 * M.Vp;
-    std::vector<double> sc;
-    DevMem scaled;
-    if (H.prec != HELM_FP64) {
-      std::vector<double> n2;
-      if (op >= 3) M.norms2(in, n2);
-      else M.pair_norms2(in, n_in, n2);
-      sc = Method::column_scales(n2);
-    }
-    if (!sc.empty()) {
-      scaled.alloc((size_t)n_in * sizeof(double2));
-      M.put_scales(sc);
-      if (op >= 3)
-        kern::launch_scale_volumes(scaled.as<double2>(), in, M.scale.as<double>(), M.N, k, H.st);
-      else
-        kern::launch_scale_cols(scaled.as<double2>(), in, M.scale.as<double>(), n_in / k, k, H.st);
-      in = scaled.as<double2>();
-    }
-    switch (op) {
-      case 0: M.apply_P(in, in + M.Vp, out, out + M.Vp); break;
-      case 1: M.apply_A(in, out); break;
-      case 2: M.apply_U(in, out); break;
-      case 3: M.polarized_rhs(in, out, out + M.Vp); break;
-      case 4: M.precondition_source(in, out, out + M.Vp); break;
-    }
-    if (!sc.empty()) {
-      for (double& v : sc) v = 1.0 / v;
-      M.put_scales(sc);
-      kern::launch_scale_cols(out, out, M.scale.as<double>(), n_out / k, k, H.st);
+    auto apply = [&](const double2* x) {
+      switch (op) {
+        case 0: M.apply_P(x, x + M.Vp, out, out + M.Vp); break;
+        case 1: M.apply_A(x, out); break;
+        case 2: M.apply_U(x, out); break;
+        case 3: M.polarized_rhs(x, out, out + M.Vp); break;
+        case 4: M.precondition_source(x, out, out + M.Vp); break;
+      }
+    };
+    if (H.prec == HELM_FP64) {
+      apply(in);
+    } else {
+      // complex64: an operand with columns too small or too large for it is
+      // found while it runs, and then goes in scaled
+      const long long n_in = op >= 3 ? M.N * k : (op == 2 ? M.Vp : 2 * M.Vp);
+      const long long n_out = op == 2 ? M.Vp : 2 * M.Vp;
+      const bool overlap = in < out + n_out && out < in + n_in;   // in is gone afterwards
+      H.range_h[0] = overlap;
+      if (!overlap) {
+        kern::launch_range_check(in, n_in, H.range_h, H.st);
+        apply(in);
+        HELM_HIP(hipGetLastError());
+        HELM_HIP(hipStreamSynchronize(H.st));
+      }
+      if (H.range_h[0]) {
+        std::vector<double> n2;
+        if (op >= 3) M.norms2(in, n2);
+        else M.pair_norms2(in, n_in, n2);
+        std::vector<double> sc = Method::column_scales(n2);
+        if (!sc.empty()) {
+          DevMem scaled;
+          scaled.alloc((size_t)n_in * sizeof(double2));
+          double2* x = scaled.as<double2>();
+          const double* s = M.scale.as<double>();
+          M.put_scales(sc);
+          if (op >= 3) kern::launch_scale_volumes(x, in, s, M.N, k, H.st);
+          else kern::launch_scale_cols(x, in, s, n_in / k, k, H.st);
+          apply(x);
+          for (double& v : sc) v = 1.0 / v;
+          M.put_scales(sc);
+          kern::launch_scale_cols(out, out, s, n_out / k, k, H.st);
+          HELM_HIP(hipStreamSynchronize(H.st));
+        } else if (overlap) {
+          apply(in);
+        }
+      }
     }
     HELM_HIP(hipGetLastError());
     HELM_HIP(hipStreamSynchronize(H.st));

@@ -164,6 +164,9 @@ void launch_scale_cols(double2* y, const double2* x, const double* s, long long 
 // the same for volumes (column c's N elements contiguous)
 void launch_scale_volumes(double2* y, const double2* x, const double* s, long long N, int k,
                           hipStream_t st);
+// odd (host memory) is set to 1 when one of n values is nonzero and outside the
+// magnitudes that complex64 substitutions take as they are
+void launch_range_check(const double2* x, long long n, int* odd, hipStream_t st);
 // scale[c] = the power of two that takes column c's largest |Re|, |Im| to [1, 2),
 // or 1 when complex64 substitutions take it as it is (x: k columns of N
 // contiguous elements); scaled (host memory) is set to 1 when one is not 1

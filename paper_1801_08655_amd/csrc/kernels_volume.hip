@@ -130,6 +130,18 @@ k_gather_volume(LayerDev L, double2* __restrict__ u, int nx, int ny, long long N
 // cube), so both ends keep well away from the format's.
 constexpr double kScaleLow = 0x1p-60, kScaleHigh = 0x1p60;
 
+__device__ __forceinline__ bool out_of_range(double2 v) {
+  const double a = fmax(fabs(v.x), fabs(v.y));
+  return (a > 0.0 && a < kScaleLow) || a > kScaleHigh;
+}
+__global__ void __launch_bounds__(256)
+k_range_check(const double2* __restrict__ x, long long n, int* odd) {
+  bool out = false;
+  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += gridDim.x * 256LL)
+    out = out || out_of_range(x[e]);
+  if (out) *odd = 1;
+}
+
 // whole extended layer, natural order <-> ND order (inspection entry point)
 template <typename T>
 __global__ void k_local_to_X(LayerDev L, const double2* __restrict__ r, int k,
@@ -144,8 +156,7 @@ __global__ void k_local_to_X(LayerDev L, const double2* __restrict__ r, int k,
     const int c = (int)(e / L.n_loc);
     double2 v = r[e];
     if (sizeof(T) == 4) {
-      const double a = fmax(fabs(v.x), fabs(v.y));
-      out = out || (a > 0.0 && a < kScaleLow) || a > kScaleHigh;
+      out = out || out_of_range(v);
       if (scale) v = make_double2(v.x * scale[c], v.y * scale[c]);
     }
     X[(long long)L.nat2nd[sp] * k + c] = from_d2<C>(v);
@@ -658,6 +669,9 @@ void launch_scale_cols(double2* y, const double2* x, const double* s, long long 
 void launch_scale_volumes(double2* y, const double2* x, const double* s, long long N, int k,
                           hipStream_t st) {
   hipLaunchKernelGGL(k_scale_volumes, dim3(grid_for(N), k), dim3(256), 0, st, y, x, s, N);
+}
+void launch_range_check(const double2* x, long long n, int* odd, hipStream_t st) {
+  hipLaunchKernelGGL(k_range_check, dim3(grid_for(n)), dim3(256), 0, st, x, n, odd);
 }
 void launch_column_scale(const double2* x, long long N, int k, double* scale, int* scaled,
                          hipStream_t st) {
