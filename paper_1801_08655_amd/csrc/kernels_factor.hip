@@ -218,10 +218,11 @@ k_orig_entries(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // --------------------------------------------------------------------------
 // panel: LU with partial pivoting of rows [k, s) x columns [k, k+nbf) on a
 // copy, to choose the nbf pivot rows; then D = (pivoted diagonal block)^-1.
-// One workgroup of NT threads per front.  The copy lives in LDS (PR rows at
-// most) when the launch's tallest panel fits, as every leaf front's does,
-// else (PR = 0) in the global panel buffer; only D, the pivots and the
-// permutation leave the kernel.
+// One workgroup of NT threads per front.  Three kernels: the panel in
+// registers (k_panel_regs, every leaf front's), the current column block in
+// registers and the rest in the global panel buffer (k_panel_rb), all of it in
+// that buffer (k_panel, panels taller than the others take); only D, the pivots
+// and the permutation leave a kernel.
 // --------------------------------------------------------------------------
 constexpr int NBMAX = 64;
 constexpr int PB = 8;   // column block of the panel LU
@@ -260,13 +261,13 @@ __device__ __forceinline__ void wave_argmax(double& v, int& idx) {
 }
 
 // D = U^-1 L^-1 of the leading nbf x nbf block of the factored panel P
-// (R rows, column-major, in LDS when LDSP): X = L^-1 by eliminating below each
-// unit pivot, then D = U^-1 X from the last row up.  Wave w of the first four
-// holds rows 16 w .. 16 w + 15 in registers, lane = column; each step passes
-// one row of X through LDS (one barrier) and updates the rows it touches.
+// (R rows, column-major): X = L^-1 by eliminating below each unit pivot, then
+// D = U^-1 X from the last row up.  Wave w of the first four holds rows 16 w ..
+// 16 w + 15 in registers, lane = column; each step passes one row of X through
+// LDS (one barrier) and updates the rows it touches.
 // With X in LDS and its entries dealt to the threads one by one (an integer
 // division each), this was half of a tall panel's time.
-template <typename T, int NT, bool LDSP>
+template <typename T, int NT>
 __device__ __forceinline__ void panel_inverse(const C_t<T>* P, int R, int nbf, int nb,
                                               C_t<T>* D) {
   using C = C_t<T>;
@@ -283,8 +284,7 @@ __device__ __forceinline__ void panel_inverse(const C_t<T>* P, int R, int nbf, i
     for (int i = 0; i < PER; ++i) {
       const int e = t + NT * i, r = e % NBMAX, c = e / NBMAX;
       const bool ok = r < nbf && c < nbf;
-      if (LDSP) v[i] = ok ? P[r + c * R] : czero<C>();
-      else v[i] = ld_or_zero(ok, P + (ok ? r + (long long)c * R : 0));
+      v[i] = ld_or_zero(ok, P + (ok ? r + (long long)c * R : 0));
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -343,7 +343,7 @@ __device__ __forceinline__ void panel_inverse(const C_t<T>* P, int R, int nbf, i
   }
 }
 
-template <typename T, int NT, int PR>
+template <typename T, int NT>
 __global__ void __launch_bounds__(NT)
 k_panel(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
         int k, int nb, void* ws0, void* ws1, void* panel_base,
@@ -351,8 +351,6 @@ k_panel(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
         int* perm_base, const long long* __restrict__ perm_off, FactorStatus* status) {
   using C = C_t<T>;
   constexpr int NW = NT / 64;
-  constexpr bool LDSP = PR > 0;
-  __shared__ C Ps[LDSP ? PR * NBMAX : 1];
   const int a = blockIdx.x;
   const FrontDev f = fronts[ids[a]];
   const int n = f.s + f.b;
@@ -361,7 +359,7 @@ k_panel(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   const int nbf = R < nb ? R : nb;
   const int t = threadIdx.x;
   const C* F = front_ptr<T>(ws0, ws1, f);
-  C* P = LDSP ? Ps : reinterpret_cast<C*>(panel_base) + panel_off[a];
+  C* P = reinterpret_cast<C*>(panel_base) + panel_off[a];
   C* D = reinterpret_cast<C*>(D_base) + panel_off[a];
   int* ipiv = ipiv_base + perm_off[a];
   int* perm = perm_base + perm_off[a];
@@ -396,13 +394,11 @@ k_panel(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
         if (v > best) { best = v; bi = r; }
       }
       wave_argmax(best, bi);
-      if (NW > 1) {
-        if ((t & 63) == 0) { red_v[t >> 6] = best; red_i[t >> 6] = bi; }
-        __syncthreads();
-      }
+      if ((t & 63) == 0) { red_v[t >> 6] = best; red_i[t >> 6] = bi; }
+      __syncthreads();
       if (t == 0) {
-        double bv = NW > 1 ? red_v[0] : best;
-        int bidx = NW > 1 ? red_i[0] : bi;
+        double bv = red_v[0];
+        int bidx = red_i[0];
         for (int w = 1; w < NW; ++w)
           if (red_v[w] > bv || (red_v[w] == bv && red_i[w] < bidx)) {
             bv = red_v[w];
@@ -482,7 +478,7 @@ k_panel(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
     atomicMin(&status->pmin, (unsigned long long)__double_as_longlong(pv_min));
     atomicMax(&status->pmax, (unsigned long long)__double_as_longlong(pv_max));
   }
-  panel_inverse<T, NT, LDSP>(P, R, nbf, nb, D);
+  panel_inverse<T, NT>(P, R, nbf, nb, D);
 }
 
 // Panels of at most 64 RW rows: the panel in registers, a row per lane (its
@@ -647,7 +643,7 @@ k_panel_regs(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
   }
 }
 
-// Tall panels (more rows than the LDS holds): the same blocked LU with
+// Tall panels (more rows than k_panel_regs takes): the same blocked LU with
 // partial pivoting, with the current column block of every row held in
 // registers.  Thread t owns the rows t, t + NT, ... (RPT of them); a column
 // step (pivot search, row exchange, scaling, rank-1 update of the block)
@@ -932,7 +928,7 @@ k_panel_rb(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
     atomicMin(&status->pmin, (unsigned long long)__double_as_longlong(pv_min));
     atomicMax(&status->pmax, (unsigned long long)__double_as_longlong(pv_max));
   }
-  panel_inverse<T, NT, false>(P, R, nbf, nb, D);
+  panel_inverse<T, NT>(P, R, nbf, nb, D);
 }
 
 // --------------------------------------------------------------------------
@@ -1272,8 +1268,8 @@ void launch_panel(const FrontDev* fronts, const int* ids, int n_active, int max_
                   const long long* perm_off, FactorStatus* status, hipStream_t st) {
   if (n_active <= 0) return;
   // threads and panel home from the tallest panel of the launch
-#define HELM_PANEL(NT, PR)                                                          \
-  hipLaunchKernelGGL((k_panel<T, NT, PR>), dim3(n_active), dim3(NT), 0, st,        \
+#define HELM_PANEL(NT)                                                              \
+  hipLaunchKernelGGL((k_panel<T, NT>), dim3(n_active), dim3(NT), 0, st,            \
                      fronts, ids, k, nb, ws0, ws1, panel, panel_off, D, ipiv, perm, \
                      perm_off, status)
 #define HELM_PANEL_RB(NT, RPT, BW)                                                  \
@@ -1304,7 +1300,7 @@ void launch_panel(const FrontDev* fronts, const int* ids, int n_active, int max_
     else if (max_rows <= 2048) HELM_PANEL_RB(1024, 2, PB);
     else if (max_rows <= 4096) HELM_PANEL_RB(1024, 4, PB);
     else if (max_rows <= 6144) HELM_PANEL_RB(1024, 6, PB / 2);
-    else HELM_PANEL(1024, 0);
+    else HELM_PANEL(1024);
   } else {
     if (max_rows <= 64) HELM_PANEL_REGS(1, 4);
     else if (max_rows <= 128) HELM_PANEL_REGS(2, 4);
@@ -1312,7 +1308,7 @@ void launch_panel(const FrontDev* fronts, const int* ids, int n_active, int max_
     else if (max_rows <= 256) HELM_PANEL_REGS(4, 4);
     else if (max_rows <= 1024) HELM_PANEL_RB(256, 4, PB);
     else if (max_rows <= 2048) HELM_PANEL_RB(512, 4, PB);
-    else HELM_PANEL(1024, 0);
+    else HELM_PANEL(1024);
   }
 #undef HELM_PANEL_REGS
 #undef HELM_PANEL_RB
