@@ -559,8 +559,8 @@ void Handle::ensure_workspace(int k) {
   clear_graphs();
   const int L = G.L;
   // one allocation for every layer's buffers: their 4 L separate ones were most
-  // of the first solve's time on a new handle (100^3, 64 columns, complex128:
-  // 4.3 ms of which 1.9 the solve's)
+  // of what a first solve takes besides the solve (one layer of 100^3, 64
+  // columns, complex128: 4.5 -> 3.3 ms, a later solve 2.4)
   std::vector<std::pair<void**, size_t>> at;
   size_t bytes = 0;
   auto add = [&](void*& slot, long long rows) {

@@ -33,7 +33,7 @@ __device__ __forceinline__ C_t<T>* front_ptr(void* ws0, void* ws1, const FrontDe
 // the 64 x 64 tiles on and below the diagonal are assembled and updated: a
 // tile of rows i0.. and columns j0.. is left out when this holds, and whoever
 // reads the block takes the lower of the two mirror entries.  28% of the
-// sweep's tiles at 100^3: complex64 sweep 80 -> 58 ms, complex128 175 -> 127.
+// sweep's tiles at 100^3: complex64 sweep 80 -> 56 ms, complex128 175 -> 124.
 __device__ __forceinline__ bool mirrored(const FrontDev& f, int i0, int j0) {
   return i0 >= f.s && j0 >= i0 + GT;
 }
@@ -1107,11 +1107,13 @@ k_swap_JO(const FrontDev* __restrict__ fronts, const int* __restrict__ ids,
 // wholly in J or in that block, and the mirrored ones of the Schur block,
 // return at once.
 // Bound: the trailing entries streamed from and to HBM once per pivot block
-// (complex64 at 200^3: 5.7 TB; 3.5 TB/s) and the latency of a two-step
-// product between them.  complex64 runs on the split bf16 tile: 1916 -> 1604
-// ms of a 200^3 factorization and 93 -> 80 ms of a 100^3 one against the FP32
-// tile (complex128 at 100^3: 186 -> 175).  Loading the tile's entries before the product needs 200 registers
-// (2 waves per SIMD): 1809 ms; kept at 3 waves it spills: 3688.
+// (complex64 at 200^3: 3.6 TB in 1.13 s, 3.2 TB/s) and the latency of a two-step
+// product between them.  complex64 runs on the split bf16 tile: against the FP32
+// tile, the mirrored tiles still among them, 1916 -> 1604 ms of a 200^3
+// factorization and 93 -> 80 ms of a 100^3 one (complex128 at 100^3: 186 ->
+// 175); now 1129, 56 and 121.  Loading the tile's entries before the product
+// needs 200 registers (2 waves per SIMD): 1809 ms against 1639; kept at 3 waves
+// it spills: 3688.
 // --------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2, 8)))
