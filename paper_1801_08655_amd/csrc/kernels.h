@@ -118,8 +118,8 @@ void launch_gather_volume(const LayerDev& L, double2* u, int nx, int ny,
                           long long N, int k, hipStream_t st);
 // whole extended layer, natural order <-> ND order.  scale (may be null): a
 // power of two per column, multiplied on the way in and divided out on the way
-// out; odd (may be null): set to 1 when a value is nonzero and outside the
-// magnitudes that complex64 substitutions take as they are (host memory).
+// out; odd (host memory; complex64 without scale): set to 1 when a value is
+// nonzero and outside the magnitudes that the substitutions take as they are.
 template <typename T>
 void launch_local_to_X(const LayerDev& L, const double2* r, int k, const double* scale,
                        int* odd, hipStream_t st);

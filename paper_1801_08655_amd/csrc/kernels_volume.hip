@@ -142,8 +142,9 @@ k_range_check(const double2* __restrict__ x, long long n, int* odd) {
   if (out) *odd = 1;
 }
 
-// whole extended layer, natural order <-> ND order (inspection entry point)
-template <typename T>
+// whole extended layer, natural order <-> ND order (inspection entry point);
+// SCALED: columns times, and divided by, scale[column]
+template <typename T, bool SCALED>
 __global__ void k_local_to_X(LayerDev L, const double2* __restrict__ r, int k,
                              const double* __restrict__ scale, int* odd) {
   using C = C_t<T>;
@@ -155,15 +156,13 @@ __global__ void k_local_to_X(LayerDev L, const double2* __restrict__ r, int k,
     const long long sp = e % L.n_loc;
     const int c = (int)(e / L.n_loc);
     double2 v = r[e];
-    if (sizeof(T) == 4) {
-      out = out || out_of_range(v);
-      if (scale) v = make_double2(v.x * scale[c], v.y * scale[c]);
-    }
+    if (SCALED) v = make_double2(v.x * scale[c], v.y * scale[c]);
+    else if (sizeof(T) == 4) out = out || out_of_range(v);
     X[(long long)L.nat2nd[sp] * k + c] = from_d2<C>(v);
   }
-  if (sizeof(T) == 4 && odd && out) *odd = 1;
+  if (!SCALED && sizeof(T) == 4 && out) *odd = 1;
 }
-template <typename T>
+template <typename T, bool SCALED>
 __global__ void k_X_to_local(LayerDev L, double2* __restrict__ w, int k,
                              const double* __restrict__ scale) {
   using C = C_t<T>;
@@ -174,7 +173,7 @@ __global__ void k_X_to_local(LayerDev L, double2* __restrict__ w, int k,
     const long long sp = e % L.n_loc;
     const int c = (int)(e / L.n_loc);
     double2 v = to_d2(X[(long long)L.nat2nd[sp] * k + c]);
-    if (sizeof(T) == 4 && scale) v = make_double2(v.x / scale[c], v.y / scale[c]);
+    if (SCALED) v = make_double2(v.x / scale[c], v.y / scale[c]);
     w[e] = v;
   }
 }
@@ -603,14 +602,20 @@ void launch_gather_volume(const LayerDev& L, double2* u, int nx, int ny,
 template <typename T>
 void launch_local_to_X(const LayerDev& L, const double2* r, int k, const double* scale,
                        int* odd, hipStream_t st) {
-  hipLaunchKernelGGL(k_local_to_X<T>, dim3(grid_for((long long)L.n_loc * k)), dim3(256),
-                     0, st, L, r, k, scale, odd);
+  const dim3 grid(grid_for((long long)L.n_loc * k));
+  if (scale)
+    hipLaunchKernelGGL((k_local_to_X<T, true>), grid, dim3(256), 0, st, L, r, k, scale, odd);
+  else
+    hipLaunchKernelGGL((k_local_to_X<T, false>), grid, dim3(256), 0, st, L, r, k, scale, odd);
 }
 template <typename T>
 void launch_X_to_local(const LayerDev& L, double2* w, int k, const double* scale,
                        hipStream_t st) {
-  hipLaunchKernelGGL(k_X_to_local<T>, dim3(grid_for((long long)L.n_loc * k)), dim3(256),
-                     0, st, L, w, k, scale);
+  const dim3 grid(grid_for((long long)L.n_loc * k));
+  if (scale)
+    hipLaunchKernelGGL((k_X_to_local<T, true>), grid, dim3(256), 0, st, L, w, k, scale);
+  else
+    hipLaunchKernelGGL((k_X_to_local<T, false>), grid, dim3(256), 0, st, L, w, k, scale);
 }
 template <typename T>
 void launch_jump(const LayerDev& L, const JumpTerms& t, const double2* B, int bottom, int nx,
