@@ -228,6 +228,10 @@ struct Handle {
     auto each = [&](auto&& f) {
       for (int c = 0; c < k; c += cols) f((long long)c * L.n_loc, std::min(cols, k - c));
     };
+    auto wait = [&] {
+      HELM_HIP(hipGetLastError());
+      HELM_HIP(hipStreamSynchronize(st));
+    };
     auto solve = [&](bool scaled) {
       each([&](long long at, int n) {
         if (scaled) kern::launch_column_scale(r + at, L.n_loc, n, scale, range_h + 1, st);
@@ -237,20 +241,24 @@ struct Handle {
         if (scaled) kern::launch_column_scale(r + at, L.n_loc, n, scale, range_h + 1, st);
         kern::launch_X_to_local<T>(L, w + at, n, scaled ? scale : nullptr, st);
       });
-      HELM_HIP(hipGetLastError());
-      HELM_HIP(hipStreamSynchronize(st));
+      wait();
     };
     const long long n = (long long)L.n_loc * k;
-    const bool overlap = r < w + n && w < r + n;   // r is gone afterwards
+    const bool overlap = r < w + n && w < r + n;   // the solve overwrites r
     if (c64) range_h[0] = range_h[1] = 0;
-    solve(c64 && overlap);
-    if (!c64 || overlap || !range_h[0]) return;
+    if (c64 && overlap) {
+      kern::launch_range_check(r, n, range_h, st);
+      wait();
+    }
+    const bool first = !(c64 && overlap && range_h[0]);
+    if (first) solve(false);
+    if (!c64 || !range_h[0] || (first && overlap)) return;
     each([&](long long at, int m) {
       kern::launch_column_scale(r + at, L.n_loc, m, scale, range_h + 1, st);
     });
-    HELM_HIP(hipGetLastError());
-    HELM_HIP(hipStreamSynchronize(st));
+    wait();
     if (range_h[1]) solve(true);
+    else if (!first) solve(false);
   }
   int* range_h = nullptr;   // host memory that local_solve's kernels write (complex64)
   template <typename T> void run_layers_t(const LayerSet& set, int k, const LayerDev* ld,

@@ -169,7 +169,8 @@ void launch_scale_volumes(double2* y, const double2* x, const double* s, long lo
 void launch_range_check(const double2* x, long long n, int* odd, hipStream_t st);
 // scale[c] = the power of two that takes column c's largest |Re|, |Im| to [1, 2),
 // or 1 when complex64 substitutions take it as it is (x: k columns of N
-// contiguous elements); scaled (host memory) is set to 1 when one is not 1
+// contiguous elements); scaled (host memory) is set to 1 when one is not 1.
+// scale has room for k (2 + N / 1024) values, the first k of which count.
 void launch_column_scale(const double2* x, long long N, int k, double* scale, int* scaled,
                          hipStream_t st);
 void launch_add(double2* y, const double2* x, const double2* z, long long n,

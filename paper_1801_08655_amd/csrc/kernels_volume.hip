@@ -177,19 +177,27 @@ __global__ void k_X_to_local(LayerDev L, double2* __restrict__ w, int k,
     w[e] = v;
   }
 }
-// one block per column
+// largest |Re|, |Im| of each column, a part per block: part[c gridDim.x + block]
 __global__ void __launch_bounds__(256)
-k_column_scale(const double2* __restrict__ x, long long N, double* __restrict__ scale,
-               int* scaled) {
-  const double2* col = x + (long long)blockIdx.x * N;
+k_column_max(const double2* __restrict__ x, long long N, double* __restrict__ part) {
+  const double2* col = x + (long long)blockIdx.y * N;
   double m = 0.0;
-  for (long long i = threadIdx.x; i < N; i += 256) m = fmax(m, fmax(fabs(col[i].x), fabs(col[i].y)));
+  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < N; i += gridDim.x * 256LL)
+    m = fmax(m, fmax(fabs(col[i].x), fabs(col[i].y)));
   for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
   __shared__ double wm[4];
   if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
   __syncthreads();
+  if (threadIdx.x == 0)
+    part[(long long)blockIdx.y * gridDim.x + blockIdx.x] =
+        fmax(fmax(wm[0], wm[1]), fmax(wm[2], wm[3]));
+}
+__global__ void __launch_bounds__(64)
+k_column_scale(const double* __restrict__ part, int parts, double* __restrict__ scale,
+               int* scaled) {
+  double m = (int)threadIdx.x < parts ? part[(long long)blockIdx.x * parts + threadIdx.x] : 0.0;
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
   if (threadIdx.x) return;
-  m = fmax(fmax(wm[0], wm[1]), fmax(wm[2], wm[3]));
   const bool keep = !(m > 0.0) || isinf(m) || (m >= kScaleLow && m <= kScaleHigh);
   // (an inverse power of two stays a normal number)
   scale[blockIdx.x] = keep ? 1.0 : ldexp(1.0, -max(ilogb(m), -1000));
@@ -680,7 +688,10 @@ void launch_range_check(const double2* x, long long n, int* odd, hipStream_t st)
 }
 void launch_column_scale(const double2* x, long long N, int k, double* scale, int* scaled,
                          hipStream_t st) {
-  hipLaunchKernelGGL(k_column_scale, dim3(k), dim3(256), 0, st, x, N, scale, scaled);
+  const int parts = (int)std::min<long long>(64, 1 + N / 1024);
+  double* part = scale + k;
+  hipLaunchKernelGGL(k_column_max, dim3(parts, k), dim3(256), 0, st, x, N, part);
+  hipLaunchKernelGGL(k_column_scale, dim3(k), dim3(64), 0, st, part, parts, scale, scaled);
 }
 void launch_add(double2* y, const double2* x, const double2* z, long long n,
                 hipStream_t st) {

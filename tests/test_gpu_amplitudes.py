@@ -97,3 +97,23 @@ def test_refined_solves(solver, k, e):
     got, b = solver.solve_points(nodes, sc, info=True)
     assert b["rhs_ir_steps"] == a["rhs_ir_steps"]
     _check(got, want, sc)
+
+
+@pytest.mark.parametrize("k", [2, 7])
+def test_tiny_tails_in_an_ordinary_column(solver, k):
+    """Values far below the column's own size do not have the column scaled, in
+    place or not: bit for bit the answer of any ordinary call's path."""
+    lo, hi = solver.layer_info(1)[2:]
+    nx, ny, _ = solver.n
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    r = torch.randn((k, hi - lo + 1, ny, nx), dtype=torch.complex128, device="cuda", generator=g)
+    z = r.clone()
+    z[:, 0] = 0
+    r[:, 0] = 1e-30   # (vanishes beside the rest in complex64)
+    want = solver.layer_solve(1, z)
+    got = solver.layer_solve(1, r)
+    d = torch.linalg.vector_norm(got - want)
+    assert d <= 1e-12 * torch.linalg.vector_norm(want)
+    w = r.clone()
+    assert torch.equal(solver.layer_solve_noalloc(1, w, w), got)
