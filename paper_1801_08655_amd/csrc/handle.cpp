@@ -115,7 +115,8 @@ void Handle::init_device(const helm_options& o) {
   }
   prec = o.precision == HELM_FP64 ? HELM_FP64 : HELM_MIXED;
   elem = prec == HELM_FP64 ? 16 : 8;
-  if (prec != HELM_FP64) HELM_HIP(hipHostMalloc((void**)&range_h, 2 * sizeof(int)));
+  if (prec != HELM_FP64)
+    HELM_HIP(hipHostMalloc((void**)&range_h, 2 * sizeof(int), hipHostMallocCoherent));
   set_profile(o.flags);
 }
 
@@ -558,9 +559,12 @@ void Handle::ensure_workspace(int k) {
   HELM_HIP(hipStreamSynchronize(st));
   clear_graphs();
   const int L = G.L;
-  // one allocation for every layer's buffers: their 4 L separate ones were most
+  // One allocation for every layer's buffers: their 4 L separate ones were most
   // of what a first solve takes besides the solve (one layer of 100^3, 64
-  // columns, complex128: 4.5 -> 3.3 ms, a later solve 2.4)
+  // columns, complex128: 4.5 -> 3.3 ms, a later solve 2.4).  Below 8 MB in all
+  // they stay separate: small allocations come from chunks that are there, one
+  // of 2 to 8 MB does not (18^3 complex64, 24 columns, 5 MB: 629 us against 995;
+  // 25^3, 14 MB: 1357 against 686).
   std::vector<std::pair<void**, size_t>> at;
   size_t bytes = 0;
   auto add = [&](void*& slot, long long rows) {
@@ -575,8 +579,15 @@ void Handle::ensure_workspace(int k) {
     add(layers_h[l].Ub[1], P.ub_rows[1]);
   }
   kcap = 0;
-  work.alloc(bytes);
-  for (auto& a : at) *a.first = static_cast<char*>(work.p) + a.second;
+  work.clear();
+  const size_t step = bytes < ((size_t)8 << 20) ? 1 : at.size();
+  for (size_t i = 0; i < at.size(); i += step) {
+    const size_t end = i + step < at.size() ? at[i + step].second : bytes;
+    work.emplace_back(new DevMem);
+    work.back()->alloc(end - at[i].second);
+    for (size_t j = i; j < i + step; ++j)
+      *at[j].first = static_cast<char*>(work.back()->p) + (at[j].second - at[i].second);
+  }
   kcap = k;
   upload_layers();
 }

@@ -130,7 +130,7 @@ struct Handle {
 
   // solve workspace (per layer) for up to kcap columns
   int kcap = 0;
-  DevMem work;                   // every layer's X, Wt and update buffers
+  std::vector<std::unique_ptr<DevMem>> work;   // every layer's X, Wt and update buffers
   std::map<std::vector<int>, std::unique_ptr<LayerSet>> sets;
   DevMem scratch;                // split-K partial products
   // captured substitution sequences: (set, k) -> executable graph
